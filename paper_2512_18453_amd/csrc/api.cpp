@@ -220,7 +220,9 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
             if (int err = launch_output_transform_few(t, Vbuf, Mbuf, ys, g, dtype, flags, stream)) return hip_result(err);
             continue;
         }
-        if (int err = launch_input_transform(t, xs, Vbuf, g, dtype, stream)) return hip_result(err);
+        // (kDefaultSlabBytes: the size of the last-level cache)
+        const bool stream_x = !fused && (size_t)nb * C * H * W * es + v_bytes(g, dtype) + m_bytes(g, dtype, flags) > kDefaultSlabBytes;
+        if (int err = launch_input_transform(t, xs, Vbuf, g, dtype, stream, stream_x)) return hip_result(err);
         if (fused) {
             if (int err = launch_fused_contract_output(t, U, Vbuf, ys, g, dtype, flags, stream)) return hip_result(err);
             continue;

@@ -102,8 +102,9 @@ int conv2d_with_workspace(const nova_transforms *t, const void *x, const void *U
 
 int launch_filter_transform(const nova_transforms *t, const void *w, int K, int C, int dtype,
                             void *U, void *stream);
+// stream_x: x, V and what follows V exceed the last-level cache together, so x is better not kept in it
 int launch_input_transform(const nova_transforms *t, const void *x, void *V, const Geometry &g,
-                           int dtype, void *stream);
+                           int dtype, void *stream, bool stream_x = false);
 int launch_contract(const nova_transforms *t, const void *U, const void *V, void *M,
                     const Geometry &g, int dtype, int flags, void *stream);
 int launch_output_transform(const nova_transforms *t, const void *M, void *y, const Geometry &g,
