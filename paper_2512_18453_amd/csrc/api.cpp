@@ -326,13 +326,21 @@ extern "C" int nova_winograd_conv2d_int8(const nova_transforms *t, const void *x
     char *ws = (char *)workspace;
     void *V = ws + off[0], *Vq = ws + off[1], *Mf = ws + off[3];
     float *v_scale = (float *)(ws + off[2]);
-    if (int err = launch_input_transform(t, x, V, g, dtype, stream)) return hip_result(err);
-    const long long elements = (long long)g.n * g.n * g.c_blocks * g.T * kChanBlock;
     const bool pos = mode == NOVA_INT8_PER_POSITION;
-    if (int err = launch_quantize_int8(V, Vq, v_scale, elements, g.n * g.n, (int)g.T, pos ? g.n * g.n : 1, pos ? 2 : 0, dtype,
-                                       stream))
-        return hip_result(err);
-    if (int err = launch_contract_int8(Uq, Vq, Mf, u_scales, v_scale, mode, 1, g, stream)) return hip_result(err);
+    // Points in the paired order: the input transform leaves the partial maxima of |V| where the codes would be and the
+    // contraction quantises V as it reads it.  Otherwise (or if they did not fit): the passes one by one.
+    const int n_part = t->symmetric ? input_maxima_count(g, dtype, pos) : -1;
+    if (n_part > 0 && (size_t)n_part * (pos ? g.n * g.n : 1) * sizeof(float) <= off[2] - off[1]) {
+        if (int err = launch_input_transform_maxima(t, x, V, (float *)Vq, pos, g, dtype, stream)) return hip_result(err);
+        if (int err = launch_contract_int8_of_v(Uq, V, Mf, u_scales, (float *)Vq, n_part, mode, g, dtype, stream)) return hip_result(err);
+    } else {
+        if (int err = launch_input_transform(t, x, V, g, dtype, stream)) return hip_result(err);
+        const long long elements = (long long)g.n * g.n * g.c_blocks * g.T * kChanBlock;
+        if (int err = launch_quantize_int8(V, Vq, v_scale, elements, g.n * g.n, (int)g.T, pos ? g.n * g.n : 1, pos ? 2 : 0, dtype,
+                                           stream))
+            return hip_result(err);
+        if (int err = launch_contract_int8(Uq, Vq, Mf, u_scales, v_scale, mode, 1, g, stream)) return hip_result(err);
+    }
     // the de-quantised products are binary32 whatever the storage format: the output transform's binary32-M path
     if (int err = launch_output_transform(t, Mf, y, g, dtype, flags, stream)) return hip_result(err);
     return NOVA_OK;

@@ -113,6 +113,7 @@ struct TileBlock {
     static constexpr int RS = N >= 8 ? 2 : 1;                   // threads that share the transform rows of one tile and word
     static constexpr int TB = sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8);
     static constexpr int THREADS = TB * GP * RS;
+    static constexpr int WAVES_PER_XI = TB * GP / 64;
     static constexpr int TILE_PAD = 2;
     // Pitches in words.  The window reads take two pixels (8 bytes) per lane, 32 lanes (two tiles' 16 windows, or
     // one tile's 32) per phase: with a window pitch of 2 * odd 8-byte units (binary32: odd) and a tile pitch of
@@ -164,10 +165,17 @@ template <bool STREAM> __device__ __forceinline__ unsigned element_bits(const f1
 }
 #undef NOVA_LOAD_X
 
+// What the transform leaves about the largest magnitude of V, for a later quantisation (partial maxima, in the
+// storage format's rounding -- rounding is monotonic, so the largest rounded value is the rounded largest):
+//   kMaxTensor     one per wave
+//   kMaxPosition   four per wave and position (16 lanes each)
+enum { kMaxNone = 0, kMaxTensor = 1, kMaxPosition = 2 };
+
 // Rows [LO, HI) of the transform of the CPT windows in `win`, stored to V as they are finished.
-template <int N, typename T, bool SYM, int LO, int HI>
-__device__ __forceinline__ void transform_window(const unsigned *win, T *v_block, size_t xi_stride, unsigned lane_off,
-                                                 const InCoef<N> &coef)
+// top (kMaxTensor): running maximum; partials, n_part (kMaxPosition): where this wave's go, entries per position.
+template <int N, typename T, bool SYM, int MAXIMA, int LO, int HI>
+__device__ __forceinline__ void transform_window(const unsigned *win, T *v_block, size_t xi_stride, unsigned lane_off, bool active,
+                                                 const InCoef<N> &coef, float &top, float *partials, int n_part)
 {
     constexpr int CPT = 4 / (int)sizeof(T);
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -215,19 +223,34 @@ __device__ __forceinline__ void transform_window(const unsigned *win, T *v_block
             } else {
                 word = __float_as_uint(o[0][j]);
             }
-            *reinterpret_cast<NOVA_GLOBAL unsigned *>(plane_element(plane, lane_off)) = word;
+            if (MAXIMA == kMaxNone || active) *reinterpret_cast<NOVA_GLOBAL unsigned *>(plane_element(plane, lane_off)) = word;
             plane = uniform_pointer(plane + xi_stride);
+            if constexpr (MAXIMA == kMaxTensor) {
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) top = fmaxf(top, fabsf(o[c][j]));
+            }
+            if constexpr (MAXIMA == kMaxPosition) {
+                float m = fabsf(o[0][j]);
+                if constexpr (CPT == 2) m = fmaxf(m, fabsf(o[CPT - 1][j]));
+                // maximum over 16 lanes (row_ror 8, 4, 2, 1); fmaxf drops a NaN
+                m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x128, 0xf, 0xf, true)));
+                m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x124, 0xf, 0xf, true)));
+                m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x122, 0xf, 0xf, true)));
+                m = fmaxf(m, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(m), 0x121, 0xf, 0xf, true)));
+                if ((threadIdx.x & 15) == 0)
+                    partials[(size_t)(i * N + j) * n_part + (threadIdx.x >> 4 & 3)] = fmaxf(0.0f, (float)round_twice(m, (T *)nullptr));
+            }
         }
     }
 }
 
 // Groups of tiles: a row of row_tiles consecutive t (the whole batch, or one tile row of an image) is cut into
 // groups_per_row groups of `per` tiles.
-template <int N, int R, typename T, bool SYM, bool STREAM>
+template <int N, int R, typename T, bool SYM, bool STREAM, int MAXIMA>
 __global__ void __launch_bounds__((TileBlock<N, T>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
 input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H, int W, int tiles_h, int tiles_w,
                        int c_blocks, unsigned t_groups, int row_tiles, int groups_per_row, int per, int Ttot, long long x_elems,
-                       int by_element, InCoef<N> coef)
+                       int by_element, float *partials, int n_part, InCoef<N> coef)
 {
     using B = TileBlock<N, T>;
     constexpr int M = N - R + 1;                 // outputs per tile side = tile stride
@@ -377,12 +400,23 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
     T *v_block = V + ((size_t)cb * Ttot + t0) * kChanBlock;
     const size_t xi_stride = (size_t)c_blocks * Ttot * kChanBlock;
     const unsigned lane_off = (unsigned)(j * kChanBlock + g * CPT) * (unsigned)sizeof(T);
-    if (j >= count) return;
+    const bool active = j < count;
+    if constexpr (MAXIMA == kMaxNone)
+        if (!active) return;                     // (for the maxima every lane stays: it holds the group's last tile)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float top = 0.0f;
+    float *mine = partials;
+    if constexpr (MAXIMA == kMaxPosition) mine += ((size_t)blockIdx.x * B::WAVES_PER_XI + wave % B::WAVES_PER_XI) * 4;
     if constexpr (B::RS == 1) {
-        transform_window<N, T, SYM, 0, N>(win, v_block, xi_stride, lane_off, coef);
+        transform_window<N, T, SYM, MAXIMA, 0, N>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
     } else {
-        if (half == 0) transform_window<N, T, SYM, 0, SP>(win, v_block, xi_stride, lane_off, coef);
-        else           transform_window<N, T, SYM, SP, N>(win, v_block, xi_stride, lane_off, coef);
+        if (half == 0) transform_window<N, T, SYM, MAXIMA, 0, SP>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
+        else           transform_window<N, T, SYM, MAXIMA, SP, N>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
+    }
+    if constexpr (MAXIMA == kMaxTensor) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+        if ((tid & 63) == 0) mine[(size_t)blockIdx.x * (B::THREADS / 64) + wave] = (float)round_twice(top, (T *)nullptr);
     }
 }
 
@@ -402,8 +436,19 @@ static void fill_in_coef(const nova_transforms *t, InCoef<N> &k)
         }
 }
 
+// partial maxima (per position with kMaxPosition) of a launch over all of g; -1: more than an int holds
+template <int N, typename T>
+static int maxima_count(const Geometry &g, int maxima)
+{
+    using B = TileBlock<N, T>;
+    const long long blocks = (g.T + B::TB - 1) / B::TB * g.c_blocks;
+    const long long count = maxima == kMaxTensor ? blocks * (B::THREADS / 64) : maxima == kMaxPosition ? blocks * B::WAVES_PER_XI * 4 : 0;
+    return count > 0x7fffffffLL ? -1 : (int)count;
+}
+
 template <int N, int R, typename T>
-static int launch_it(const nova_transforms *t, const void *x, void *V, const Geometry &g, bool stream_x, hipStream_t stream)
+static int launch_it(const nova_transforms *t, const void *x, void *V, const Geometry &g, bool stream_x, int maxima, float *partials,
+                     hipStream_t stream)
 {
     using B = TileBlock<N, T>;
     InCoef<N> coef;
@@ -413,11 +458,15 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     // streaming hint on x a group keeps to one tile row instead: what it shares with a neighbour is not
     // found in the cache again (56 x 56 x 256 channels, batch 32, F(8,3), whole call: 110 us with rows and the
     // hint, 114 with the hint alone, 116 with neither; the transform alone 34 / 39 / 29 us).
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, false> : input_transform_kernel<N, R, T, false, false>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, false, kMaxNone>;
+    if (maxima != kMaxNone && !t->symmetric) return (int)hipErrorInvalidValue;
+    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, false, kMaxTensor>;
+    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, false, kMaxPosition>;
     bool rows = false;
     if constexpr (N >= 8 && sizeof(T) == 2)
-        if (stream_x && t->symmetric && g.tiles_w > B::TB * 3 / 4 && g.tiles_w <= B::TB) {
-            kern = input_transform_kernel<N, R, T, true, true>;
+        if (stream_x && maxima == kMaxNone && t->symmetric && g.tiles_w > B::TB * 3 / 4 && g.tiles_w <= B::TB) {
+            kern = input_transform_kernel<N, R, T, true, true, kMaxNone>;
             rows = true;
         }
     const int row_tiles = rows ? g.tiles_w : (int)g.T;
@@ -430,30 +479,57 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     const int by_element = x_elems < N - R + 1 || (long long)kChanBlock * g.H * g.W >= (1LL << 30) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, g.c_blocks, (unsigned)t_groups, row_tiles, groups_per_row, per, (int)g.T, x_elems,
-                       by_element, coef);
+                       by_element, partials, maxima_count<N, T>(g, maxima), coef);
     return (int)hipGetLastError();
+}
+
+static int launch_it_any(const nova_transforms *t, const void *x, void *V, const Geometry &g, int dtype, bool stream_x, int maxima,
+                         float *partials, hipStream_t s)
+{
+    const bool h = dtype == NOVA_F16;
+#define NOVA_IT(N, R) (h ? launch_it<N, R, f16>(t, x, V, g, stream_x, maxima, partials, s) \
+                         : launch_it<N, R, float>(t, x, V, g, stream_x, maxima, partials, s))
+    if (t->r == 3) {
+        switch (t->n) {
+        case 4: return NOVA_IT(4, 3);
+        case 6: return NOVA_IT(6, 3);
+        case 8: return NOVA_IT(8, 3);
+        case 10: return NOVA_IT(10, 3);
+        }
+    } else if (t->r == 5) {
+        switch (t->n) {
+        case 6: return NOVA_IT(6, 5);
+        case 8: return NOVA_IT(8, 5);
+        case 10: return NOVA_IT(10, 5);
+        }
+    }
+#undef NOVA_IT
+    return (int)hipErrorInvalidValue;
 }
 
 int launch_input_transform(const nova_transforms *t, const void *x, void *V, const Geometry &g,
                            int dtype, void *stream, bool stream_x)
 {
-    hipStream_t s = (hipStream_t)stream;
+    return launch_it_any(t, x, V, g, dtype, stream_x, kMaxNone, nullptr, (hipStream_t)stream);
+}
+
+int input_maxima_count(const Geometry &g, int dtype, bool per_position)
+{
+    const int maxima = per_position ? kMaxPosition : kMaxTensor;
     const bool h = dtype == NOVA_F16;
-    if (t->r == 3) {
-        switch (t->n) {
-        case 4: return h ? launch_it<4, 3, f16>(t, x, V, g, stream_x, s) : launch_it<4, 3, float>(t, x, V, g, stream_x, s);
-        case 6: return h ? launch_it<6, 3, f16>(t, x, V, g, stream_x, s) : launch_it<6, 3, float>(t, x, V, g, stream_x, s);
-        case 8: return h ? launch_it<8, 3, f16>(t, x, V, g, stream_x, s) : launch_it<8, 3, float>(t, x, V, g, stream_x, s);
-        case 10: return h ? launch_it<10, 3, f16>(t, x, V, g, stream_x, s) : launch_it<10, 3, float>(t, x, V, g, stream_x, s);
-        }
-    } else if (t->r == 5) {
-        switch (t->n) {
-        case 6: return h ? launch_it<6, 5, f16>(t, x, V, g, stream_x, s) : launch_it<6, 5, float>(t, x, V, g, stream_x, s);
-        case 8: return h ? launch_it<8, 5, f16>(t, x, V, g, stream_x, s) : launch_it<8, 5, float>(t, x, V, g, stream_x, s);
-        case 10: return h ? launch_it<10, 5, f16>(t, x, V, g, stream_x, s) : launch_it<10, 5, float>(t, x, V, g, stream_x, s);
-        }
+    switch (g.n) {
+    case 4: return h ? maxima_count<4, f16>(g, maxima) : maxima_count<4, float>(g, maxima);
+    case 6: return h ? maxima_count<6, f16>(g, maxima) : maxima_count<6, float>(g, maxima);
+    case 8: return h ? maxima_count<8, f16>(g, maxima) : maxima_count<8, float>(g, maxima);
+    case 10: return h ? maxima_count<10, f16>(g, maxima) : maxima_count<10, float>(g, maxima);
     }
-    return (int)hipErrorInvalidValue;
+    return -1;
+}
+
+int launch_input_transform_maxima(const nova_transforms *t, const void *x, void *V, float *partials, bool per_position,
+                                  const Geometry &g, int dtype, void *stream)
+{
+    return launch_it_any(t, x, V, g, dtype, false, per_position ? kMaxPosition : kMaxTensor, partials, (hipStream_t)stream);
 }
 
 // ---- Few input channels (C <= 4): V in the compact layout Vc [n*n][T][4] that the few-channel

@@ -105,6 +105,11 @@ int launch_filter_transform(const nova_transforms *t, const void *w, int K, int 
 // stream_x: x, V and what follows V exceed the last-level cache together, so x is better not kept in it
 int launch_input_transform(const nova_transforms *t, const void *x, void *V, const Geometry &g,
                            int dtype, void *stream, bool stream_x = false);
+// The same, leaving partial maxima of |V| (points in the paired order only): input_maxima_count of them, per position
+// with per_position ([position][count]); -1: the shape has too many.
+int input_maxima_count(const Geometry &g, int dtype, bool per_position);
+int launch_input_transform_maxima(const nova_transforms *t, const void *x, void *V, float *partials, bool per_position,
+                                  const Geometry &g, int dtype, void *stream);
 int launch_contract(const nova_transforms *t, const void *U, const void *V, void *M,
                     const Geometry &g, int dtype, int flags, void *stream);
 int launch_output_transform(const nova_transforms *t, const void *M, void *y, const Geometry &g,
@@ -134,6 +139,9 @@ int launch_quantize_int8(const void *src, void *dst, void *scales, long long ele
                          int n_scales, int kind, int dtype, void *stream);
 int launch_contract_int8(const void *Uq, const void *Vq, void *Mo, const void *u_scales, const void *v_scale,
                          int scale_kind, int dequantise, const Geometry &g, void *stream);
+// ... of V in its storage format, quantised on the way in; partials (n_part maxima, per position with kind 2) are overwritten
+int launch_contract_int8_of_v(const void *Uq, const void *V, void *Mo, const void *u_scales, float *partials, int n_part,
+                              int scale_kind, const Geometry &g, int dtype, void *stream);
 int launch_relu_maxpool2x2(const void *in, void *out, int N, int C, int H, int W, int dtype,
                            void *stream);
 }  // namespace nova
