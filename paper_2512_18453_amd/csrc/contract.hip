@@ -5,13 +5,15 @@
 // (rows x 32-channel) operand tile is one contiguous piece of memory and every lane's MFMA
 // fragment is a 16-byte read.
 //
-// binary16 path: v_mfma_f32_32x32x16_f16, binary32 accumulation, two kernels.
-//   streaming kernel (C = 64, 128 or 256 and K a multiple of 64; further down): U stays in
-//     registers, V streams once through an LDS ring filled by direct global->LDS loads;
-//   tiled kernel (everything else): a workgroup of 4 waves owns a BM x BN tile of one M[xi]; the
-//     channel loop moves 32 channels per step through double-buffered LDS (rows padded from 64 to
-//     80 bytes, which spreads the 16 lanes of a 128-bit read phase over all 64 banks), global loads
-//     for step s+1 are issued before the MFMAs of step s.
+// binary16 path: v_mfma_f32_32x32x16_f16, binary32 accumulation, two kernels with the same order of summation
+// (ascending channels, 16 per instruction), so that which of them runs does not show in M:
+//   streaming kernel (large layers with C = 64, 128 or 256; further down): U stays in registers, V streams once
+//     through an LDS ring filled by direct global->LDS loads;
+//   tiled kernel (everything else): a ring of LDS stages of 32 channels, filled the same way.
+// Both store M a whole 128-byte row of 32 output channels per half-wave: 16-byte stores of four neighbouring
+// channels per lane, 32 bytes of each row at a time, moved the same bytes in 5-30 % more time (streaming kernel,
+// us: 256 -> 256 @14x14 batch 256 binary16 M 28.5 -> 22.8, binary32 30.0 -> 26.4; 128 -> 128 @28x28 batch 128
+// 28.0 -> 24.8; 256 -> 256 @56x56 batch 32 40.7 -> 39.3).
 // binary32 path: same layouts, plain FMA tiles (validation path, not tuned).
 #include <type_traits>
 
@@ -35,120 +37,122 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 
-constexpr int kRowHalves = 40;   // LDS row pitch of a 32-channel operand row, in binary16 units (80 B)
-
-template <int BM, int BN, int WM, int WN, typename MT>
-__global__ void __launch_bounds__(256)
-contract_f16_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *__restrict__ Mo,
-                    int T, int Tp, int Kp, int c_blocks, int k_blocks, int row_blocks, int col_blocks)
+// s_waitcnt vmcnt(X): at most X of the wave's vector-memory operations are outstanding afterwards (they retire
+// in the order issued)
+template <int X>
+__device__ __forceinline__ void stream_wait()
 {
-    constexpr int MB = BM / WM / 32;          // 32x32 MFMA blocks per wave, rows
-    constexpr int NB = BN / WN / 32;          // and columns
-    constexpr int A_SEGS = BM * 4 / 256;      // 16-byte segments per thread and stage
-    constexpr int B_SEGS = (BN * 4 + 255) / 256;
-    static_assert(WM * WN == 4 && BM % (WM * 32) == 0 && BN % (WN * 32) == 0, "tile shape");
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(X < 63 ? X : 63) : "memory");
+}
 
-    __shared__ __align__(16) f16 lds_a[2][BM * kRowHalves];
-    __shared__ __align__(16) f16 lds_b[2][BN * kRowHalves];
+// Tiled variant.  WM x WN waves own BM tiles x BN output channels of one M[xi].  The channel loop takes 32
+// channels per stage from a ring of S stages in LDS, filled by direct global->LDS loads S - 1 stages ahead: a
+// stage costs one round trip to memory only where the loop begins (with one stage in flight, as before,
+// every 32 channels cost one: 16 us for 512 channels on a 14 x 14 image however few tiles).  A stage is BM rows
+// of V and BN rows of U, 64 bytes each, XOR-swizzled by 16-byte slot like the streaming kernel's; a wave-wide
+// load moves 16 rows.  Rows beyond the tensors are clamped to the last valid row (their products are
+// never stored); past the last channel block loads are still issued, so that the wait counts are constants, but
+// every lane rereads the same 16 bytes: one cached request.  Summation order per product: ascending channels in steps of 16, as in the
+// streaming kernel -- M does not depend on which kernel or tile shape formed it.
+template <int BM, int BN, int WM, int WN, int S, typename MT>
+__global__ void __launch_bounds__(64 * WM * WN)
+contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *__restrict__ Mo,
+                     int T, int Tp, int Kp, int c_blocks, int k_blocks, int row_blocks, int col_blocks)
+{
+    constexpr int WAVES = WM * WN;
+    constexpr int MB = BM / WM / 32, NB = BN / WN / 32;     // 32 x 32 blocks per wave
+    constexpr int GROUPS = (BM + BN) / 16;                  // wave-wide loads per stage
+    constexpr int NP = (GROUPS + WAVES - 1) / WAVES;        // ... per wave (a surplus one repeats the wave's first)
+    constexpr int STAGE = (BM + BN) * 64;
+    static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && S >= 3 && S * STAGE <= 64 * 1024, "tile shape");
+    __shared__ __align__(1024) unsigned char ring[S * STAGE];
+    const unsigned ring_base = (unsigned)(size_t)((__attribute__((address_space(3))) void *)ring);
 
     unsigned bid = xcd_local_block_id(blockIdx.x, gridDim.x);
     const int cbk = bid % col_blocks; bid /= col_blocks;
     const int rbk = bid % row_blocks; bid /= row_blocks;
     const int xi = bid;
     const int t0 = rbk * BM, k0 = cbk * BN;
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave / WN, wn = wave % WN;
 
-    // per-thread global segments: segment s -> (row s/4, 16-byte piece s%4); rows beyond the
-    // tensor are clamped to the last valid row (their products are never stored)
-    const f16 *a_src[A_SEGS];
-    const f16 *b_src[B_SEGS];
-    int a_dst[A_SEGS], b_dst[B_SEGS];
+    // lane l of a load: row l / 4 of the 16, physical 16-byte slot l % 4, which holds slot (l % 4) ^ (row / 4) % 4
+    const f16 *src[NP];
+    unsigned off[NP], dst[NP];
+    size_t step[NP];
 #pragma unroll
-    for (int i = 0; i < A_SEGS; ++i) {
-        const int s = tid + i * 256, row = s >> 2, piece = s & 3;
-        int t = t0 + row; if (t > T - 1) t = T - 1;
-        a_src[i] = V + ((size_t)xi * c_blocks * T + t) * kChanBlock + piece * 8;
-        a_dst[i] = row * kRowHalves + piece * 8;
+    for (int i = 0; i < NP; ++i) {
+        int grp = wave + i * WAVES;
+        if (grp >= GROUPS) grp = wave;
+        const bool of_v = grp * 16 < BM;
+        int row = grp * 16 - (of_v ? 0 : BM) + (lane >> 2);
+        const int last = of_v ? T - 1 - t0 : Kp - 1 - k0;
+        if (row > last) row = last;
+        off[i] = (unsigned)row * 64u + (unsigned)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
+        src[i] = uniform_pointer(of_v ? V + ((size_t)xi * c_blocks * T + t0) * kChanBlock : U + ((size_t)xi * c_blocks * Kp + k0) * kChanBlock);
+        step[i] = (size_t)(of_v ? T : Kp) * kChanBlock;
+        dst[i] = ring_base + (unsigned)grp * 1024u;
     }
+    int issued = 0;
+    auto issue_stage = [&](int slot) __attribute__((always_inline)) {
+        const bool surplus = issued >= c_blocks;
 #pragma unroll
-    for (int i = 0; i < B_SEGS; ++i) {
-        const int s = tid + i * 256, row = s >> 2, piece = s & 3;
-        int k = k0 + row; if (k > Kp - 1) k = Kp - 1;
-        b_src[i] = U + ((size_t)xi * c_blocks * Kp + k) * kChanBlock + piece * 8;
-        b_dst[i] = row * kRowHalves + piece * 8;
-    }
-    const size_t a_step = (size_t)T * kChanBlock, b_step = (size_t)Kp * kChanBlock;
-
-    float16v acc[MB][NB];
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    uint4v a_reg[A_SEGS], b_reg[B_SEGS];
-    auto load_global = [&](int cb) {
-#pragma unroll
-        for (int i = 0; i < A_SEGS; ++i) a_reg[i] = *reinterpret_cast<const uint4v *>(a_src[i] + cb * a_step);
-#pragma unroll
-        for (int i = 0; i < B_SEGS; ++i)
-            if (BN * 4 >= 256 || tid + i * 256 < BN * 4)
-                b_reg[i] = *reinterpret_cast<const uint4v *>(b_src[i] + cb * b_step);
-    };
-    auto store_lds = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < A_SEGS; ++i) *reinterpret_cast<uint4v *>(&lds_a[buf][a_dst[i]]) = a_reg[i];
-#pragma unroll
-        for (int i = 0; i < B_SEGS; ++i)
-            if (BN * 4 >= 256 || tid + i * 256 < BN * 4)
-                *reinterpret_cast<uint4v *>(&lds_b[buf][b_dst[i]]) = b_reg[i];
+        for (int i = 0; i < NP; ++i) {
+            global_to_lds16<false>(src[i], surplus ? 0u : off[i], (unsigned)__builtin_amdgcn_readfirstlane((int)(dst[i] + (unsigned)(slot * STAGE))));
+            if (issued + 1 < c_blocks) src[i] = uniform_pointer(src[i] + step[i]);
+        }
+        ++issued;
     };
 
-    load_global(0);
-    store_lds(0);
-    __syncthreads();
+    float16v acc[NB][MB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.0f;
 
-    const int frag_row = lane & 31, frag_k = (lane >> 5) * 8;
+    for (int j = 0; j < S - 1; ++j) issue_stage(j);
+    const int frag_row = lane & 31, swz = (frag_row >> 2) & 3;
+    const int frag_off[2] = {frag_row * 64 + (((lane >> 5) ^ swz) * 16), frag_row * 64 + (((2 + (lane >> 5)) ^ swz) * 16)};
+    int slot = 0;
     for (int cb = 0; cb < c_blocks; ++cb) {
-        const int buf = cb & 1;
-        if (cb + 1 < c_blocks) load_global(cb + 1);
+        stream_wait<(S - 2) * NP>();                       // this wave's pieces of the stage have landed
+        __syncthreads();                                   // everyone's have; the slot before is free again
+        issue_stage(slot == 0 ? S - 1 : slot - 1);
+        const unsigned char *stage = ring + slot * STAGE;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
-            half8 af[MB], bf[NB];
+            half8 vf[MB], uf[NB];
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
-                af[i] = *reinterpret_cast<const half8 *>(
-                    &lds_a[buf][((wm * MB + i) * 32 + frag_row) * kRowHalves + kk * 16 + frag_k]);
+            for (int i = 0; i < MB; ++i) vf[i] = *reinterpret_cast<const half8 *>(stage + (wm * MB + i) * 2048 + frag_off[kk]);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) uf[j] = *reinterpret_cast<const half8 *>(stage + BM * 64 + (wn * NB + j) * 2048 + frag_off[kk]);
 #pragma unroll
             for (int j = 0; j < NB; ++j)
-                bf[j] = *reinterpret_cast<const half8 *>(
-                    &lds_b[buf][((wn * NB + j) * 32 + frag_row) * kRowHalves + kk * 16 + frag_k]);
 #pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i], bf[j], acc[i][j], 0, 0, 0);
+                for (int i = 0; i < MB; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[i], uf[j], acc[j][i], 0, 0, 0);
         }
-        if (cb + 1 < c_blocks) store_lds(buf ^ 1);
-        __syncthreads();
+        slot = slot == S - 1 ? 0 : slot + 1;
     }
+    // the surplus loads must land before the LDS is released
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
-    // D[row][col]: lane holds col = lane%32 and rows 8*(e/4) + 4*(lane/32) + e%4
-    const int col = lane & 31, row_base = (lane >> 5) * 4;
+    // D[row = t][col = k]: lane holds channel lane%32 of a block and tiles 8*(e/4) + 4*(lane/32) + e%4, so that a
+    // store covers two whole 128-byte rows of M (with U as the row operand a lane has four neighbouring channels,
+    // and a store 32 pieces of 32 bytes: a quarter as many stores, 5-30 % slower)
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int kb = (k0 >> 5) + wn * NB + j;
         if (kb >= k_blocks) continue;
-        MT *dst = Mo + ((size_t)xi * k_blocks + kb) * (size_t)Tp * kChanBlock + col;
+        MT *plane = Mo + ((size_t)xi * k_blocks + kb) * (size_t)Tp * kChanBlock + frag_row;
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int t = t0 + (wm * MB + i) * 32 + (e >> 2) * 8 + row_base + (e & 3);
-                if (t < T) store_from_f32(dst + (size_t)t * kChanBlock, acc[i][j][e]);
+                const int t = t0 + (wm * MB + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                if (t < T) store_from_f32(plane + (size_t)t * kChanBlock, acc[j][i][e]);
             }
     }
 }
@@ -189,23 +193,23 @@ __device__ __forceinline__ void stream_to_lds16(const void *uniform_base, unsign
     global_to_lds16<false>(uniform_base, byte_offset, lds_wave_base);
 }
 template <int IMM>
-__device__ __forceinline__ void stream_store(float *uniform_base, unsigned byte_offset, float a, float b, float c, float d)
+__device__ __forceinline__ void stream_store(float *uniform_base, unsigned byte_offset, float a)
 {
-    typedef float float4v __attribute__((ext_vector_type(4)));
-    const float4v v = {a, b, c, d};
-    asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3" : : "v"(byte_offset), "v"(v), "s"(uniform_base), "n"(IMM) : "memory");
+    asm volatile("global_store_dword %0, %1, %2 offset:%3" : : "v"(byte_offset), "v"(a), "s"(uniform_base), "n"(IMM) : "memory");
 }
 template <int IMM>
-__device__ __forceinline__ void stream_store(f16 *uniform_base, unsigned byte_offset, float a, float b, float c, float d)
+__device__ __forceinline__ void stream_store(f16 *uniform_base, unsigned byte_offset, float a)
 {
-    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
-    const half4 v = {(f16)a, (f16)b, (f16)c, (f16)d};
-    asm volatile("global_store_dwordx2 %0, %1, %2 offset:%3" : : "v"(byte_offset), "v"(v), "s"(uniform_base), "n"(IMM) : "memory");
+    const f16 v = (f16)a;
+    asm volatile("global_store_short %0, %1, %2 offset:%3" : : "v"(byte_offset), "v"(v), "s"(uniform_base), "n"(IMM) : "memory");
 }
-template <int X>
-__device__ __forceinline__ void stream_wait()
+template <typename MT, int E = 0>
+__device__ __forceinline__ void stream_store_block(MT *plane, unsigned m_off, const float16v &acc)
 {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(X < 63 ? X : 63) : "memory");
+    if constexpr (E < 16) {
+        stream_store<((E >> 2) * 8 + (E & 3)) * kChanBlock * (int)sizeof(MT)>(plane, m_off, acc[E]);
+        stream_store_block<MT, E + 1>(plane, m_off, acc);
+    }
 }
 // wait for the loads of the i-th stage of this workgroup (i counted from its first stage):
 // younger operations = (S-2) stages of loads plus the stores of the min(i, S-1) stages completed
@@ -234,7 +238,7 @@ contract_stream_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT 
     constexpr int THREADS = 64 * WN * WM;
     constexpr int SR = 32 * WM;                      // rows (tiles t) per stage
     constexpr int NP = CB * SR * 4 / THREADS;        // 16-byte loads per thread and stage
-    constexpr int NS = 4 * NB;                       // stores per thread and stage
+    constexpr int NS = 16 * NB;                      // stores per thread and stage
     constexpr int STAGE_BYTES = CB * SR * 64;        // [CB][SR] rows of 32 binary16 channels
     static_assert(NP >= 1 && NP * THREADS == CB * SR * 4 && S >= 3 && S * STAGE_BYTES * OCC <= 144 * 1024,
                   "pipeline shape");
@@ -332,16 +336,16 @@ contract_stream_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
         MT *m_plane = uniform_pointer(Mo + ((size_t)xi * k_blocks + (size_t)(kg * WN + wn) * NB) * Tp * kChanBlock);
-        // lane holds t = lane%32 and output channels 8*(e/4) + 4*(lane/32) + e%4 of each block:
-        // four consecutive channels per store; rows up to Tp exist, so no store is conditional
-        unsigned m_off = ((unsigned)(tb0 * SR + wm * 32 + frag_row) * kChanBlock + (unsigned)(lane >> 5) * 4u) * (unsigned)sizeof(MT);
+        // lane holds output channel lane%32 of each block and t = 8*(e/4) + 4*(lane/32) + e%4: a store covers two
+        // whole 128-byte rows of M; rows up to Tp exist, so no store is conditional
+        unsigned m_off = ((unsigned)(tb0 * SR + wm * 32 + (lane >> 5) * 4) * kChanBlock + (unsigned)frag_row) * (unsigned)sizeof(MT);
         int slot = 0;
         for (int j = 0; j < count; ++j) {
             stream_wait_stage<0, S, NP, NS>(j);                // this wave's pieces of stage j have landed
             __syncthreads();                                   // everyone's have; slot-1 is free again
             issue_stage(j + S - 1, slot == 0 ? S - 1 : slot - 1);
 
-            // acc[nb] = U-block (32 output channels) x V-stage rows (32 tiles): D[row = k][col = t]
+            // acc[nb] = V-stage rows (32 tiles) x U-block (32 output channels): D[row = t][col = k]
             float16v acc[NB];
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb)
@@ -355,7 +359,7 @@ contract_stream_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT 
                     const half8 vf = *reinterpret_cast<const half8 *>(stage + cb * SR * 64 + frag_off[kk]);
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ufrag[nb][cb][kk], vf, acc[nb], 0, 0, 0);
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, ufrag[nb][cb][kk], acc[nb], 0, 0, 0);
                     // keep the fragment reads of later channel blocks from being hoisted all the way
                     // up: sixteen 128-bit fragments in flight at once do not fit the register budget
                     if (kk == 1) __builtin_amdgcn_sched_barrier(0);
@@ -369,10 +373,7 @@ contract_stream_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT 
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 MT *plane = m_plane + (size_t)nb * Tp * kChanBlock;
-                stream_store<0 * 8 * (int)sizeof(MT)>(plane, m_off, acc[nb][0], acc[nb][1], acc[nb][2], acc[nb][3]);
-                stream_store<1 * 8 * (int)sizeof(MT)>(plane, m_off, acc[nb][4], acc[nb][5], acc[nb][6], acc[nb][7]);
-                stream_store<2 * 8 * (int)sizeof(MT)>(plane, m_off, acc[nb][8], acc[nb][9], acc[nb][10], acc[nb][11]);
-                stream_store<3 * 8 * (int)sizeof(MT)>(plane, m_off, acc[nb][12], acc[nb][13], acc[nb][14], acc[nb][15]);
+                stream_store_block<MT>(plane, m_off, acc[nb]);
             }
             m_off += (unsigned)(SR * kChanBlock) * (unsigned)sizeof(MT);
             slot = slot == S - 1 ? 0 : slot + 1;
@@ -430,13 +431,13 @@ contract_f32_kernel(const float *__restrict__ U, const float *__restrict__ V, fl
         }
 }
 
-template <int BM, int BN, int WM, int WN, typename MT>
-static int launch_c16(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t stream)
+template <int BM, int BN, int WM, int WN, int S, typename MT>
+static int launch_tile(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t stream)
 {
     const int row_blocks = ceil_div((int)g.T, BM), col_blocks = ceil_div(g.Kp, BN);
     const long long blocks = (long long)g.n * g.n * row_blocks * col_blocks;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL((contract_f16_kernel<BM, BN, WM, WN, MT>), dim3((unsigned)blocks), dim3(256), 0, stream,
+    hipLaunchKernelGGL((contract_tile_kernel<BM, BN, WM, WN, S, MT>), dim3((unsigned)blocks), dim3(64 * WM * WN), 0, stream,
                        (const f16 *)U, (const f16 *)V, (MT *)Mo, (int)g.T, (int)g.Tp, g.Kp, g.c_blocks, g.k_blocks,
                        row_blocks, col_blocks);
     return (int)hipGetLastError();
@@ -464,35 +465,50 @@ static int launch_stream(const void *U, const void *V, void *Mo, const Geometry 
     return (int)hipGetLastError();
 }
 
+// Tile shape (us per launch, buffers alternating so that nothing is found in the cache).  64 x 64 fills the chip
+// soonest and is the fastest one on small layers: 48 -> 96 5x5 @35x35 batch 16 12.0 (128 x 64: 15.2), 512 -> 512
+// @14x14 batch 1 F(4,3) 6.6 (8.2), 128 -> 128 @112x112 batch 5 F(6,3), 15 M products, 15.6 (16.6).  Larger tiles read
+// U and V less often: 128 x 128 by 8 waves in long channel loops once it fills the chip as well (512 -> 512 @7x7
+// F(8,3) batch 256 30.7 against 36.0 and 41.8 for 128 x 64 and 64 x 64, batch 128 15.8 against 20.3 and 17.4),
+// 128 x 64 in other large layers (164 -> 33 @98x29 batch 43 F(4,3), 20 M, 38.4 against 41.4; 64 -> 64 @112x112 batch 32
+// F(4,3), 58 M, 56.0 against 59.7).  One block of output channels: 128 x 32, none of it padding.
 template <typename MT>
 static int launch_c16_tiled(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t s)
 {
-    if (g.Kp >= 128) return launch_c16<128, 128, 2, 2, MT>(U, V, Mo, g, s);
-    if (g.Kp >= 64) return launch_c16<128, 64, 2, 2, MT>(U, V, Mo, g, s);
-    return launch_c16<128, 32, 4, 1, MT>(U, V, Mo, g, s);
+    if (g.Kp == 32) return launch_tile<128, 32, 4, 1, 3, MT>(U, V, Mo, g, s);
+    const double positions = (double)g.n * g.n;
+    if (g.c_blocks >= 8 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
+        return launch_tile<128, 128, 2, 4, 3, MT>(U, V, Mo, g, s);
+    if (positions * (double)g.T * g.Kp >= 16e6) return launch_tile<128, 64, 2, 2, 3, MT>(U, V, Mo, g, s);
+    return launch_tile<64, 64, 2, 2, 3, MT>(U, V, Mo, g, s);
 }
 
+// The streaming kernel takes C in {64, 128, 256} and K a multiple of 128 where there are enough stages per
+// workgroup to pay for its start (the U fragments): by the number of products, streaming / best tile in us:
+//   C = 256, M binary32: from 12 M  (256 -> 256 @56x56 F(8,3) batch 12, 15 M: 19.3 / 20.1, batch 32, 40 M: 44 / 64;
+//                                    F(6,3) @28x28 batch 24, 10 M: 15.6 / 14.6)
+//   C = 128: from 24 M              (128 -> 128 @112x112 F(6,3) batch 11, 33 M: 32.5 / 35.8, batch 5, 15 M: 16.5 / 15.6)
+//   C = 64: from 40 M               (64 -> 128 @224x224 F(4,3) batch 8, 116 M: 99 / 107; 64 -> 256 @56x56, 36 M: 26 / 26)
+//   M binary16: from 16 M           (256 -> 256 @14x14 F(8,3) batch 256, 26 M: 22.9 / 31.8; 64 -> 256 @56x56, 60 M: 27 / 45)
+// (C = 512 variants, 16 channel blocks in 128 fragment registers at one workgroup per CU, measured no faster than
+// tiles at T = 512 and slower at T = 128.)  Ring depth S: as many stages as fit about 128 KiB of LDS, at most 8.
 template <typename MT>
 static int launch_c16_shape(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t s)
 {
-    // streaming kernel: C in {64, 128, 256} and K a multiple of the workgroup's channel span
-    // (C = 512 variants, 16 channel blocks in 128 fragment registers at one workgroup per CU, measured
-    // no faster than the tiled kernel at T = 512 and slower at T = 128);
-    // ring depth S: as many stages as fit about 128 KiB of LDS, at most 8
     const int cb = g.c_blocks;
-    const int wn = g.Kp % 256 == 0 ? 4 : g.Kp % 128 == 0 ? 2 : g.Kp % 64 == 0 ? 1 : 0;
-    {
-        //                                            WN WM NB CB  S OCC
-        if (wn == 4 && cb == 8) return launch_stream<8, 1, 1, 8, 4, 2, MT>(U, V, Mo, g, s);   // 8 waves x 32 channels
-        if (wn == 4 && cb == 4) return launch_stream<4, 1, 2, 4, 8, 2, MT>(U, V, Mo, g, s);
-        if (wn == 4 && cb == 2) return launch_stream<4, 1, 2, 2, 8, 2, MT>(U, V, Mo, g, s);
-        if (wn == 2 && cb == 8) return launch_stream<2, 2, 2, 8, 4, 1, MT>(U, V, Mo, g, s);
-        if (wn == 2 && cb == 4) return launch_stream<2, 2, 2, 4, 4, 2, MT>(U, V, Mo, g, s);
-        if (wn == 2 && cb == 2) return launch_stream<2, 2, 2, 2, 8, 2, MT>(U, V, Mo, g, s);
-        if (wn == 1 && cb == 4) return launch_stream<1, 4, 2, 4, 4, 1, MT>(U, V, Mo, g, s);
-        if (wn == 1 && cb == 2) return launch_stream<1, 4, 2, 2, 4, 2, MT>(U, V, Mo, g, s);
+    const double products = (double)g.n * g.n * (double)g.T * g.Kp;
+    const double from = sizeof(MT) == 2 ? 16e6 : cb == 8 ? 12e6 : cb == 4 ? 24e6 : 40e6;
+    if ((cb == 2 || cb == 4 || cb == 8) && g.Kp % 128 == 0 && products >= from) {
+        const bool wide = g.Kp % 256 == 0;
+        //                                              WN WM NB CB  S OCC
+        if (wide && cb == 8) return launch_stream<8, 1, 1, 8, 4, 2, MT>(U, V, Mo, g, s);   // 8 waves x 32 channels
+        if (wide && cb == 4) return launch_stream<4, 1, 2, 4, 8, 2, MT>(U, V, Mo, g, s);
+        if (wide) return launch_stream<4, 1, 2, 2, 8, 2, MT>(U, V, Mo, g, s);
+        if (cb == 8) return launch_stream<2, 2, 2, 8, 4, 1, MT>(U, V, Mo, g, s);
+        if (cb == 4) return launch_stream<2, 2, 2, 4, 4, 2, MT>(U, V, Mo, g, s);
+        return launch_stream<2, 2, 2, 2, 8, 2, MT>(U, V, Mo, g, s);
     }
-    return launch_c16_tiled<MT>(U, V, Mo, g, s);       // other shapes: tiled kernel
+    return launch_c16_tiled<MT>(U, V, Mo, g, s);
 }
 
 int launch_contract(const nova_transforms *, const void *U, const void *V, void *Mo, const Geometry &g,

@@ -1,0 +1,52 @@
+"""The products do not depend on which contraction kernel or tile shape formed them: every variant the dispatch can
+choose (by channels, output channels and number of products) against binary64 sums of the stored U and V, and bit for
+bit against the same images contracted in small slabs, which run the small tiles."""
+import pytest
+import torch
+
+from paper_2512_18453_amd import nova, synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+CASES = [
+    # m, N, C, K, H, W: 128 x 32 tiles; 64 x 64 with ragged edges both ways, one to many channel blocks
+    (4, 1, 5, 32, 9, 9), (4, 3, 33, 20, 45, 50), (6, 2, 31, 33, 31, 33), (4, 1, 64, 64, 32, 32), (4, 1, 97, 129, 33, 31),
+    (4, 1, 512, 512, 14, 14), (6, 5, 300, 96, 30, 30),
+    # 128 x 64 tiles by the number of products, 128 x 128 by the length of the channel loop
+    (4, 9, 48, 96, 140, 140), (8, 15, 260, 260, 20, 20),
+    # streaming kernel at its thresholds: C = 256, 128, 64; K a multiple of 256 or of 128 only
+    (8, 12, 256, 256, 49, 50), (8, 21, 256, 128, 50, 50), (8, 18, 128, 256, 57, 56), (8, 36, 128, 128, 56, 57),
+    (4, 6, 64, 256, 170, 180), (4, 12, 64, 128, 170, 180),
+]
+
+
+def unblock(a, n2, rows, chans):
+    return a.view(n2, -(-chans // 32), rows, 32).transpose(1, 2).reshape(n2, rows, -1)[:, :, :chans]
+
+
+@pytest.mark.parametrize("m,N,C,K,H,W", CASES)
+def test_products(m, N, C, K, H, W):
+    t = nova.nova_make_transforms(synth.point_set("nova", m), m, 3)
+    gen = torch.Generator(device=DEV).manual_seed(C + K)
+    x = torch.randn((N, C, H, W), device=DEV, generator=gen).half()
+    U = nova.nova_filter_transform(t, (torch.randn((K, C, 3, 3), device=DEV, generator=gen) * (2.0 / (9 * C)) ** 0.5).half())
+    n2, per = t.n * t.n, -(-H // m) * -(-W // m)
+    T, Kp = N * per, -(-K // 32) * 32
+    V = nova.nova_input_transform(t, x)
+    Ul, Vl = unblock(U, n2, Kp, C)[:, :K].double(), unblock(V, n2, T, C)
+    parts = [nova.nova_input_transform(t, x[i:i + 1].contiguous()) for i in range(min(N, 3))]
+    for flags in (0, nova.NOVA_FLAG_M_F16):
+        print(f"[case] products F({m},3) N={N} C={C} K={K} {H}x{W} flags={flags}", flush=True)
+        M = nova.nova_contract(t, U, V, N, C, H, W, K, flags)
+        M = unblock(M, n2, -(-T // 128) * 128, K)[:, :T]
+        for i, v in enumerate(parts):
+            one = unblock(nova.nova_contract(t, U, v, 1, C, H, W, K, flags), n2, -(-per // 128) * 128, K)[:, :per]
+            assert torch.equal(M[:, i * per:(i + 1) * per], one)
+        for xi in (0, n2 // 2 + 1, n2 - 1):
+            want = torch.matmul(Vl[xi].double(), Ul[xi].t().contiguous())
+            size = torch.matmul(Vl[xi].double().abs(), Ul[xi].t().abs().contiguous())
+            # C exact products added in binary32 (twice the standard bound, for sums that are truncated), then one rounding
+            bound = 2 * (C + 2) * 2.0 ** -24 * size + (2.0 ** -11 * want.abs() + 2.0 ** -25 if flags else 0.0)
+            assert ((M[xi].double() - want).abs() <= bound).all(), xi
