@@ -14,7 +14,7 @@
 // channels per lane, 32 bytes of each row at a time, moved the same bytes in 5-30 % more time (streaming kernel,
 // us: 256 -> 256 @14x14 batch 256 binary16 M 28.5 -> 22.8, binary32 30.0 -> 26.4; 128 -> 128 @28x28 batch 128
 // 28.0 -> 24.8; 256 -> 256 @56x56 batch 32 40.7 -> 39.3).
-// binary32 path: same layouts, plain FMA tiles (validation path, not tuned).
+// binary32 path: the tiled kernel on v_mfma_f32_32x32x2_f32.
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -35,7 +35,7 @@ int device_cu_count()
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
-typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
+typedef float float4f __attribute__((ext_vector_type(4)));
 
 // s_waitcnt vmcnt(X): at most X of the wave's vector-memory operations are outstanding afterwards (they retire
 // in the order issued)
@@ -54,16 +54,25 @@ __device__ __forceinline__ void stream_wait()
 // never stored); past the last channel block loads are still issued, so that the wait counts are constants, but
 // every lane rereads the same 16 bytes: one cached request.  Summation order per product: ascending channels in steps of 16, as in the
 // streaming kernel -- M does not depend on which kernel or tile shape formed it.
-template <int BM, int BN, int WM, int WN, int S, typename MT>
+// binary32 storage: v_mfma_f32_32x32x2_f32.  A row is 128 bytes (slots XOR-swizzled with (row / 2) % 8, a wave-wide
+// load moves 8 rows); a 128-bit read gives a lane four channels, which four instructions take in turn, so
+// the channels enter in the order 0, 4, 1, 5, 2, 6, 3, 7 of every eight; every other eight go to a second chain
+// of sums (rounding error of M against 64 bits, geometric mean over 40 drawn layers: 0.83 times that of one
+// multiply-add chain over the channels).  With plain multiply-add tiles (one
+// 4-byte LDS read per 2 products, one step in flight) 40 -> 70 @45x61 batch 8 F(6,3) took 23.9 us, this way 13.5.
+template <int BM, int BN, int WM, int WN, int S, typename ST, typename MT>
 __global__ void __launch_bounds__(64 * WM * WN)
-contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *__restrict__ Mo,
+contract_tile_kernel(const ST *__restrict__ U, const ST *__restrict__ V, MT *__restrict__ Mo, int C,
                      int T, int Tp, int Kp, int c_blocks, int k_blocks, int row_blocks, int col_blocks)
 {
+    constexpr int ROW = kChanBlock * (int)sizeof(ST);       // bytes of 32 channels
+    constexpr int SLOTS = ROW / 16, LOAD_ROWS = 1024 / ROW; // 16-byte slots per row, rows per wave-wide load
+    constexpr int SWZ = sizeof(ST) == 2 ? 2 : 1;            // slot ^ (row >> SWZ) % SLOTS
     constexpr int WAVES = WM * WN;
     constexpr int MB = BM / WM / 32, NB = BN / WN / 32;     // 32 x 32 blocks per wave
-    constexpr int GROUPS = (BM + BN) / 16;                  // wave-wide loads per stage
+    constexpr int GROUPS = (BM + BN) / LOAD_ROWS;           // wave-wide loads per stage
     constexpr int NP = (GROUPS + WAVES - 1) / WAVES;        // ... per wave (a surplus one repeats the wave's first)
-    constexpr int STAGE = (BM + BN) * 64;
+    constexpr int STAGE = (BM + BN) * ROW;
     static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && S >= 3 && S * STAGE <= 64 * 1024, "tile shape");
     __shared__ __align__(1024) unsigned char ring[S * STAGE];
     const unsigned ring_base = (unsigned)(size_t)((__attribute__((address_space(3))) void *)ring);
@@ -77,19 +86,20 @@ contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *_
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int wm = wave / WN, wn = wave % WN;
 
-    // lane l of a load: row l / 4 of the 16, physical 16-byte slot l % 4, which holds slot (l % 4) ^ (row / 4) % 4
-    const f16 *src[NP];
+    // lane l of a load: row l / SLOTS of the LOAD_ROWS, physical slot l % SLOTS
+    const ST *src[NP];
     unsigned off[NP], dst[NP];
     size_t step[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
         int grp = wave + i * WAVES;
         if (grp >= GROUPS) grp = wave;
-        const bool of_v = grp * 16 < BM;
-        int row = grp * 16 - (of_v ? 0 : BM) + (lane >> 2);
+        const bool of_v = grp * LOAD_ROWS < BM;
+        int row = grp * LOAD_ROWS - (of_v ? 0 : BM) + lane / SLOTS;
+        const unsigned slot = (unsigned)((lane % SLOTS) ^ ((row >> SWZ) % SLOTS));
         const int last = of_v ? T - 1 - t0 : Kp - 1 - k0;
         if (row > last) row = last;
-        off[i] = (unsigned)row * 64u + (unsigned)((lane & 3) ^ ((lane >> 4) & 3)) * 16u;
+        off[i] = (unsigned)row * (unsigned)ROW + slot * 16u;
         src[i] = uniform_pointer(of_v ? V + ((size_t)xi * c_blocks * T + t0) * kChanBlock : U + ((size_t)xi * c_blocks * Kp + k0) * kChanBlock);
         step[i] = (size_t)(of_v ? T : Kp) * kChanBlock;
         dst[i] = ring_base + (unsigned)grp * 1024u;
@@ -105,17 +115,22 @@ contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *_
         ++issued;
     };
 
-    float16v acc[NB][MB];
+    constexpr int CHAINS = sizeof(ST) == 4 ? 2 : 1;
+    float16v acc[CHAINS][NB][MB];
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int ch = 0; ch < CHAINS; ++ch)
 #pragma unroll
-        for (int i = 0; i < MB; ++i)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.0f;
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[ch][j][i][e] = 0.0f;
 
     for (int j = 0; j < S - 1; ++j) issue_stage(j);
-    const int frag_row = lane & 31, swz = (frag_row >> 2) & 3;
-    const int frag_off[2] = {frag_row * 64 + (((lane >> 5) ^ swz) * 16), frag_row * 64 + (((2 + (lane >> 5)) ^ swz) * 16)};
+    const int frag_row = lane & 31, swz = (frag_row >> SWZ) % SLOTS;
+    int frag_off[SLOTS / 2];
+#pragma unroll
+    for (int kk = 0; kk < SLOTS / 2; ++kk) frag_off[kk] = frag_row * ROW + (((kk * 2 + (lane >> 5)) ^ swz) * 16);
     int slot = 0;
     for (int cb = 0; cb < c_blocks; ++cb) {
         stream_wait<(S - 2) * NP>();                       // this wave's pieces of the stage have landed
@@ -123,16 +138,31 @@ contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *_
         issue_stage(slot == 0 ? S - 1 : slot - 1);
         const unsigned char *stage = ring + slot * STAGE;
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            half8 vf[MB], uf[NB];
+        for (int kk = 0; kk < SLOTS / 2; ++kk) {
+            typedef typename std::conditional<sizeof(ST) == 2, half8, float4f>::type frag_t;
+            frag_t vf[MB], uf[NB];
+            // (binary32: channels past C are zero on both sides and need not be multiplied)
+            if (sizeof(ST) == 4 && cb * kChanBlock + kk * 8 >= C) break;
 #pragma unroll
-            for (int i = 0; i < MB; ++i) vf[i] = *reinterpret_cast<const half8 *>(stage + (wm * MB + i) * 2048 + frag_off[kk]);
+            for (int i = 0; i < MB; ++i) vf[i] = *reinterpret_cast<const frag_t *>(stage + (wm * MB + i) * 32 * ROW + frag_off[kk]);
 #pragma unroll
-            for (int j = 0; j < NB; ++j) uf[j] = *reinterpret_cast<const half8 *>(stage + BM * 64 + (wn * NB + j) * 2048 + frag_off[kk]);
+            for (int j = 0; j < NB; ++j) uf[j] = *reinterpret_cast<const frag_t *>(stage + BM * ROW + (wn * NB + j) * 32 * ROW + frag_off[kk]);
+            if constexpr (sizeof(ST) == 2) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
+                for (int j = 0; j < NB; ++j)
 #pragma unroll
-                for (int i = 0; i < MB; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[i], uf[j], acc[j][i], 0, 0, 0);
+                    for (int i = 0; i < MB; ++i) acc[0][j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[i], uf[j], acc[0][j][i], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int j = 0; j < NB; ++j)
+#pragma unroll
+                        for (int i = 0; i < MB; ++i) {
+                            float16v &sum = acc[kk % CHAINS][j][i];
+                            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[i][e], uf[j][e], sum, 0, 0, 0);
+                        }
+            }
         }
         slot = slot == S - 1 ? 0 : slot + 1;
     }
@@ -152,7 +182,9 @@ contract_tile_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT *_
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int t = t0 + (wm * MB + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                if (t < T) store_from_f32(plane + (size_t)t * kChanBlock, acc[j][i][e]);
+                float sum = acc[0][j][i][e];
+                if constexpr (CHAINS == 2) sum += acc[CHAINS - 1][j][i][e];
+                if (t < T) store_from_f32(plane + (size_t)t * kChanBlock, sum);
             }
     }
 }
@@ -385,60 +417,14 @@ contract_stream_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, MT 
     }
 }
 
-// binary32: 64 x 64 tile, 256 threads, 4 x 4 outputs per thread
-__global__ void __launch_bounds__(256)
-contract_f32_kernel(const float *__restrict__ U, const float *__restrict__ V, float *__restrict__ Mo,
-                    int T, int Tp, int Kp, int c_blocks, int k_blocks, int row_blocks, int col_blocks)
-{
-    __shared__ float lds_a[64][kChanBlock + 1];
-    __shared__ float lds_b[64][kChanBlock + 1];
-    unsigned bid = blockIdx.x;
-    const int cbk = bid % col_blocks; bid /= col_blocks;
-    const int rbk = bid % row_blocks; bid /= row_blocks;
-    const int xi = bid;
-    const int t0 = rbk * 64, k0 = cbk * 64;
-    const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
-
-    float acc[4][4] = {};
-    for (int cb = 0; cb < c_blocks; ++cb) {
-        for (int e = tid; e < 64 * kChanBlock; e += 256) {
-            const int row = e >> 5, c = e & 31;
-            int t = t0 + row; if (t > T - 1) t = T - 1;
-            int k = k0 + row; if (k > Kp - 1) k = Kp - 1;
-            lds_a[row][c] = V[(((size_t)xi * c_blocks + cb) * T + t) * kChanBlock + c];
-            lds_b[row][c] = U[(((size_t)xi * c_blocks + cb) * Kp + k) * kChanBlock + c];
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int c = 0; c < kChanBlock; ++c) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = lds_a[ty + 16 * i][c]; b[i] = lds_b[tx + 16 * i][c]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma32(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = t0 + ty + 16 * i, k = k0 + tx + 16 * j;
-            if (t < T && (k >> 5) < k_blocks)
-                Mo[(((size_t)xi * k_blocks + (k >> 5)) * Tp + t) * kChanBlock + (k & 31)] = acc[i][j];
-        }
-}
-
-template <int BM, int BN, int WM, int WN, int S, typename MT>
+template <int BM, int BN, int WM, int WN, int S, typename ST, typename MT>
 static int launch_tile(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t stream)
 {
     const int row_blocks = ceil_div((int)g.T, BM), col_blocks = ceil_div(g.Kp, BN);
     const long long blocks = (long long)g.n * g.n * row_blocks * col_blocks;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL((contract_tile_kernel<BM, BN, WM, WN, S, MT>), dim3((unsigned)blocks), dim3(64 * WM * WN), 0, stream,
-                       (const f16 *)U, (const f16 *)V, (MT *)Mo, (int)g.T, (int)g.Tp, g.Kp, g.c_blocks, g.k_blocks,
+    hipLaunchKernelGGL((contract_tile_kernel<BM, BN, WM, WN, S, ST, MT>), dim3((unsigned)blocks), dim3(64 * WM * WN), 0, stream,
+                       (const ST *)U, (const ST *)V, (MT *)Mo, g.C, (int)g.T, (int)g.Tp, g.Kp, g.c_blocks, g.k_blocks,
                        row_blocks, col_blocks);
     return (int)hipGetLastError();
 }
@@ -475,12 +461,12 @@ static int launch_stream(const void *U, const void *V, void *Mo, const Geometry 
 template <typename MT>
 static int launch_c16_tiled(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t s)
 {
-    if (g.Kp == 32) return launch_tile<128, 32, 4, 1, 3, MT>(U, V, Mo, g, s);
+    if (g.Kp == 32) return launch_tile<128, 32, 4, 1, 3, f16, MT>(U, V, Mo, g, s);
     const double positions = (double)g.n * g.n;
     if (g.c_blocks >= 8 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
-        return launch_tile<128, 128, 2, 4, 3, MT>(U, V, Mo, g, s);
-    if (positions * (double)g.T * g.Kp >= 16e6) return launch_tile<128, 64, 2, 2, 3, MT>(U, V, Mo, g, s);
-    return launch_tile<64, 64, 2, 2, 3, MT>(U, V, Mo, g, s);
+        return launch_tile<128, 128, 2, 4, 3, f16, MT>(U, V, Mo, g, s);
+    if (positions * (double)g.T * g.Kp >= 16e6) return launch_tile<128, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);
+    return launch_tile<64, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);
 }
 
 // The streaming kernel takes C in {64, 128, 256} and K a multiple of 128 where there are enough stages per
@@ -519,13 +505,8 @@ int launch_contract(const nova_transforms *, const void *U, const void *V, void 
     if (dtype == NOVA_F16)
         return (flags & NOVA_FLAG_M_F16) ? launch_c16_shape<f16>(U, V, Mo, g, s)
                                          : launch_c16_shape<float>(U, V, Mo, g, s);
-    const int row_blocks = ceil_div((int)g.T, 64), col_blocks = ceil_div(g.Kp, 64);
-    const long long blocks = (long long)g.n * g.n * row_blocks * col_blocks;
-    if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(contract_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (const float *)U,
-                       (const float *)V, (float *)Mo, (int)g.T, (int)g.Tp, g.Kp, g.c_blocks, g.k_blocks, row_blocks,
-                       col_blocks);
-    return (int)hipGetLastError();
+    if (g.Kp == 32) return launch_tile<64, 32, 2, 1, 3, float, float>(U, V, Mo, g, s);
+    return launch_tile<64, 64, 2, 2, 3, float, float>(U, V, Mo, g, s);
 }
 
 }  // namespace nova

@@ -50,3 +50,22 @@ def test_products(m, N, C, K, H, W):
             # C exact products added in binary32 (twice the standard bound, for sums that are truncated), then one rounding
             bound = 2 * (C + 2) * 2.0 ** -24 * size + (2.0 ** -11 * want.abs() + 2.0 ** -25 if flags else 0.0)
             assert ((M[xi].double() - want).abs() <= bound).all(), xi
+
+
+@pytest.mark.parametrize("m,N,C,K,H,W", [(4, 1, 1, 1, 5, 5), (4, 1, 8, 32, 33, 32), (2, 2, 9, 33, 13, 21), (6, 3, 32, 64, 49, 31),
+                                         (4, 2, 41, 65, 32, 65), (6, 2, 160, 96, 25, 60), (8, 1, 64, 31, 65, 64)])
+def test_products_in_binary32(m, N, C, K, H, W):
+    # edges of the 64 x 64 and 64 x 32 tiles, channel loops that end inside a group of eight channels
+    print(f"[case] binary32 products F({m},3) N={N} C={C} K={K} {H}x{W}", flush=True)
+    t = nova.nova_make_transforms(synth.point_set("standard" if m == 2 else "nova", m), m, 3)
+    gen = torch.Generator(device=DEV).manual_seed(C + K)
+    x = torch.randn((N, C, H, W), device=DEV, generator=gen)
+    U = nova.nova_filter_transform(t, torch.randn((K, C, 3, 3), device=DEV, generator=gen) * (2.0 / (9 * C)) ** 0.5)
+    n2, T = t.n * t.n, N * -(-H // m) * -(-W // m)
+    V = nova.nova_input_transform(t, x)
+    M = unblock(nova.nova_contract(t, U, V, N, C, H, W, K), n2, -(-T // 128) * 128, K)[:, :T].double()
+    Ul, Vl = unblock(U, n2, -(-K // 32) * 32, C)[:, :K].double(), unblock(V, n2, T, C).double()
+    want = torch.matmul(Vl, Ul.transpose(1, 2).contiguous())
+    size = torch.matmul(Vl.abs(), Ul.abs().transpose(1, 2).contiguous())
+    # C products, each rounded or not, and C sums in binary32; twice the standard bound as above
+    assert ((M - want).abs() <= 2 * (2 * C + 2) * 2.0 ** -24 * size + 1e-37).all()
