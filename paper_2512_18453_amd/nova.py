@@ -127,7 +127,11 @@ def _dtype_code(t):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream as a hipStream_t.  (The raw handle: building the Stream object that
+    torch.cuda.current_stream() returns takes 2.9 us, as long as a kernel launch; this 0.3.)"""
+    if not torch.cuda.is_initialized():
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def _dev(t):
