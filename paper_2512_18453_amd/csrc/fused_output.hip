@@ -321,12 +321,12 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
                 const int k_in = (one_pass ? wave : (wave & 3)) * kFusedWaveChannels + 2 * (lane >> 4) + e;
                 f16 *dst = stage + k_in * sh.k_pitch + jr * M * sh.cols_pitch + jc * M;
 #pragma unroll
-                for (int p = 0; p < M; ++p)
+                for (int p = 0; p < M; ++p) {
+                    float o[M];
 #pragma unroll
-                    for (int q = 0; q < M; ++q) {
-                        const float val = Y[e][p][q];
-                        dst[p * sh.cols_pitch + q] = (f16)(val < floor_at ? floor_at : val);
-                    }
+                    for (int q = 0; q < M; ++q) o[q] = Y[e][p][q] < floor_at ? floor_at : Y[e][p][q];
+                    store_block_row<M>(dst + p * sh.cols_pitch, o);
+                }
             }
         }
         __syncthreads();

@@ -58,6 +58,39 @@ __device__ __forceinline__ void output_transform_1d(const float (&v)[N], float (
     }
 }
 
+// A row of M results to its place in the LDS block, in the widest pieces its alignment allows (M elements are a
+// whole number of them; block pitches are multiples of 4 elements, tile columns multiples of M): a quarter to a
+// half of the LDS instructions of element stores, and conversions two at a time.
+template <int M>
+__device__ __forceinline__ void store_block_row(f16 *dst, const float (&o)[M])
+{
+    typedef _Float16 half4 __attribute__((ext_vector_type(4)));
+    typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+    static_assert(M % 2 == 0, "whole pieces");
+    if constexpr (M % 4 == 0) {
+#pragma unroll
+        for (int q = 0; q < M; q += 4)
+            *reinterpret_cast<half4 *>(__builtin_assume_aligned(dst + q, 8)) = half4{(f16)o[q], (f16)o[q + 1], (f16)o[q + 2], (f16)o[q + 3]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; q += 2) *reinterpret_cast<half2v *>(__builtin_assume_aligned(dst + q, 4)) = half2v{(f16)o[q], (f16)o[q + 1]};
+    }
+}
+template <int M>
+__device__ __forceinline__ void store_block_row(float *dst, const float (&o)[M])
+{
+    typedef float float4v __attribute__((ext_vector_type(4)));
+    typedef float float2v __attribute__((ext_vector_type(2)));
+    if constexpr (M % 4 == 0) {
+#pragma unroll
+        for (int q = 0; q < M; q += 4)
+            *reinterpret_cast<float4v *>(__builtin_assume_aligned(dst + q, 16)) = float4v{o[q], o[q + 1], o[q + 2], o[q + 3]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < M; q += 2) *reinterpret_cast<float2v *>(__builtin_assume_aligned(dst + q, 8)) = float2v{o[q], o[q + 1]};
+    }
+}
+
 struct OutShape {
     int twb;          // tiles per group (all tile rows of the group together)
     int twc;          // tile columns per group

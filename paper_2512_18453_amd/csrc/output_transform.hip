@@ -131,24 +131,22 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
         for (int p = 0; p < M; ++p) {
             float o[M];
             output_transform_1d<N, R, SYM>(z[p], o, coef);
+            if constexpr (RELU) {
 #pragma unroll
-            for (int q = 0; q < M; ++q) {
-                float val = o[q];
-                if constexpr (RELU) val = val < 0.0f ? 0.0f : val;      // NaN stays NaN
-                if constexpr (CF > 0) {
+                for (int q = 0; q < M; ++q) o[q] = o[q] < 0.0f ? 0.0f : o[q];      // NaN stays NaN
+            }
+            if constexpr (CF > 0) {
+#pragma unroll
+                for (int q = 0; q < M; q += kHeldPer) {
                     if constexpr (sizeof(T) == 2) {
-                        const f16 hv = (f16)val;
-                        unsigned short bits;
-                        __builtin_memcpy(&bits, &hv, 2);
-                        const int at = p * M + q;
-                        if ((at & 1) == 0) held[at >> 1] = bits;
-                        else held[at >> 1] |= (unsigned int)bits << 16;
+                        const f16 pair[2] = {(f16)o[q], (f16)o[q + 1]};
+                        __builtin_memcpy(&held[(p * M + q) / 2], pair, 4);
                     } else {
-                        held[p * M + q] = val;
+                        held[p * M + q] = o[q];
                     }
-                } else {
-                    store_from_f32(dst + p * sh.cols_pitch + q, val);
                 }
+            } else {
+                store_block_row<M>(dst + p * sh.cols_pitch, o);
             }
         }
     }
@@ -156,18 +154,23 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
         __syncthreads();                      // the operands in LDS have been read
         if (active) {
             T *dst = lds + k_in * sh.k_pitch + jr * M * sh.cols_pitch + jc * M;
+            // (pieces as in store_block_row: their alignment is the same)
+            typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+            constexpr int WORDS = M * (int)sizeof(T) / 4;
 #pragma unroll
-            for (int p = 0; p < M; ++p)
+            for (int p = 0; p < M; ++p) {
+                unsigned row[WORDS];
+                __builtin_memcpy(row, &held[p * WORDS], WORDS * 4);
+                unsigned *at = reinterpret_cast<unsigned *>(__builtin_assume_aligned(dst + p * sh.cols_pitch, 4));
+                if constexpr (WORDS % 2 == 0) {
 #pragma unroll
-                for (int q = 0; q < M; ++q) {
-                    const int at = p * M + q;
-                    if constexpr (sizeof(T) == 2) {
-                        const unsigned short bits = (unsigned short)(held[at >> 1] >> ((at & 1) * 16));
-                        __builtin_memcpy(dst + p * sh.cols_pitch + q, &bits, 2);
-                    } else {
-                        __builtin_memcpy(dst + p * sh.cols_pitch + q, &held[at], 4);
-                    }
+                    for (int w = 0; w < WORDS; w += 2)
+                        *reinterpret_cast<u32x2 *>(__builtin_assume_aligned(at + w, 8)) = u32x2{row[w], row[w + 1]};
+                } else {
+#pragma unroll
+                    for (int w = 0; w < WORDS; ++w) at[w] = row[w];
                 }
+            }
         }
     }
     __syncthreads();
@@ -209,8 +212,29 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     // wide reads of M there)
     int twb_max = CF > 0 ? 8 : 16;
     while (twb_max > 1 && lds_need(twb_max, 1) > 64 * 1024) --twb_max;
+    const bool aligned = ((uintptr_t)y % 16) == 0;
     sh.groups = ceil_div(g.tiles_w, twb_max);
-    const int twb = ceil_div(g.tiles_w, sh.groups);     // tiles of one tile row per group
+    int twb = ceil_div(g.tiles_w, sh.groups);           // tiles of one tile row per group
+    if ((sizeof(T) == 2 || M >= 4) && sh.groups > 1 && g.W % PE == 0 && aligned && !(flags & NOVA_FLAG_POOL2)) {
+        // Several groups per row: their width decides how the rows leave -- in 16-byte pieces if it is a whole number
+        // of them, and without sharing a 64-byte sector between two workgroups if it is a whole number of
+        // those; last groups narrower than the others leave lanes idle.  Taken: the evenly cut width or a
+        // vectorisable one, by the lowest estimate of slots launched * (1 + 2 / width) * 1.2 for shared sectors
+        // * 1.3 for element stores (1.5 where no M is read and the stores weigh more).  us per launch, even
+        // cut / this rule: 64 ch @224x224 batch 4 F(6,3) 30.9 / 22.6, F(4,3) 34.7 / 27.4, 128 ch @96x96 batch 8 F(4,3)
+        // 25.2 / 20.7; whole call 3 -> 64 @224x224 batch 32 F(8,3) 172 / 138.  (Pooled rows are a quarter of the
+        // bytes: 20.7 / 24.3, hence not for them.)
+        double best = 0.0;
+        const int even = twb;
+        for (int c = 1; c <= twb_max; ++c) {
+            const bool pieces = (c * M) % PE == 0;
+            if (!pieces && c != even) continue;
+            const double stores = !pieces ? (CF > 0 ? 1.5 : 1.3) : (c * M * (int)sizeof(T)) % 64 == 0 ? 1.0 : 1.2;
+            const double cost = (double)ceil_div(g.tiles_w, c) * c * (1.0 + 2.0 / c) * stores;
+            if (best == 0.0 || cost < best) { best = cost; twb = c; }
+        }
+        sh.groups = ceil_div(g.tiles_w, twb);
+    }
     // narrow images: a group spans the width; give it as many tile rows as keep it within 8 tiles
     // (more per workgroup measured slower: 56 x 56 with 2 x 7 tiles 42 us against 39 us with 7)
     int trb = 1;
@@ -225,7 +249,6 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     if (lds_bytes > 64 * 1024) return (int)hipErrorInvalidValue;
     if (CF == 0 && (size_t)g.k_blocks * g.Tp * kChanBlock * sizeof(MT) >= ((size_t)1 << 32)) return (int)hipErrorInvalidValue;
     if (CF > 0 && g.C > CF) return (int)hipErrorInvalidValue;
-    const bool aligned = ((uintptr_t)y % 16) == 0;
     const bool vec = g.W % PE == 0 && aligned && (sh.groups == 1 || (twb * M) % PE == 0);
     // (W >= 2 and at least two pieces: the reciprocals used for the divisions do not exist for 1)
     const bool flat = !vec && aligned && sh.groups == 1 && g.W >= 2 && sh.rows * g.W + 2 * (PE - 1) >= 2 * PE &&
