@@ -73,45 +73,16 @@ __device__ __forceinline__ void input_transform_rows(const float (&v)[N], float 
 // [0, SP), half 1 rows [SP, N); SP is odd so that no (+a, -a) pair of rows is cut.
 template <int N> struct RowSplit { static constexpr int value = ((N / 2) % 2 == 1) ? N / 2 : N / 2 + 1; };
 
-// Few-channel kernel: rows [LO, HI) of one window that lies in LDS at `tile` (columns fastest).
-template <int N, typename T, bool SYM, int LO, int HI>
-__device__ __forceinline__ void transform_rows_of_tile(const T *tile, int row_pitch, T *mine, const InCoef<N> &coef)
-{
-    // columns of the tile first: tmp[i - LO][b] = sum_a B^T[i][a] d[a][b] for this wave's rows i
-    float tmp[HI - LO][N];
-    T win[N][N];                                  // the tile window d[a][b] in storage format
-#pragma unroll
-    for (int a = 0; a < N; ++a)
-#pragma unroll
-        for (int b = 0; b < N; ++b) win[a][b] = tile[a * row_pitch + b];
-#pragma unroll
-    for (int b = 0; b < N; ++b) {
-        float d[N], o[HI - LO];
-#pragma unroll
-        for (int a = 0; a < N; ++a) d[a] = (float)win[a][b];
-        input_transform_rows<N, SYM, LO, HI>(d, o, coef);
-#pragma unroll
-        for (int i = 0; i < HI - LO; ++i) tmp[i][b] = o[i];
-    }
-    // then along each of those rows: V[i][j] = sum_b tmp[i][b] B^T[j][b], rounded to storage
-#pragma unroll
-    for (int i = LO; i < HI; ++i) {
-        float o[N];
-        input_transform_rows<N, SYM, 0, N>(tmp[i - LO], o, coef);
-#pragma unroll
-        for (int jj = 0; jj < N; ++jj) mine[(i - LO) * N + jj] = round_twice(o[jj], (T *)nullptr);
-    }
-}
-
 // A workgroup takes TB tiles that are neighbours in t (whatever tile rows and images they belong to) and one
-// block of 32 channels.  A word of LDS holds one pixel of CPT channels: two neighbouring channels in
-// binary16, one in binary32.
-template <int N, typename T>
+// block of CH channels: 32, or 4 for the compact layout of the first layer.  A word of LDS holds one pixel of CPT
+// channels: two neighbouring channels in binary16, one in binary32.
+template <int N, typename T, int CH>
 struct TileBlock {
     static constexpr int CPT = 4 / (int)sizeof(T);              // channels per word
-    static constexpr int GP = kChanBlock / CPT;                 // words per pixel of a 32-channel block
+    static constexpr int GP = CH / CPT;                         // words per pixel of a channel block
     static constexpr int RS = N >= 8 ? 2 : 1;                   // threads that share the transform rows of one tile and word
-    static constexpr int TB = sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8);
+    static constexpr int TB = CH == 4 ? 64 / GP : sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8);
+    static constexpr int RUN = TB < 16 ? TB : 16;               // neighbouring tiles whose lanes exchange columns (16: a DPP row)
     static constexpr int THREADS = TB * GP * RS;
     static constexpr int WAVES_PER_XI = TB * GP / 64;
     static constexpr int TILE_PAD = 2;
@@ -246,13 +217,13 @@ __device__ __forceinline__ void transform_window(const unsigned *win, T *v_block
 
 // Groups of tiles: a row of row_tiles consecutive t (the whole batch, or one tile row of an image) is cut into
 // groups_per_row groups of `per` tiles.
-template <int N, int R, typename T, bool SYM, bool STREAM, int MAXIMA>
-__global__ void __launch_bounds__((TileBlock<N, T>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
+template <int N, int R, typename T, bool SYM, int CH, bool STREAM, int MAXIMA>
+__global__ void __launch_bounds__((TileBlock<N, T, CH>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
 input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H, int W, int tiles_h, int tiles_w,
                        int c_blocks, unsigned t_groups, int row_tiles, int groups_per_row, int per, int Ttot, long long x_elems,
                        int by_element, float *partials, int n_part, InCoef<N> coef)
 {
-    using B = TileBlock<N, T>;
+    using B = TileBlock<N, T, CH>;
     constexpr int M = N - R + 1;                 // outputs per tile side = tile stride
     constexpr int PAD = (R - 1) / 2;             // zero border of the convolution
     constexpr int CPT = B::CPT;
@@ -279,8 +250,8 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
         const int t = t0 + (j < count ? j : count - 1);
         const int trow = t / tiles_w, tc = t - trow * tiles_w, img = trow / tiles_h, tr = trow - img * tiles_h;
         const int h_lo = tr * M - PAD, w_lo = tc * M - PAD;
-        const int c_lim = C - cb * kChanBlock;
-        const T *planes = x + ((long long)img * C + (long long)cb * kChanBlock) * H * W;     // this block's first channel plane
+        const int c_lim = C - cb * CH;
+        const T *planes = x + ((long long)img * C + (long long)cb * CH) * H * W;     // this block's first channel plane
         unsigned *tile_lds = lds + j * B::TILE;
         if (by_element) {
             // planes too large for 32-bit offsets, or x shorter than a window row
@@ -302,10 +273,12 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
             const int HW = H * W, first = h_lo * W + w0;
             // x may end before the M elements of a row do; then they are taken from the end of x and moved
             const long long remaining = x_elems - (planes - x);
-            const bool tail = __any(remaining < (long long)(c_lim < kChanBlock ? c_lim : kChanBlock) * HW + M);
+            const bool tail = __any(remaining < (long long)(c_lim < CH ? c_lim : CH) * HW + M);
             const int room = remaining < 0x7fffffffLL ? (int)remaining : 0x7fffffff;
-            // the group's first tile loads its left halo, its last tile the right one
-            const bool lead = j == 0 && tc > 0, trail = j == count - 1 && tc < tiles_w - 1;
+            // the first tile of a run of lanes loads its left halo, the last one the right one (never the same tile: a run
+            // has several, and where the group ends inside it, the last tile's lane is repeated)
+            const bool first_lane = j % B::RUN == 0, last_lane = j % B::RUN == B::RUN - 1 || j == count - 1;
+            const bool lead = first_lane && tc > 0, trail = last_lane && tc < tiles_w - 1;
             const int halo_w = lead ? w0 - PAD : w0 + M;
             unsigned raw[ITEMS][CPT][WORDS], halo[ITEMS][CPT][PAD];
 #pragma unroll
@@ -332,7 +305,7 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
                     }
                 }
             }
-            const bool any_right = __any(valid < M), odd_channel = CPT == 2 && c_lim < kChanBlock && (c_lim & 1);
+            const bool any_right = __any(valid < M), odd_channel = CPT == 2 && c_lim < CH && (c_lim & 1);
 #pragma unroll
             for (int k = 0; k < ITEMS; ++k) {
                 const int rest = (tid + k * B::THREADS) / B::TB, g = rest / N, a = rest - g * N;
@@ -381,8 +354,8 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
                 for (int q = 0; q < PAD; ++q) {
                     const unsigned before = (unsigned)__builtin_amdgcn_update_dpp(0, (int)px[M + q], 0x111, 0xf, 0xf, true);
                     const unsigned after = (unsigned)__builtin_amdgcn_update_dpp(0, (int)px[PAD + q], 0x101, 0xf, 0xf, true);
-                    px[q] = j == 0 ? (tc > 0 ? edge[q] : 0u) : tc > 0 ? before : 0u;
-                    px[PAD + M + q] = tc == tiles_w - 1 ? 0u : j == count - 1 ? edge[q] : after;
+                    px[q] = tc == 0 ? 0u : first_lane ? edge[q] : before;
+                    px[PAD + M + q] = tc == tiles_w - 1 ? 0u : last_lane ? edge[q] : after;
                 }
                 unsigned *dst = tile_lds + g * B::WIN + a * N;
 #pragma unroll
@@ -397,9 +370,9 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
     const int g = tid % B::GP, j = tid / B::GP % B::TB;
     const int half = __builtin_amdgcn_readfirstlane(tid / (B::GP * B::TB));
     const unsigned *win = lds + j * B::TILE + g * B::WIN;
-    T *v_block = V + ((size_t)cb * Ttot + t0) * kChanBlock;
-    const size_t xi_stride = (size_t)c_blocks * Ttot * kChanBlock;
-    const unsigned lane_off = (unsigned)(j * kChanBlock + g * CPT) * (unsigned)sizeof(T);
+    T *v_block = V + ((size_t)cb * Ttot + t0) * CH;
+    const size_t xi_stride = (size_t)c_blocks * Ttot * CH;
+    const unsigned lane_off = (unsigned)(j * CH + g * CPT) * (unsigned)sizeof(T);
     const bool active = j < count;
     if constexpr (MAXIMA == kMaxNone)
         if (!active) return;                     // (for the maxima every lane stays: it holds the group's last tile)
@@ -440,7 +413,7 @@ static void fill_in_coef(const nova_transforms *t, InCoef<N> &k)
 template <int N, typename T>
 static int maxima_count(const Geometry &g, int maxima)
 {
-    using B = TileBlock<N, T>;
+    using B = TileBlock<N, T, kChanBlock>;
     const long long blocks = (g.T + B::TB - 1) / B::TB * g.c_blocks;
     const long long count = maxima == kMaxTensor ? blocks * (B::THREADS / 64) : maxima == kMaxPosition ? blocks * B::WAVES_PER_XI * 4 : 0;
     return count > 0x7fffffffLL ? -1 : (int)count;
@@ -450,7 +423,7 @@ template <int N, int R, typename T>
 static int launch_it(const nova_transforms *t, const void *x, void *V, const Geometry &g, bool stream_x, int maxima, float *partials,
                      hipStream_t stream)
 {
-    using B = TileBlock<N, T>;
+    using B = TileBlock<N, T, kChanBlock>;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
     if (g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
@@ -458,15 +431,15 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     // streaming hint on x a group keeps to one tile row instead: what it shares with a neighbour is not
     // found in the cache again (56 x 56 x 256 channels, batch 32, F(8,3), whole call: 110 us with rows and the
     // hint, 114 with the hint alone, 116 with neither; the transform alone 34 / 39 / 29 us).
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, false, kMaxNone>
-                             : input_transform_kernel<N, R, T, false, false, kMaxNone>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kChanBlock, false, kMaxNone>;
     if (maxima != kMaxNone && !t->symmetric) return (int)hipErrorInvalidValue;
-    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, false, kMaxTensor>;
-    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, false, kMaxPosition>;
+    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxTensor>;
+    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxPosition>;
     bool rows = false;
     if constexpr (N >= 8 && sizeof(T) == 2)
         if (stream_x && maxima == kMaxNone && t->symmetric && g.tiles_w > B::TB * 3 / 4 && g.tiles_w <= B::TB) {
-            kern = input_transform_kernel<N, R, T, true, true, kMaxNone>;
+            kern = input_transform_kernel<N, R, T, true, kChanBlock, true, kMaxNone>;
             rows = true;
         }
     const int row_tiles = rows ? g.tiles_w : (int)g.T;
@@ -532,95 +505,29 @@ int launch_input_transform_maxima(const nova_transforms *t, const void *x, void 
     return launch_it_any(t, x, V, g, dtype, false, per_position ? kMaxPosition : kMaxTensor, partials, (hipStream_t)stream);
 }
 
-// ---- Few input channels (C <= 4): V in the compact layout Vc [n*n][T][4] that the few-channel
-// output transform reads (no 32-channel blocks: 3 of 32 channels would carry data).  One pair of
-// waves takes 16 neighbouring tiles of a tile row and the 4 channels, lane = (tile, channel); the
-// two waves split the transform rows as above.  Same arithmetic contract; channels >= C are zero.
+// ---- Few input channels (C <= 4): V in the compact layout Vc [n*n][T][4] that the few-channel output transform
+// reads (no 32-channel blocks: 3 of 32 channels would carry data).  The same kernel with blocks of 4
+// channels: a wave takes 32 tiles (binary16) or 16 (binary32) and stores 256 contiguous bytes per position.
+// (A kernel of its own, strip staged element by element, one channel per lane, 2-byte stores: 24.7 us on
+// 3 x 224 x 224, batch 32, F(8,3); this one 12.0.)
 constexpr int kFewIn = 4;                  // channels
-constexpr int kFewTiles = 64 / kFewIn;     // tiles per group
-
-template <int N, int R, typename T, bool SYM>
-__global__ void __launch_bounds__(128)
-input_transform_few_kernel(const T *__restrict__ x, T *__restrict__ Vc, int C, int H, int W,
-                           int tiles_h, int tiles_w, int groups, long long Ttot, int row_pitch, InCoef<N> coef)
-{
-    constexpr int M = N - R + 1;
-    constexpr int PAD = (R - 1) / 2;
-    constexpr int SP = RowSplit<N>::value;
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    T *lds = reinterpret_cast<T *>(lds_raw);
-
-    unsigned bid = blockIdx.x;
-    const int tg = bid % groups; bid /= groups;
-    const int tr = bid % tiles_h; bid /= tiles_h;
-    const int img = bid;
-    const int tc0 = tg * kFewTiles;
-    const int h_lo = tr * M - PAD, w_lo = tc0 * M - PAD;
-    const int cols = kFewTiles * M + R - 1;
-    const int ch_pitch = N * row_pitch;
-
-    // strip [4 channels][N rows][cols], lanes along W; outside the image and for channels >= C: zero
-    const unsigned cols_magic = (unsigned)((((unsigned long long)1 << 32) + cols - 1) / cols);
-    const int slots = kFewIn * N * cols;
-    constexpr int RT = 8;
-    for (int base = threadIdx.x; base < slots; base += RT * (int)blockDim.x) {
-        T val[RT];
-        int dst[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const int s = base + r * (int)blockDim.x;
-            const int line = (int)__umulhi((unsigned)s, cols_magic);       // (channel, row)
-            const int q = s - line * cols;
-            const int c = line / N, a = line - c * N;
-            const int h = h_lo + a, w = w_lo + q;
-            const bool ok = s < slots && c < C && h >= 0 && h < H && w >= 0 && w < W;
-            dst[r] = s < slots ? c * ch_pitch + a * row_pitch + q : -1;
-            val[r] = (T)0.0f;
-            if (ok) val[r] = x[(((size_t)img * C + c) * H + h) * W + w];
-        }
-#pragma unroll
-        for (int r = 0; r < RT; ++r)
-            if (dst[r] >= 0) lds[dst[r]] = val[r];
-    }
-    __syncthreads();
-
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int j = lane / kFewIn, c_in = lane % kFewIn;
-    if (tc0 + j >= tiles_w) return;
-    const T *tile = lds + c_in * ch_pitch + j * M;
-    constexpr int ROWS_MAX = SP > N - SP ? SP : N - SP;
-    T res[ROWS_MAX * N];
-    if (wave == 0) transform_rows_of_tile<N, T, SYM, 0, SP>(tile, row_pitch, res, coef);
-    else           transform_rows_of_tile<N, T, SYM, SP, N>(tile, row_pitch, res, coef);
-
-    // a wave writes 64 consecutive values (16 tiles x 4 channels) per xi
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const int first = wave_u == 0 ? 0 : SP * N, count = wave_u == 0 ? SP * N : (N - SP) * N;
-    const long long t0 = ((long long)img * tiles_h + tr) * tiles_w + tc0;
-    const unsigned off = (unsigned)lane * (unsigned)sizeof(T);
-#pragma unroll
-    for (int e = 0; e < ROWS_MAX * N; ++e)
-        if (e < count) {
-            T *plane = Vc + ((size_t)(first + e) * Ttot + t0) * kFewIn;
-            *reinterpret_cast<NOVA_GLOBAL T *>(plane_element(plane, off)) = res[e];
-        }
-}
 
 template <int N, int R, typename T>
 static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g, hipStream_t stream)
 {
-    constexpr int M = N - R + 1;
-    if (g.C > kFewIn) return (int)hipErrorInvalidValue;
+    using B = TileBlock<N, T, kFewIn>;
+    if (g.C > kFewIn || g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
-    const int groups = ceil_div(g.tiles_w, kFewTiles);
-    const int row_pitch = (kFewTiles * M + R - 1 + 3) / 4 * 4;
-    const size_t lds_bytes = (size_t)kFewIn * N * row_pitch * sizeof(T);
-    const long long blocks = (long long)groups * g.tiles_h * g.N;
+    const long long blocks = (g.T + B::TB - 1) / B::TB;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    auto kern = t->symmetric ? input_transform_few_kernel<N, R, T, true> : input_transform_few_kernel<N, R, T, false>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(128), lds_bytes, stream,
-                       (const T *)x, (T *)Vc, g.C, g.H, g.W, g.tiles_h, g.tiles_w, groups, g.T, row_pitch, coef);
+    const long long x_elems = (long long)g.N * g.C * g.H * g.W;
+    const int by_element = x_elems < N - R + 1 || (long long)kFewIn * g.H * g.W >= (1LL << 30) ? 1 : 0;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kFewIn, false, kMaxNone>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)Vc, g.C, g.H, g.W,
+                       g.tiles_h, g.tiles_w, 1, (unsigned)blocks, (int)g.T, (int)blocks, B::TB, (int)g.T, x_elems, by_element,
+                       (float *)nullptr, 0, coef);
     return (int)hipGetLastError();
 }
 

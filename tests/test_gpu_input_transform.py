@@ -60,6 +60,29 @@ def test_group_edges_bit_for_bit(m, r, N, C, H, W, symmetric):
             assert np.array_equal(got[:, :, :C].astype(np.float64), want), (dtype, shift)
 
 
+@pytest.mark.parametrize("m,r,N,C,H,W", [(8, 3, 1, 3, 8, 250), (8, 3, 1, 1, 8, 136), (8, 3, 2, 4, 9, 264), (6, 3, 1, 2, 6, 97),
+                                         (4, 3, 3, 3, 5, 61), (4, 5, 1, 1, 4, 130), (6, 5, 9, 3, 7, 11), (2, 3, 1, 3, 2, 65)])
+def test_compact_layout_of_few_channels(m, r, N, C, H, W):
+    # with at most four channels the single call keeps V as [position][tile][4], at the start of its workspace:
+    # runs of 16 tiles whose lanes exchange columns, groups of 16 and 32
+    size = m + r - 3
+    points = synth.point_set("standard" if size == 2 else "nova", size)
+    t = nova.nova_make_transforms(points, m, r)
+    rng = np.random.default_rng(m + W)
+    T = N * -(-H // m) * -(-W // m)
+    for dtype, storage in ((np.float16, 16), (np.float32, 32)):
+        print(f"[case] compact input transform F({m},{r}) {np.dtype(dtype).name} N={N} C={C} H={H} W={W}", flush=True)
+        x = rng.standard_normal((N, C, H, W)).astype(dtype)
+        _, _, want, _ = conv.winograd_conv2d_emulated(x.astype(np.float64), np.zeros((1, C, r, r)), [Fr(a, b) for a, b in points], m,
+                                                      storage=storage, want_intermediates=True)
+        dt = nova.NOVA_F16 if storage == 16 else nova.NOVA_F32
+        ws = torch.zeros(nova.nova_conv2d_workspace_bytes(N, C, H, W, 5, m, dt, 0, N, r), dtype=torch.uint8, device=DEV)
+        U = torch.zeros(nova.nova_filter_bytes(5, C, m, dt, r) // (storage // 8), dtype=torch.from_numpy(x).dtype, device=DEV)
+        nova.nova_winograd_conv2d(t, torch.from_numpy(x).to(DEV), U, 5, workspace=ws)
+        Vc = ws.view(U.dtype)[:t.n * t.n * T * 4].cpu().numpy().reshape(t.n * t.n, T, 4).astype(np.float64)
+        assert np.array_equal(Vc[:, :, :C], want) and not Vc[:, :, C:].any()
+
+
 def test_streamed_input_gives_the_same_result():
     # x, V and M together larger than the last-level cache and one tile row per group: the whole batch in one
     # pass against slabs that fit
