@@ -127,7 +127,10 @@ extern "C" int nova_input_transform(const nova_transforms *t, const void *x, voi
     if (!x || !V || !dims_ok(N, C, H, W, 1) || !dtype_ok(dtype)) return NOVA_EINVAL;
     const Geometry g = make_geometry(N, C, H, W, 1, t->m, t->r);
     if (V_bytes < v_bytes(g, dtype)) return NOVA_ENOSPC;
-    return hip_result(launch_input_transform(t, x, V, g, dtype, stream));
+    // (as the whole call decides; the products that follow are not known here: taken as for K = C)
+    const size_t m_like = m_bytes(make_geometry(N, 1, H, W, C, t->m, t->r), dtype, 0);
+    const bool stream_x = (size_t)N * C * H * W * dtype_size(dtype) + v_bytes(g, dtype) + m_like > kDefaultSlabBytes;
+    return hip_result(launch_input_transform(t, x, V, g, dtype, stream, stream_x));
 }
 
 extern "C" int nova_contract(const nova_transforms *t, const void *U, const void *V, void *M, size_t M_bytes,
@@ -370,4 +373,4 @@ extern "C" const char *nova_strerror(int code)
 }
 
 extern "C" int nova_last_hip_error(void) { return g_last_hip_error; }
-extern "C" const char *nova_version(void) { return "libnova 0.5 (gfx950)"; }
+extern "C" const char *nova_version(void) { return "libnova 0.6 (gfx950)"; }
