@@ -210,8 +210,6 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     char *Vbuf = (char *)workspace;
     char *Mbuf = Vbuf + v_part;
     const bool few = few_channels(C);
-    if (few)
-        if (int err = launch_pack_few_channels(U, Mbuf, make_geometry(1, C, H, W, K, m, r), dtype, stream)) return hip_result(err);
     for (int n0 = 0; n0 < N; n0 += (int)imgs) {
         const int nb = (N - n0 < imgs) ? N - n0 : (int)imgs;
         const Geometry g = make_geometry(nb, C, H, W, K, m, r);
@@ -219,7 +217,7 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
         const size_t y_image = (flags & NOVA_FLAG_POOL2) ? (size_t)K * (H / 2) * (W / 2) : (size_t)K * H * W;
         char *ys = (char *)y + (size_t)n0 * y_image * es;
         if (few) {
-            if (int err = launch_input_transform_few(t, xs, Vbuf, g, dtype, stream)) return hip_result(err);
+            if (int err = launch_input_transform_few(t, xs, Vbuf, g, n0 == 0 ? U : nullptr, Mbuf, dtype, stream)) return hip_result(err);
             if (int err = launch_output_transform_few(t, Vbuf, Mbuf, ys, g, dtype, flags, stream)) return hip_result(err);
             continue;
         }

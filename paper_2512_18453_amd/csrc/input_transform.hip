@@ -215,13 +215,19 @@ __device__ __forceinline__ void transform_window(const unsigned *win, T *v_block
     }
 }
 
+// Filters to pack beside the transform (blocks of 4 channels only): to[row][c] = from[row][0][c] for c < 4, a row
+// being (xi, k) of U [n*n][1][Kp][32].  Done by workgroups of the same launch: a launch of its own cost 3.5 us of
+// host time and 3-5 us on the device (3 -> 64 @224x224 batch 32 F(8,3), whole call 125 -> 121 us).
+template <typename T>
+struct PackFilters { const T *from; T *to; long long rows; };
+
 // Groups of tiles: a row of row_tiles consecutive t (the whole batch, or one tile row of an image) is cut into
 // groups_per_row groups of `per` tiles.
 template <int N, int R, typename T, bool SYM, int CH, bool STREAM, int MAXIMA>
 __global__ void __launch_bounds__((TileBlock<N, T, CH>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
 input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H, int W, int tiles_h, int tiles_w,
                        int c_blocks, unsigned t_groups, int row_tiles, int groups_per_row, int per, int Ttot, long long x_elems,
-                       int by_element, float *partials, int n_part, InCoef<N> coef)
+                       int by_element, float *partials, int n_part, PackFilters<T> pack, InCoef<N> coef)
 {
     using B = TileBlock<N, T, CH>;
     constexpr int M = N - R + 1;                 // outputs per tile side = tile stride
@@ -233,7 +239,18 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) unsigned lds[];
 
-    const unsigned bid = xcd_local_block_id(blockIdx.x, gridDim.x);
+    const unsigned tile_blocks = t_groups * (unsigned)c_blocks;
+    if constexpr (CH == 4) {
+        if (blockIdx.x >= tile_blocks) {                         // the workgroups after the tiles' pack filters
+            const long long row = (long long)(blockIdx.x - tile_blocks) * B::THREADS + threadIdx.x;
+            if (row < pack.rows) {
+#pragma unroll
+                for (int c = 0; c < CH; ++c) pack.to[row * CH + c] = pack.from[row * kChanBlock + c];
+            }
+            return;
+        }
+    }
+    const unsigned bid = xcd_local_block_id(blockIdx.x, tile_blocks);
     const int cb = (int)(bid / t_groups);
     const int group = (int)(bid - (unsigned)cb * t_groups), group_row = group / groups_per_row;
     const int in_row = (group - group_row * groups_per_row) * per;                  // the group's first tile within its row
@@ -452,7 +469,7 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     const int by_element = x_elems < N - R + 1 || (long long)kChanBlock * g.H * g.W >= (1LL << 30) ? 1 : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, g.c_blocks, (unsigned)t_groups, row_tiles, groups_per_row, per, (int)g.T, x_elems,
-                       by_element, partials, maxima_count<N, T>(g, maxima), coef);
+                       by_element, partials, maxima_count<N, T>(g, maxima), PackFilters<T>{nullptr, nullptr, 0}, coef);
     return (int)hipGetLastError();
 }
 
@@ -513,7 +530,8 @@ int launch_input_transform_maxima(const nova_transforms *t, const void *x, void 
 constexpr int kFewIn = 4;                  // channels
 
 template <int N, int R, typename T>
-static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g, hipStream_t stream)
+static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g, const void *U, void *Uc,
+                         hipStream_t stream)
 {
     using B = TileBlock<N, T, kFewIn>;
     if (g.C > kFewIn || g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
@@ -525,9 +543,12 @@ static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, cons
     const int by_element = x_elems < N - R + 1 || (long long)kFewIn * g.H * g.W >= (1LL << 30) ? 1 : 0;
     auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, kMaxNone>
                              : input_transform_kernel<N, R, T, false, kFewIn, false, kMaxNone>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)Vc, g.C, g.H, g.W,
+    const PackFilters<T> pack = {(const T *)U, (T *)Uc, U ? (long long)g.n * g.n * g.Kp : 0};
+    const long long pack_blocks = (pack.rows + B::THREADS - 1) / B::THREADS;
+    if (blocks + pack_blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks + pack_blocks)), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)Vc, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, 1, (unsigned)blocks, (int)g.T, (int)blocks, B::TB, (int)g.T, x_elems, by_element,
-                       (float *)nullptr, 0, coef);
+                       (float *)nullptr, 0, pack, coef);
     return (int)hipGetLastError();
 }
 
@@ -537,22 +558,22 @@ size_t few_channels_input_bytes(const Geometry &g, int dtype)
 }
 
 int launch_input_transform_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g,
-                               int dtype, void *stream)
+                               const void *U, void *Uc, int dtype, void *stream)
 {
     hipStream_t s = (hipStream_t)stream;
     const bool h = dtype == NOVA_F16;
     if (t->r == 3) {
         switch (t->n) {
-        case 4: return h ? launch_it_few<4, 3, f16>(t, x, Vc, g, s) : launch_it_few<4, 3, float>(t, x, Vc, g, s);
-        case 6: return h ? launch_it_few<6, 3, f16>(t, x, Vc, g, s) : launch_it_few<6, 3, float>(t, x, Vc, g, s);
-        case 8: return h ? launch_it_few<8, 3, f16>(t, x, Vc, g, s) : launch_it_few<8, 3, float>(t, x, Vc, g, s);
-        case 10: return h ? launch_it_few<10, 3, f16>(t, x, Vc, g, s) : launch_it_few<10, 3, float>(t, x, Vc, g, s);
+        case 4: return h ? launch_it_few<4, 3, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<4, 3, float>(t, x, Vc, g, U, Uc, s);
+        case 6: return h ? launch_it_few<6, 3, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<6, 3, float>(t, x, Vc, g, U, Uc, s);
+        case 8: return h ? launch_it_few<8, 3, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<8, 3, float>(t, x, Vc, g, U, Uc, s);
+        case 10: return h ? launch_it_few<10, 3, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<10, 3, float>(t, x, Vc, g, U, Uc, s);
         }
     } else if (t->r == 5) {
         switch (t->n) {
-        case 6: return h ? launch_it_few<6, 5, f16>(t, x, Vc, g, s) : launch_it_few<6, 5, float>(t, x, Vc, g, s);
-        case 8: return h ? launch_it_few<8, 5, f16>(t, x, Vc, g, s) : launch_it_few<8, 5, float>(t, x, Vc, g, s);
-        case 10: return h ? launch_it_few<10, 5, f16>(t, x, Vc, g, s) : launch_it_few<10, 5, float>(t, x, Vc, g, s);
+        case 6: return h ? launch_it_few<6, 5, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<6, 5, float>(t, x, Vc, g, U, Uc, s);
+        case 8: return h ? launch_it_few<8, 5, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<8, 5, float>(t, x, Vc, g, U, Uc, s);
+        case 10: return h ? launch_it_few<10, 5, f16>(t, x, Vc, g, U, Uc, s) : launch_it_few<10, 5, float>(t, x, Vc, g, U, Uc, s);
         }
     }
     return (int)hipErrorInvalidValue;

@@ -121,15 +121,14 @@ bool fused_contract_output_preferred(const nova_transforms *t, const Geometry &g
 int launch_fused_contract_output(const nova_transforms *t, const void *U, const void *V, void *y, const Geometry &g,
                                  int dtype, int flags, void *stream);
 // Few input channels (C <= few_channels_limit()): the output transform forms the products itself
-// from V and a packed copy Uc of the filters' first channels (few_channels_filter_bytes), which
-// launch_pack_few_channels writes from U.
+// from V and a packed copy Uc of the filters' first channels (few_channels_filter_bytes).
 int few_channels_limit();
 size_t few_channels_filter_bytes(const Geometry &g, int dtype);
-// ... and reads V in the compact layout [n*n][T][4] that launch_input_transform_few writes
+// ... and reads V in the compact layout [n*n][T][4] that launch_input_transform_few writes; that launch also
+// packs Uc from U, if U is given
 size_t few_channels_input_bytes(const Geometry &g, int dtype);
 int launch_input_transform_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g,
-                               int dtype, void *stream);
-int launch_pack_few_channels(const void *U, void *Uc, const Geometry &g, int dtype, void *stream);
+                               const void *U, void *Uc, int dtype, void *stream);
 int launch_output_transform_few(const nova_transforms *t, const void *V, const void *Uc, void *y,
                                 const Geometry &g, int dtype, int flags, void *stream);
 // INT8 operands in the Winograd domain: symmetric quantisation of a blocked tensor [positions][channel

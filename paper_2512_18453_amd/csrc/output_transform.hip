@@ -178,17 +178,6 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
     store_output_block<T, M, STG>(lds, y, img, kb, tr, tc0, K, H, W, tiles_w, sh);
 }
 
-// Uc[xi][k][c] = U[xi][0][k][c] for c < kFewChannels (U [n*n][1][Kp][32])
-template <typename T>
-__global__ void __launch_bounds__(256)
-pack_few_channels_kernel(const T *__restrict__ U, T *__restrict__ Uc, long long rows)
-{
-    const long long row = (long long)blockIdx.x * blockDim.x + threadIdx.x;      // (xi, k)
-    if (row >= rows) return;
-#pragma unroll
-    for (int c = 0; c < kFewChannels; ++c) Uc[row * kFewChannels + c] = U[row * kChanBlock + c];
-}
-
 // CF = 0: Mp holds the products.  CF = kFewChannels: Mp is V, and `few_u` the packed filters.
 template <int N, int R, typename T, typename MT, int CF>
 static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u, void *y, const Geometry &g, int flags,
@@ -326,19 +315,6 @@ int few_channels_limit() { return kFewChannels; }
 size_t few_channels_filter_bytes(const Geometry &g, int dtype)
 {
     return (size_t)g.n * g.n * g.Kp * kFewChannels * dtype_size(dtype);
-}
-
-int launch_pack_few_channels(const void *U, void *Uc, const Geometry &g, int dtype, void *stream)
-{
-    const long long rows = (long long)g.n * g.n * g.Kp;
-    const unsigned blocks = (unsigned)((rows + 255) / 256);
-    if (dtype == NOVA_F16)
-        hipLaunchKernelGGL(pack_few_channels_kernel<f16>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                           (const f16 *)U, (f16 *)Uc, rows);
-    else
-        hipLaunchKernelGGL(pack_few_channels_kernel<float>, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
-                           (const float *)U, (float *)Uc, rows);
-    return (int)hipGetLastError();
 }
 
 int launch_output_transform_few(const nova_transforms *t, const void *V, const void *Uc, void *y,
