@@ -76,11 +76,15 @@ template <int N> struct RowSplit { static constexpr int value = ((N / 2) % 2 == 
 // A workgroup takes TB tiles that are neighbours in t (whatever tile rows and images they belong to) and one
 // block of CH channels: 32, or 4 for the compact layout of the first layer.  A word of LDS holds one pixel of CPT
 // channels: two neighbouring channels in binary16, one in binary32.
-template <int N, typename T, int CH>
+template <int N, typename T, int CH, bool WIDE>
 struct TileBlock {
     static constexpr int CPT = 4 / (int)sizeof(T);              // channels per word
     static constexpr int GP = CH / CPT;                         // words per pixel of a channel block
-    static constexpr int RS = N >= 8 ? 2 : 1;                   // threads that share the transform rows of one tile and word
+    // threads that share the transform rows of one tile and word; WIDE: one per pair of rows (+a, -a), for launches
+    // that leave the chip half empty, where a thread's chain of instructions is what takes the time
+    static constexpr int RS = WIDE ? N / 2 : N >= 8 ? 2 : 1;
+    // rows [bound(i), bound(i + 1)) are thread i's; no (+a, -a) pair (2q + 1, 2q + 2) is cut
+    static constexpr int bound(int i) { return i == 0 ? 0 : i == RS ? N : WIDE ? 2 * i + 1 : RowSplit<N>::value; }
     static constexpr int TB = CH == 4 ? 64 / GP : sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8);
     static constexpr int RUN = TB < 16 ? TB : 16;               // neighbouring tiles whose lanes exchange columns (16: a DPP row)
     static constexpr int THREADS = TB * GP * RS;
@@ -215,6 +219,17 @@ __device__ __forceinline__ void transform_window(const unsigned *win, T *v_block
     }
 }
 
+// The row range of thread `part` (wave-uniform) of the B::RS that share a tile and word.
+template <int N, typename T, bool SYM, int MAXIMA, typename B, int I>
+__device__ __forceinline__ void transform_part(int part, const unsigned *win, T *v_block, size_t xi_stride, unsigned lane_off, bool active,
+                                               const InCoef<N> &coef, float &top, float *partials, int n_part)
+{
+    if constexpr (I + 1 < B::RS) {
+        if (part != I) return transform_part<N, T, SYM, MAXIMA, B, I + 1>(part, win, v_block, xi_stride, lane_off, active, coef, top, partials, n_part);
+    }
+    transform_window<N, T, SYM, MAXIMA, B::bound(I), B::bound(I + 1)>(win, v_block, xi_stride, lane_off, active, coef, top, partials, n_part);
+}
+
 // Filters to pack beside the transform (blocks of 4 channels only): to[row][c] = from[row][0][c] for c < 4, a row
 // being (xi, k) of U [n*n][1][Kp][32].  Done by workgroups of the same launch: a launch of its own cost 3.5 us of
 // host time and 3-5 us on the device (3 -> 64 @224x224 batch 32 F(8,3), whole call 125 -> 121 us).
@@ -223,19 +238,18 @@ struct PackFilters { const T *from; T *to; long long rows; };
 
 // Groups of tiles: a row of row_tiles consecutive t (the whole batch, or one tile row of an image) is cut into
 // groups_per_row groups of `per` tiles.
-template <int N, int R, typename T, bool SYM, int CH, bool STREAM, int MAXIMA>
-__global__ void __launch_bounds__((TileBlock<N, T, CH>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
+template <int N, int R, typename T, bool SYM, int CH, bool WIDE, bool STREAM, int MAXIMA>
+__global__ void __launch_bounds__((TileBlock<N, T, CH, WIDE>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
 input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H, int W, int tiles_h, int tiles_w,
                        int c_blocks, unsigned t_groups, int row_tiles, int groups_per_row, int per, int Ttot, long long x_elems,
                        int by_element, float *partials, int n_part, PackFilters<T> pack, InCoef<N> coef)
 {
-    using B = TileBlock<N, T, CH>;
+    using B = TileBlock<N, T, CH, WIDE>;
     constexpr int M = N - R + 1;                 // outputs per tile side = tile stride
     constexpr int PAD = (R - 1) / 2;             // zero border of the convolution
     constexpr int CPT = B::CPT;
     constexpr int ITEMS = N / B::RS;             // window rows a thread stages
     constexpr int WORDS = M * (int)sizeof(T) / 4;                  // words of a tile's own columns in one row
-    constexpr int SP = RowSplit<N>::value;
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
     extern __shared__ __align__(16) unsigned lds[];
 
@@ -385,7 +399,7 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
 
     // ---- transform: lanes run over the words of a tile's channel block, a wave over 64 / GP tiles
     const int g = tid % B::GP, j = tid / B::GP % B::TB;
-    const int half = __builtin_amdgcn_readfirstlane(tid / (B::GP * B::TB));
+    const int part = __builtin_amdgcn_readfirstlane(tid / (B::GP * B::TB));          // which of the RS row ranges
     const unsigned *win = lds + j * B::TILE + g * B::WIN;
     T *v_block = V + ((size_t)cb * Ttot + t0) * CH;
     const size_t xi_stride = (size_t)c_blocks * Ttot * CH;
@@ -397,12 +411,7 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
     float top = 0.0f;
     float *mine = partials;
     if constexpr (MAXIMA == kMaxPosition) mine += ((size_t)blockIdx.x * B::WAVES_PER_XI + wave % B::WAVES_PER_XI) * 4;
-    if constexpr (B::RS == 1) {
-        transform_window<N, T, SYM, MAXIMA, 0, N>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
-    } else {
-        if (half == 0) transform_window<N, T, SYM, MAXIMA, 0, SP>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
-        else           transform_window<N, T, SYM, MAXIMA, SP, N>(win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
-    }
+    transform_part<N, T, SYM, MAXIMA, B, 0>(part, win, v_block, xi_stride, lane_off, active, coef, top, mine, n_part);
     if constexpr (MAXIMA == kMaxTensor) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
@@ -430,7 +439,7 @@ static void fill_in_coef(const nova_transforms *t, InCoef<N> &k)
 template <int N, typename T>
 static int maxima_count(const Geometry &g, int maxima)
 {
-    using B = TileBlock<N, T, kChanBlock>;
+    using B = TileBlock<N, T, kChanBlock, false>;
     const long long blocks = (g.T + B::TB - 1) / B::TB * g.c_blocks;
     const long long count = maxima == kMaxTensor ? blocks * (B::THREADS / 64) : maxima == kMaxPosition ? blocks * B::WAVES_PER_XI * 4 : 0;
     return count > 0x7fffffffLL ? -1 : (int)count;
@@ -440,7 +449,7 @@ template <int N, int R, typename T>
 static int launch_it(const nova_transforms *t, const void *x, void *V, const Geometry &g, bool stream_x, int maxima, float *partials,
                      hipStream_t stream)
 {
-    using B = TileBlock<N, T, kChanBlock>;
+    using B = TileBlock<N, T, kChanBlock, false>;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
     if (g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
@@ -448,17 +457,25 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     // streaming hint on x a group keeps to one tile row instead: what it shares with a neighbour is not
     // found in the cache again (56 x 56 x 256 channels, batch 32, F(8,3), whole call: 110 us with rows and the
     // hint, 114 with the hint alone, 116 with neither; the transform alone 34 / 39 / 29 us).
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxNone>
-                             : input_transform_kernel<N, R, T, false, kChanBlock, false, kMaxNone>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kChanBlock, false, false, kMaxNone>;
     if (maxima != kMaxNone && !t->symmetric) return (int)hipErrorInvalidValue;
-    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxTensor>;
-    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, kMaxPosition>;
+    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxTensor>;
+    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxPosition>;
     bool rows = false;
     if constexpr (N >= 8 && sizeof(T) == 2)
         if (stream_x && maxima == kMaxNone && t->symmetric && g.tiles_w > B::TB * 3 / 4 && g.tiles_w <= B::TB) {
-            kern = input_transform_kernel<N, R, T, true, kChanBlock, true, kMaxNone>;
+            kern = input_transform_kernel<N, R, T, true, kChanBlock, false, true, kMaxNone>;
             rows = true;
         }
+    int threads = B::THREADS;
+    // no more workgroups than compute units: one thread per pair of transform rows.  us per launch, without / with:
+    // 512 ch @14x14 F(4,3) 6.2 / 5.2, 33 ch @30x41 batch 3 F(4,3) 7.5 / 5.4, binary32 16 ch @32x32 F(4,3) 5.7 / 4.6,
+    // 256 ch @28x28 batch 16 F(8,3) (256 workgroups) 9.4 / 9.0, batch 32 (512) 13.3 / 15.0
+    if (!rows && maxima == kMaxNone && t->symmetric && (g.T + B::TB - 1) / B::TB * g.c_blocks <= device_cu_count()) {
+        kern = input_transform_kernel<N, R, T, true, kChanBlock, true, false, kMaxNone>;
+        threads = TileBlock<N, T, kChanBlock, true>::THREADS;
+    }
     const int row_tiles = rows ? g.tiles_w : (int)g.T;
     const int groups_per_row = ceil_div(row_tiles, B::TB);
     const int per = rows ? ceil_div(row_tiles, groups_per_row) : B::TB;
@@ -467,7 +484,7 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     const long long x_elems = (long long)g.N * g.C * g.H * g.W;
     const int by_element = x_elems < N - R + 1 || (long long)kChanBlock * g.H * g.W >= (1LL << 30) ? 1 : 0;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), B::LDS_BYTES, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, g.c_blocks, (unsigned)t_groups, row_tiles, groups_per_row, per, (int)g.T, x_elems,
                        by_element, partials, maxima_count<N, T>(g, maxima), PackFilters<T>{nullptr, nullptr, 0}, coef);
     return (int)hipGetLastError();
@@ -533,7 +550,7 @@ template <int N, int R, typename T>
 static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g, const void *U, void *Uc,
                          hipStream_t stream)
 {
-    using B = TileBlock<N, T, kFewIn>;
+    using B = TileBlock<N, T, kFewIn, false>;
     if (g.C > kFewIn || g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
@@ -541,8 +558,8 @@ static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, cons
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     const long long x_elems = (long long)g.N * g.C * g.H * g.W;
     const int by_element = x_elems < N - R + 1 || (long long)kFewIn * g.H * g.W >= (1LL << 30) ? 1 : 0;
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, kMaxNone>
-                             : input_transform_kernel<N, R, T, false, kFewIn, false, kMaxNone>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kFewIn, false, false, kMaxNone>;
     const PackFilters<T> pack = {(const T *)U, (T *)Uc, U ? (long long)g.n * g.n * g.Kp : 0};
     const long long pack_blocks = (pack.rows + B::THREADS - 1) / B::THREADS;
     if (blocks + pack_blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;

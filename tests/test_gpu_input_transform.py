@@ -83,6 +83,23 @@ def test_compact_layout_of_few_channels(m, r, N, C, H, W):
         assert np.array_equal(Vc[:, :, :C], want) and not Vc[:, :, C:].any()
 
 
+@pytest.mark.parametrize("m,r", [(2, 3), (4, 3), (6, 3), (8, 3), (2, 5), (4, 5), (6, 5)])
+def test_large_launches_equal_small_ones(m, r):
+    # launches of no more workgroups than compute units share a tile among more threads: the whole batch
+    # (several times as many workgroups) against single images, bit for bit
+    size = m + r - 3
+    t = nova.nova_make_transforms(synth.point_set("standard" if size == 2 else "nova", size), m, r)
+    gen = torch.Generator(device=DEV).manual_seed(m + r)
+    N, C, H, W = 24, 70, 9 * m + 1, 11 * m - 1
+    per, n2 = -(-H // m) * -(-W // m), t.n * t.n
+    for dtype in (torch.float16, torch.float32):
+        print(f"[case] large and small launches F({m},{r}) {dtype}", flush=True)
+        x = torch.randn((N, C, H, W), device=DEV, generator=gen).to(dtype)
+        V = nova.nova_input_transform(t, x).view(n2, 3, N, per, 32)
+        for i in (0, 7, N - 1):
+            assert torch.equal(V[:, :, i], nova.nova_input_transform(t, x[i:i + 1].contiguous()).view(n2, 3, per, 32))
+
+
 def test_streamed_input_gives_the_same_result():
     # x, V and M together larger than the last-level cache and one tile row per group: the whole batch in one
     # pass against slabs that fit
