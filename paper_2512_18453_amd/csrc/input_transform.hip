@@ -307,7 +307,7 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
             const bool tail = __any(remaining < (long long)(c_lim < CH ? c_lim : CH) * HW + M);
             const int room = remaining < 0x7fffffffLL ? (int)remaining : 0x7fffffff;
             // the first tile of a run of lanes loads its left halo, the last one the right one (never the same tile: a run
-            // has several, and where the group ends inside it, the last tile's lane is repeated)
+            // has several; lanes past the group's last tile load it again and stage a window that is never read)
             const bool first_lane = j % B::RUN == 0, last_lane = j % B::RUN == B::RUN - 1 || j == count - 1;
             const bool lead = first_lane && tc > 0, trail = last_lane && tc < tiles_w - 1;
             const int halo_w = lead ? w0 - PAD : w0 + M;
@@ -400,13 +400,15 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
     // ---- transform: lanes run over the words of a tile's channel block, a wave over 64 / GP tiles
     const int g = tid % B::GP, j = tid / B::GP % B::TB;
     const int part = __builtin_amdgcn_readfirstlane(tid / (B::GP * B::TB));          // which of the RS row ranges
-    const unsigned *win = lds + j * B::TILE + g * B::WIN;
+    // (for the maxima every lane stays, and one without a tile reads the group's last one; the place of its own holds
+    // a window that no tile has: the last tile's columns between halos taken from the same tile)
+    const unsigned *win = lds + (MAXIMA == kMaxNone || j < count ? j : count - 1) * B::TILE + g * B::WIN;
     T *v_block = V + ((size_t)cb * Ttot + t0) * CH;
     const size_t xi_stride = (size_t)c_blocks * Ttot * CH;
     const unsigned lane_off = (unsigned)(j * CH + g * CPT) * (unsigned)sizeof(T);
     const bool active = j < count;
     if constexpr (MAXIMA == kMaxNone)
-        if (!active) return;                     // (for the maxima every lane stays: it holds the group's last tile)
+        if (!active) return;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float top = 0.0f;
     float *mine = partials;

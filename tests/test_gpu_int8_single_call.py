@@ -31,7 +31,7 @@ def both(t, x, w, mode, flags=0):
     Vq, sv = nova.nova_quantize_input_int8(t, nova.nova_input_transform(t, x), N, C, H, W, mode)
     M = nova.nova_contract_int8(t, Uq, Vq, su, sv, mode, N, C, H, W, K, dequantise=True)
     want = nova.nova_output_transform(t, M, N, K, H, W, x.dtype, flags)
-    ws = torch.full((nova.nova_conv2d_int8_workspace_bytes(N, C, H, W, K, t.m, nova._dtype_code(x)),), 0xFF, dtype=torch.uint8,
+    ws = torch.full((nova.nova_conv2d_int8_workspace_bytes(N, C, H, W, K, t.m, nova._dtype_code(x), t.r),), 0xFF, dtype=torch.uint8,
                     device=DEV)                                        # NaN everywhere
     return nova.nova_winograd_conv2d_int8(t, x, Uq, su, mode, K, flags=flags, workspace=ws), want, sv
 
@@ -72,3 +72,54 @@ def test_values_that_are_not_finite(bad):
     for mode in MODES:
         got, want, _ = both(t, x, w, mode)
         assert torch.equal(got.nan_to_num(nan=7.0), want.nan_to_num(nan=7.0))
+
+
+# Tile counts that leave the last group of the input transform part empty, the image a whole number of tiles wide, so that
+# the last tile's own last columns are not zero: what a lane without a tile reads must not reach the maxima.
+# (m, r, last tile's own columns, the columns left of them): patterns for which a window whose left halo repeats the
+# tile's own last columns would exceed every real one (no such pattern of 0 and +-1 exists for two-column tiles).
+PATTERNS = [
+    (4, 3, (0, 0, 0, -1), (0,)),
+    (6, 3, (-1, -1, -1, 0, -1, 1), (-1,)),
+    (8, 3, (-1, 0, -1, -1, -1, -1, -1, -1), (1,)),
+    (4, 5, (-1, -1, 0, 0), (-1, -1)),
+    (6, 5, (-1, -1, -1, 0, 0, 1), (-1, -1)),
+]
+
+
+@pytest.mark.parametrize("m,r,own,left", PATTERNS)
+@pytest.mark.parametrize("N,tiles", [(1, 3), (1, 5), (3, 3)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_lanes_without_a_tile_leave_the_scale_alone(m, r, own, left, N, tiles, dtype):
+    t = nova.nova_make_transforms(synth.point_set("nova", m + r - 3), m, r)
+    C, K, H, W = 35, 33, tiles * m, tiles * m
+    pad = (r - 1) // 2
+    gen = torch.Generator(device=DEV).manual_seed(m + r + tiles)
+    x = torch.randn((N, C, H, W), device=DEV, generator=gen) * 0.01
+    cols = torch.tensor(left + own, dtype=torch.float32, device=DEV)
+    x[-1, 34, H - m - pad:, W - m - pad:] = cols[:, None] * cols * 4
+    B = torch.tensor(nova.nova_get_matrix_f64(t, nova.NOVA_MATRIX_BT), dtype=torch.float64)
+    repeated = torch.nn.functional.pad(x[-1, 34, H - m - pad:, W - m - pad:].cpu().double(), (0, pad, 0, pad))
+    repeated[:, :pad] = repeated[:, m:m + pad].clone()
+    beyond = (B @ repeated @ B.t()).abs().max().item()
+    w = (torch.randn((K, C, r, r), device=DEV, generator=gen) * 0.1).to(dtype)
+    for mode in MODES:
+        print(f"[case] int8 planted maximum F({m},{r}) {dtype} mode {mode} N={N} {H}x{W}", flush=True)
+        got, want, sv = both(t, x.to(dtype), w, mode)
+        assert sv.max().item() * 127 * 1.05 < beyond              # (the pattern does what it is there for)
+        assert torch.isfinite(want).all() and torch.equal(got, want)
+
+
+@pytest.mark.parametrize("m,N,C,K,H,W", [(4, 1, 64, 32, 12, 12), (4, 1, 16, 33, 20, 20), (4, 1, 64, 64, 28, 28), (2, 1, 40, 32, 10, 10),
+                                         (6, 1, 64, 32, 18, 18), (6, 3, 33, 40, 30, 24), (8, 3, 64, 32, 24, 24), (8, 1, 40, 70, 40, 40)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_ragged_groups_of_whole_tiles(m, N, C, K, H, W, dtype):
+    t = nova.nova_make_transforms(synth.point_set("standard" if m == 2 else "nova", m), m, 3)
+    for seed in range(6):
+        gen = torch.Generator(device=DEV).manual_seed(seed)
+        x = torch.randn((N, C, H, W), device=DEV, generator=gen).abs().to(dtype)
+        w = (torch.randn((K, C, 3, 3), device=DEV, generator=gen) * (2.0 / (9 * C)) ** 0.5).to(dtype)
+        for mode in MODES:
+            print(f"[case] int8 ragged groups F({m},3) {dtype} mode {mode} N={N} C={C} K={K} {H}x{W} seed {seed}", flush=True)
+            got, want, _ = both(t, x, w, mode)
+            assert torch.isfinite(want).all() and torch.equal(got, want)
