@@ -455,15 +455,17 @@ static int launch_stream(const void *U, const void *V, void *Mo, const Geometry 
 // soonest and is the fastest one on small layers: 48 -> 96 5x5 @35x35 batch 16 12.0 (128 x 64: 15.2), 512 -> 512
 // @14x14 batch 1 F(4,3) 6.6 (8.2), 128 -> 128 @112x112 batch 5 F(6,3), 15 M products, 15.6 (16.6).  Larger tiles read
 // U and V less often: 128 x 128 by 8 waves in long channel loops once it fills the chip as well (512 -> 512 @7x7
-// F(8,3) batch 256 30.7 against 36.0 and 41.8 for 128 x 64 and 64 x 64, batch 128 15.8 against 20.3 and 17.4),
-// 128 x 64 in other large layers (164 -> 33 @98x29 batch 43 F(4,3), 20 M, 38.4 against 41.4; 64 -> 64 @112x112 batch 32
-// F(4,3), 58 M, 56.0 against 59.7).  One block of output channels: 128 x 32, none of it padding.
+// F(8,3) batch 256 30.7 against 36.0 and 41.8 for 128 x 64 and 64 x 64, batch 128 15.8 against 20.3 and 17.4), but not
+// for 64 output channels or fewer, where half of them would be padding (whole calls, 128 x 128 / the tile taken instead:
+// 256 -> 64 @56x56 F(6,3) batch 16 42.7 / 41.0, 512 -> 64 @60x60 F(8,3) batch 7 44.7 / 43.3; the contraction alone there
+// 12.9 / 11.5); 128 x 64 in other large layers (164 -> 33 @98x29 batch 43 F(4,3), 20 M, 38.4 against 41.4; 64 -> 64
+// @112x112 batch 32 F(4,3), 58 M, 56.0 against 59.7).  One block of output channels: 128 x 32, none of it padding.
 template <typename MT>
 static int launch_c16_tiled(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t s)
 {
     if (g.Kp == 32) return launch_tile<128, 32, 4, 1, 3, f16, MT>(U, V, Mo, g, s);
     const double positions = (double)g.n * g.n;
-    if (g.c_blocks >= 8 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
+    if (g.c_blocks >= 8 && g.Kp > 64 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
         return launch_tile<128, 128, 2, 4, 3, f16, MT>(U, V, Mo, g, s);
     if (positions * (double)g.T * g.Kp >= 16e6) return launch_tile<128, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);
     return launch_tile<64, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);

@@ -16,6 +16,8 @@ CASES = [
     (4, 1, 512, 512, 14, 14), (6, 5, 300, 96, 30, 30),
     # 128 x 64 tiles by the number of products, 128 x 128 by the length of the channel loop
     (4, 9, 48, 96, 140, 140), (8, 15, 260, 260, 20, 20),
+    # long channel loops with 64 output channels or fewer
+    (8, 15, 260, 64, 20, 20), (8, 25, 260, 50, 40, 40), (4, 64, 257, 33, 45, 45),
     # streaming kernel at its thresholds: C = 256, 128, 64; K a multiple of 256 or of 128 only
     (8, 12, 256, 256, 49, 50), (8, 21, 256, 128, 50, 50), (8, 18, 128, 256, 57, 56), (8, 36, 128, 128, 56, 57),
     (4, 6, 64, 256, 170, 180), (4, 12, 64, 128, 170, 180),
