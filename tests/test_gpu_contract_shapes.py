@@ -71,3 +71,52 @@ def test_products_in_binary32(m, N, C, K, H, W):
     size = torch.matmul(Vl.abs(), Ul.abs().transpose(1, 2).contiguous())
     # C products, each rounded or not, and C sums in binary32; twice the standard bound as above
     assert ((M - want).abs() <= 2 * (2 * C + 2) * 2.0 ** -24 * size + 1e-37).all()
+
+
+def block(a, rows):
+    # [n2][t or k][C] -> the flat blocked layout [n2][C/32][rows][32], zero padded
+    n2, have, C = a.shape
+    out = torch.zeros((n2, rows, -(-C // 32) * 32), dtype=a.dtype, device=a.device)
+    out[:, :have, :C] = a
+    return out.view(n2, rows, -1, 32).transpose(1, 2).contiguous().view(-1)
+
+
+@pytest.mark.parametrize("dtype,scale_v,scale_u", [(torch.float32, 2.0 ** -70, 2.0 ** -68),        # the products are subnormal
+                                                   (torch.float32, 2.0 ** -130, 1.0), (torch.float32, 1.0, 2.0 ** -135),
+                                                   (torch.float16, 2.0 ** -18, 1.0), (torch.float16, 1.0, 2.0 ** -20)])
+@pytest.mark.parametrize("C,K", [(5, 20), (70, 65)])
+def test_subnormal_operands_and_products(dtype, scale_v, scale_u, C, K):
+    # operands handed to the contraction directly: nothing may be flushed to zero
+    print(f"[case] subnormal products {dtype} V {scale_v} U {scale_u} C={C} K={K}", flush=True)
+    m, N, H, W = 2, 1, 20, 23
+    t = nova.nova_make_transforms(synth.point_set("standard", 2), 2, 3)
+    n2, T = t.n * t.n, N * -(-H // m) * -(-W // m)
+    gen = torch.Generator(device=DEV).manual_seed(C)
+    V = (torch.randint(1, 64, (n2, T, C), device=DEV, generator=gen).double() * scale_v).to(dtype)
+    U = (torch.randint(-63, 64, (n2, K, C), device=DEV, generator=gen).double() * scale_u).to(dtype)
+    assert (V.double() / scale_v).abs().max() < 64 and (V.double() == (V.double() / scale_v).round() * scale_v).all()
+    M = nova.nova_contract(t, block(U, -(-K // 32) * 32), block(V, T), N, C, H, W, K)
+    M = unblock(M, n2, -(-T // 128) * 128, K)[:, :T].double()
+    # whole multiples of scale_v * scale_u below 2^24 of them: every product and partial sum is exact
+    assert torch.equal(M, torch.matmul(V.double(), U.double().transpose(1, 2).contiguous()))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("C,K,H", [(5, 20, 20), (70, 65, 20), (64, 128, 20)])
+def test_operands_that_are_not_finite(dtype, C, K, H):
+    # an infinity or NaN reaches the products of its own row and column and no others
+    print(f"[case] contraction of values that are not finite {dtype} C={C} K={K}", flush=True)
+    t = nova.nova_make_transforms(synth.point_set("standard", 2), 2, 3)
+    n2, T = t.n * t.n, (H // 2) ** 2
+    gen = torch.Generator(device=DEV).manual_seed(C)
+    V, U = (torch.randint(-9, 10, (n2, rows, C), device=DEV, generator=gen).to(dtype) for rows in (T, K))
+    V[1, 3, 2], V[1, 7, C - 1], V[2, T - 1, 0], V[3, 0, 1] = float("inf"), float("-inf"), float("nan"), float("inf")
+    U[2, K - 1, C - 1], U[3, 4, 0], U[4, 0, 3], U[3, 5, 1] = float("inf"), float("nan"), float("-inf"), float("-inf")
+    U[1, 6, 2] = 0.0                                                       # infinity times zero
+    M = nova.nova_contract(t, block(U, -(-K // 32) * 32), block(V, T), 1, C, H, H, K)
+    M = unblock(M, n2, -(-T // 128) * 128, K)[:, :T].double()
+    want = torch.zeros((n2, T, K), dtype=torch.float64, device=DEV)
+    for c in range(C):
+        want += V[:, :, c, None].double() * U[:, None, :, c].double()      # (integers: the finite sums are exact)
+    assert want.isinf().any() and want.isnan().any() and want.isfinite().any()
+    assert torch.equal(M.isnan(), want.isnan()) and torch.equal(M.nan_to_num(nan=0.0), want.nan_to_num(nan=0.0))
