@@ -458,7 +458,11 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     // Groups of TB consecutive tiles, whatever rows and images they belong to: every lane has a tile.  With the
     // streaming hint on x a group keeps to one tile row instead: what it shares with a neighbour is not
     // found in the cache again (56 x 56 x 256 channels, batch 32, F(8,3), whole call: 110 us with rows and the
-    // hint, 114 with the hint alone, 116 with neither; the transform alone 34 / 39 / 29 us).
+    // hint, 114 with the hint alone, 116 with neither; the transform alone, repeated on the same buffers, 34 / 39 / 29,
+    // with x and V from memory 34.7 with both against 36.9 with neither).  Taken where a row is one nearly full
+    // group.  Whole calls, time without / with both, layers whose x, V and M are 300 MB, n = 8 and 10, five pairs of
+    // channel counts, by tiles per row: 4 and 5 0.94-0.99, 6 0.98-1.06, 7 0.98-1.08, 8 0.98-1.11, 9 and 10 (two groups)
+    // 0.90-0.96, 12 0.93-0.99, 14 0.96-0.99, 15 and 16 0.96-1.03, 21 and 28 0.91-1.00.
     auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxNone>
                              : input_transform_kernel<N, R, T, false, kChanBlock, false, false, kMaxNone>;
     if (maxima != kMaxNone && !t->symmetric) return (int)hipErrorInvalidValue;
@@ -480,7 +484,7 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     }
     const int row_tiles = rows ? g.tiles_w : (int)g.T;
     const int groups_per_row = ceil_div(row_tiles, B::TB);
-    const int per = rows ? ceil_div(row_tiles, groups_per_row) : B::TB;
+    const int per = rows ? row_tiles : B::TB;               // (a row is one group)
     const long long t_groups = g.T / row_tiles * groups_per_row;
     const long long blocks = t_groups * g.c_blocks;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
