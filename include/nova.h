@@ -338,6 +338,8 @@ int nova_winograd_conv2d_int8(const nova_transforms *t, const void *x, const voi
  * NOVA_PATH_STAGES (input transform, contraction, output transform), NOVA_PATH_FEW_CHANNELS (at most 4
  * input channels: compact V, the products formed inside the output transform) or NOVA_PATH_FUSED_OUTPUT
  * (input transform, then the kernel above: taken wherever it is supported).  Negative: an error code.
+ * (A call with little work runs the whole layer as one kernel instead, with the same results bit for bit, and
+ * then leaves its workspace as it was.)
  * Host only.
  */
 enum { NOVA_PATH_STAGES = 0, NOVA_PATH_FEW_CHANNELS = 1, NOVA_PATH_FUSED_OUTPUT = 2 };

@@ -62,6 +62,12 @@ static size_t second_part_bytes(const Geometry &g, int dtype, int flags)
     return few_channels(g.C) ? few_channels_filter_bytes(g, dtype) : m_bytes(g, dtype, flags);
 }
 
+static bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+    return p < q + b_bytes && q < p + a_bytes;
+}
+
 // V and M of a slab together: the size of the last-level cache (256 MB), so that what one stage
 // writes is still there when the next reads it.  Measured on 224 x 224 and 112 x 112 VGG layers
 // (batch 32): 7-10 % faster than the whole batch in one pass, and faster than smaller slabs.
@@ -207,6 +213,16 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     const long long imgs = (N + slab_count - 1) / slab_count;
     size_t v_part = 0;
     (void)slab_bytes(imgs, &v_part);
+
+    // Little work: one kernel for the whole call, which leaves the workspace alone.  (It reads x and U while it writes
+    // y; the separate kernels have read both before, so a call whose y overlaps one of them stays with those.)
+    const Geometry whole = make_geometry(N, C, H, W, K, m, r);
+    const size_t x_bytes = (size_t)N * C * H * W * dtype_size(dtype);
+    const size_t y_bytes = ((flags & NOVA_FLAG_POOL2) ? (size_t)N * K * (H / 2) * (W / 2) : (size_t)N * K * H * W) * dtype_size(dtype);
+    if (!overlap(x, x_bytes, y, y_bytes) && !overlap(U, nova_filter_bytes(K, C, m, r, dtype), y, y_bytes)) {
+        const int tiles = layer_tiles(t, whole, dtype, v_bytes(whole, dtype) + (fused ? 0 : m_bytes(whole, dtype, flags)));
+        if (tiles > 0) return hip_result(launch_layer(t, x, U, y, whole, dtype, flags, tiles, stream));
+    }
 
     const size_t es = dtype_size(dtype);
     char *Vbuf = (char *)workspace;

@@ -55,9 +55,9 @@ __device__ __forceinline__ void stream_wait()
 // every lane rereads the same 16 bytes: one cached request.  Summation order per product: ascending channels in steps of 16, as in the
 // streaming kernel -- M does not depend on which kernel or tile shape formed it.
 // binary32 storage: v_mfma_f32_32x32x2_f32.  A row is 128 bytes (slots XOR-swizzled with (row / 2) % 8, a wave-wide
-// load moves 8 rows); a 128-bit read gives a lane four channels, which four instructions take in turn, so
-// the channels enter in the order 0, 4, 1, 5, 2, 6, 3, 7 of every eight; every other eight go to a second chain
-// of sums (rounding error of M against 64 bits, geometric mean over 40 drawn layers: 0.83 times that of one
+// load moves 8 rows); a 128-bit read gives a lane four channels, which four instructions take in turn, two reads
+// for every 16 channels, which enter in the order 0, 4, 8, 12, 1, 5, 9, 13 (one chain of sums) and 2, 6, 10, 14, 3, 7, 11,
+// 15 (a second one): the order in which a 16 x 16 x 4 instruction meets them in 64-byte rows (layer.hip) (rounding error of M against 64 bits, geometric mean over 40 drawn layers: 0.83 times that of one
 // multiply-add chain over the channels).  With plain multiply-add tiles (one
 // 4-byte LDS read per 2 products, one step in flight) 40 -> 70 @45x61 batch 8 F(6,3) took 23.9 us, this way 13.5.
 template <int BM, int BN, int WM, int WN, int S, typename ST, typename MT>
@@ -137,31 +137,41 @@ contract_tile_kernel(const ST *__restrict__ U, const ST *__restrict__ V, MT *__r
         __syncthreads();                                   // everyone's have; the slot before is free again
         issue_stage(slot == 0 ? S - 1 : slot - 1);
         const unsigned char *stage = ring + slot * STAGE;
+        // fragments of 16 channels: one read in binary16, two (channels 0..7 and 8..15) in binary32
+        typedef typename std::conditional<sizeof(ST) == 2, half8, float4f>::type frag_t;
+        constexpr int READS = sizeof(ST) == 2 ? 1 : 2;
 #pragma unroll
-        for (int kk = 0; kk < SLOTS / 2; ++kk) {
-            typedef typename std::conditional<sizeof(ST) == 2, half8, float4f>::type frag_t;
-            frag_t vf[MB], uf[NB];
+        for (int kk = 0; kk < SLOTS / 2; kk += READS) {
             // (binary32: channels past C are zero on both sides and need not be multiplied)
-            if (sizeof(ST) == 4 && cb * kChanBlock + kk * 8 >= C) break;
+            const int left = C - cb * kChanBlock - kk * 8;
+            if (sizeof(ST) == 4 && left <= 0) break;
+            frag_t vf[READS][MB], uf[READS][NB];
 #pragma unroll
-            for (int i = 0; i < MB; ++i) vf[i] = *reinterpret_cast<const frag_t *>(stage + (wm * MB + i) * 32 * ROW + frag_off[kk]);
+            for (int q = 0; q < READS; ++q) {
 #pragma unroll
-            for (int j = 0; j < NB; ++j) uf[j] = *reinterpret_cast<const frag_t *>(stage + BM * ROW + (wn * NB + j) * 32 * ROW + frag_off[kk]);
+                for (int i = 0; i < MB; ++i) vf[q][i] = *reinterpret_cast<const frag_t *>(stage + (wm * MB + i) * 32 * ROW + frag_off[kk + q]);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) uf[q][j] = *reinterpret_cast<const frag_t *>(stage + BM * ROW + (wn * NB + j) * 32 * ROW + frag_off[kk + q]);
+            }
             if constexpr (sizeof(ST) == 2) {
 #pragma unroll
                 for (int j = 0; j < NB; ++j)
 #pragma unroll
-                    for (int i = 0; i < MB; ++i) acc[0][j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[i], uf[j], acc[0][j][i], 0, 0, 0);
+                    for (int i = 0; i < MB; ++i) acc[0][j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[0][i], uf[0][j], acc[0][j][i], 0, 0, 0);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int j = 0; j < NB; ++j)
+                    for (int q = 0; q < READS; ++q) {
+                        if (q == 1 && left <= 8) continue;
 #pragma unroll
-                        for (int i = 0; i < MB; ++i) {
-                            float16v &sum = acc[kk % CHAINS][j][i];
-                            sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[i][e], uf[j][e], sum, 0, 0, 0);
-                        }
+                        for (int j = 0; j < NB; ++j)
+#pragma unroll
+                            for (int i = 0; i < MB; ++i) {
+                                float16v &sum = acc[e / 2 % CHAINS][j][i];
+                                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[q][i][e], uf[q][j][e], sum, 0, 0, 0);
+                            }
+                    }
             }
         }
         slot = slot == S - 1 ? 0 : slot + 1;

@@ -37,6 +37,29 @@ __device__ __forceinline__ float output_transform_1d_out(int i, float v_zero, fl
     return acc;
 }
 
+// Outputs i and i + 1 as two binary16 values in a word, each rounded together with its last multiply-add: what the
+// compiler makes of `(f16)output_transform_1d_out(...)` where nothing stands between the two (v_fma_mixlo_f16), spelled
+// out where results have to be the same bits from several kernels.
+template <int N, int R>
+__device__ __forceinline__ unsigned output_transform_1d_f16_pair(int i, float v_zero, float v_inf,
+                                                                 const float (&s)[(N - 2) / 2 > 0 ? (N - 2) / 2 : 1],
+                                                                 const float (&d)[(N - 2) / 2 > 0 ? (N - 2) / 2 : 1], const OutCoef<N, R> &k)
+{
+    constexpr int M = N - R + 1, H = (N - 2) / 2;
+    static_assert(M % 2 == 0 && H >= 1, "pairs of outputs");
+    float acc[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        acc[e] = i + e == 0 ? k.zero * v_zero : (i + e == M - 1) ? k.inf * v_inf : 0.0f;
+#pragma unroll
+        for (int j = 0; j < H - 1; ++j) acc[e] = fma32(k.pw[j * M + i + e], e ? d[j] : s[j], acc[e]);      // (i is even)
+    }
+    unsigned word;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]" : "=v"(word) : "s"(k.pw[(H - 1) * M + i]), "v"(s[H - 1]), "v"(acc[0]));
+    asm("v_fma_mixhi_f16 %0, %1, %2, %3 op_sel_hi:[0,0,0]" : "+v"(word) : "s"(k.pw[(H - 1) * M + i + 1]), "v"(d[H - 1]), "v"(acc[1]));
+    return word;
+}
+
 template <int N, int R, bool SYM>
 __device__ __forceinline__ void output_transform_1d(const float (&v)[N], float (&out)[N - R + 1], const OutCoef<N, R> &k)
 {
