@@ -195,24 +195,31 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
 
     // (64 input channels: contraction and output transform run as one kernel and keep no M, where that is faster)
     const bool fused = fused_contract_output_preferred(t, make_geometry(1, C, H, W, K, m, r), dtype, flags);
-    // largest slab (whole images) whose V and M fit the workspace; slab_bytes grows with the count
-    auto slab_bytes = [&](long long count, size_t *v_part) {
-        const Geometry sg = make_geometry((int)count, C, H, W, K, m, r);
-        const size_t vb = align256(first_part_bytes(sg, dtype));
-        if (v_part) *v_part = vb;
-        return vb + (fused ? 0 : align256(second_part_bytes(sg, dtype, flags)));
+    // What follows V: M; nothing on the fused path; with `columns` what contract_columns.hip leaves, m planes of n
+    auto second_part = [&](const Geometry &sg, bool columns) {
+        const size_t planes = fused ? 0 : second_part_bytes(sg, dtype, flags);
+        return columns ? planes / sg.n * sg.m : planes;
     };
-    if (slab_bytes(1, nullptr) > workspace_bytes) return NOVA_ENOSPC;
-    long long lo = 1, hi = N;                    // invariant: lo fits
-    while (lo < hi) {
-        const long long mid = (lo + hi + 1) / 2;
-        if (slab_bytes(mid, nullptr) <= workspace_bytes) lo = mid; else hi = mid - 1;
-    }
-    // (as many slabs as that size needs, but of equal size: 20 + 12 images run slower than 16 + 16)
-    const long long slab_count = (N + lo - 1) / lo;
-    const long long imgs = (N + slab_count - 1) / slab_count;
-    size_t v_part = 0;
-    (void)slab_bytes(imgs, &v_part);
+    auto slab_bytes = [&](long long count, bool columns) {
+        const Geometry sg = make_geometry((int)count, C, H, W, K, m, r);
+        return align256(first_part_bytes(sg, dtype)) + align256(second_part(sg, columns));
+    };
+    // largest slab (whole images) whose parts fit the workspace; slab_bytes grows with the count
+    auto images_per_slab = [&](bool columns) {
+        long long lo = 1, hi = N;                    // invariant: lo fits
+        while (lo < hi) {
+            const long long mid = (lo + hi + 1) / 2;
+            if (slab_bytes(mid, columns) <= workspace_bytes) lo = mid; else hi = mid - 1;
+        }
+        // (as many slabs as that size needs, but of equal size: 20 + 12 images run slower than 16 + 16)
+        const long long slab_count = (N + lo - 1) / lo;
+        return (int)((N + slab_count - 1) / slab_count);
+    };
+    if (slab_bytes(1, false) > workspace_bytes) return NOVA_ENOSPC;
+    int imgs = images_per_slab(true);
+    const bool columns = !fused && contract_columns_preferred(t, make_geometry(imgs, C, H, W, K, m, r), dtype, flags);
+    if (!columns) imgs = images_per_slab(false);
+    const size_t v_part = align256(first_part_bytes(make_geometry(imgs, C, H, W, K, m, r), dtype));
 
     // Little work: one kernel for the whole call, which leaves the workspace alone.  (It reads x and U while it writes
     // y; the separate kernels have read both before, so a call whose y overlaps one of them stays with those.)
@@ -228,8 +235,8 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     char *Vbuf = (char *)workspace;
     char *Mbuf = Vbuf + v_part;
     const bool few = few_channels(C);
-    for (int n0 = 0; n0 < N; n0 += (int)imgs) {
-        const int nb = (N - n0 < imgs) ? N - n0 : (int)imgs;
+    for (int n0 = 0; n0 < N; n0 += imgs) {
+        const int nb = N - n0 < imgs ? N - n0 : imgs;
         const Geometry g = make_geometry(nb, C, H, W, K, m, r);
         const char *xs = (const char *)x + (size_t)n0 * C * H * W * es;
         const size_t y_image = (flags & NOVA_FLAG_POOL2) ? (size_t)K * (H / 2) * (W / 2) : (size_t)K * H * W;
@@ -240,10 +247,15 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
             continue;
         }
         // (kDefaultSlabBytes: the size of the last-level cache)
-        const bool stream_x = !fused && (size_t)nb * C * H * W * es + v_bytes(g, dtype) + m_bytes(g, dtype, flags) > kDefaultSlabBytes;
+        const bool stream_x = !fused && (size_t)nb * C * H * W * es + v_bytes(g, dtype) + second_part(g, columns) > kDefaultSlabBytes;
         if (int err = launch_input_transform(t, xs, Vbuf, g, dtype, stream, stream_x)) return hip_result(err);
         if (fused) {
             if (int err = launch_fused_contract_output(t, U, Vbuf, ys, g, dtype, flags, stream)) return hip_result(err);
+            continue;
+        }
+        if (columns) {
+            if (int err = launch_contract_columns(t, U, Vbuf, Mbuf, g, stream)) return hip_result(err);
+            if (int err = launch_output_rows(t, Mbuf, ys, g, flags, stream)) return hip_result(err);
             continue;
         }
         if (int err = launch_contract(t, U, Vbuf, Mbuf, g, dtype, flags, stream)) return hip_result(err);

@@ -114,6 +114,11 @@ int launch_contract(const nova_transforms *t, const void *U, const void *V, void
                     const Geometry &g, int dtype, int flags, void *stream);
 int launch_output_transform(const nova_transforms *t, const void *M, void *y, const Geometry &g,
                             int dtype, int flags, void *stream);
+// Contraction and the column half of the output transform in one kernel, Z [n][m][K/32][Tp][32] in place of M, then the row
+// half; nova_winograd_conv2d takes them for the slabs contract_columns_preferred names.  Results as by the separate kernels.
+bool contract_columns_preferred(const nova_transforms *t, const Geometry &g, int dtype, int flags);
+int launch_contract_columns(const nova_transforms *t, const void *U, const void *V, void *Z, const Geometry &g, void *stream);
+int launch_output_rows(const nova_transforms *t, const void *Z, void *y, const Geometry &g, int flags, void *stream);
 // Contraction and output transform in one kernel (no M), for the shapes fused_contract_output_applies names;
 // nova_winograd_conv2d takes it for those fused_contract_output_preferred names
 bool fused_contract_output_applies(const nova_transforms *t, const Geometry &g, int dtype, int flags);

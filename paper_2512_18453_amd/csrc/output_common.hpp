@@ -114,6 +114,21 @@ __device__ __forceinline__ void store_block_row(float *dst, const float (&o)[M])
     }
 }
 
+// The same for values already rounded, two to a word
+template <int M>
+__device__ __forceinline__ void store_block_words(f16 *dst, const unsigned (&w)[M / 2])
+{
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    unsigned *at = reinterpret_cast<unsigned *>(__builtin_assume_aligned(dst, 4));
+    if constexpr (M % 4 == 0) {
+#pragma unroll
+        for (int q = 0; q < M / 2; q += 2) *reinterpret_cast<u32x2 *>(__builtin_assume_aligned(at + q, 8)) = u32x2{w[q], w[q + 1]};
+    } else {
+#pragma unroll
+        for (int q = 0; q < M / 2; ++q) at[q] = w[q];
+    }
+}
+
 struct OutShape {
     int twb;          // tiles per group (all tile rows of the group together)
     int twc;          // tile columns per group

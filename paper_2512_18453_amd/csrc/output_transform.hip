@@ -28,7 +28,9 @@ constexpr int kFewChannels = 4;
 // CF = 0: products read from Mp (MT: their type).  CF = kFewChannels: products formed from Vp
 // [n*n][Ttot][CF] and Uc [n*n][k_blocks*32][CF]; MT = f16 rounds each product to binary16 first,
 // as storing M in binary16 would.
-template <int N, int R, typename T, typename MT, bool SYM, int STG, bool RELU, int CF>
+// COLUMNS_DONE: Mp holds what contract_columns.hip leaves, Z[j][p] = column j transformed to its outputs p, N x M planes
+// instead of N x N; what is left is a transform per row, whose N values are all that a thread has to hold.
+template <int N, int R, typename T, typename MT, bool SYM, int STG, bool RELU, int CF, bool COLUMNS_DONE>
 __global__ void __launch_bounds__(512)
 output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, const T *__restrict__ Uc,
                         T *__restrict__ y, int K, int H, int W,
@@ -90,9 +92,9 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
         const size_t xi_stride = (size_t)k_blocks * Ttot * kChanBlock;
         const unsigned in_plane = (unsigned)((((size_t)kb * Ttot + t) * kChanBlock + k_in) * sizeof(MT));   // bytes
 
-        float z[M][N];                    // A^T M, column by column
+        float z[COLUMNS_DONE ? 1 : M][N];                    // A^T M, column by column
 #pragma unroll
-        for (int b = 0; b < N; ++b) {
+        for (int b = 0; b < (COLUMNS_DONE ? 0 : N); ++b) {
             float v[N], o[M];
             if constexpr (CF > 0) {
                 typedef T few_t __attribute__((ext_vector_type(CF > 0 ? CF : 1)));
@@ -130,7 +132,22 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
 #pragma unroll
         for (int p = 0; p < M; ++p) {
             float o[M];
-            output_transform_1d<N, R, SYM>(z[p], o, coef);
+            if constexpr (COLUMNS_DONE) {
+#pragma unroll
+                for (int b = 0; b < N; ++b)
+                    z[0][b] = (float)__builtin_nontemporal_load(plane_element(Mp + (size_t)(b * M + p) * xi_stride, in_plane));
+                if constexpr (sizeof(T) == 2 && !RELU) {
+                    constexpr int H = (N - 2) / 2;
+                    float s[H], d[H];
+                    unsigned words[M / 2];
+                    output_transform_1d_pairs<N, R>(z[0], s, d);
+#pragma unroll
+                    for (int q = 0; q < M; q += 2) words[q / 2] = output_transform_1d_f16_pair<N, R>(q, z[0][0], z[0][N - 1], s, d, coef);
+                    store_block_words<M>(dst + p * sh.cols_pitch, words);
+                    continue;
+                }
+            }
+            output_transform_1d<N, R, SYM>(z[COLUMNS_DONE ? 0 : p], o, coef);
             if constexpr (RELU) {
 #pragma unroll
                 for (int q = 0; q < M; ++q) o[q] = o[q] < 0.0f ? 0.0f : o[q];      // NaN stays NaN
@@ -179,7 +196,7 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
 }
 
 // CF = 0: Mp holds the products.  CF = kFewChannels: Mp is V, and `few_u` the packed filters.
-template <int N, int R, typename T, typename MT, int CF>
+template <int N, int R, typename T, typename MT, int CF, bool COLUMNS_DONE = false>
 static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u, void *y, const Geometry &g, int flags,
                      hipStream_t stream)
 {
@@ -257,12 +274,13 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     auto pick = [&](auto sym) {
         constexpr bool S = decltype(sym)::value;
         switch (stg) {
-        case kStoreVec:  return relu ? output_transform_kernel<N, R, T, MT, S, kStoreVec, true, CF> : output_transform_kernel<N, R, T, MT, S, kStoreVec, false, CF>;
-        case kStoreFlat: return relu ? output_transform_kernel<N, R, T, MT, S, kStoreFlat, true, CF> : output_transform_kernel<N, R, T, MT, S, kStoreFlat, false, CF>;
-        default:         return relu ? output_transform_kernel<N, R, T, MT, S, kStoreScalar, true, CF> : output_transform_kernel<N, R, T, MT, S, kStoreScalar, false, CF>;
+        case kStoreVec:  return relu ? output_transform_kernel<N, R, T, MT, S, kStoreVec, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreVec, false, CF, COLUMNS_DONE>;
+        case kStoreFlat: return relu ? output_transform_kernel<N, R, T, MT, S, kStoreFlat, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreFlat, false, CF, COLUMNS_DONE>;
+        default:         return relu ? output_transform_kernel<N, R, T, MT, S, kStoreScalar, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreScalar, false, CF, COLUMNS_DONE>;
         }
     };
-    kern = t->symmetric ? pick(std::true_type{}) : pick(std::false_type{});
+    if constexpr (COLUMNS_DONE) kern = pick(std::true_type{});
+    else kern = t->symmetric ? pick(std::true_type{}) : pick(std::false_type{});
     if constexpr (CF > 0)
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes, stream,
                            (const MT *)nullptr, (const T *)Mp, (const T *)few_u, (T *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w,
@@ -308,6 +326,29 @@ int launch_output_transform(const nova_transforms *t, const void *Mp, void *y, c
                             int dtype, int flags, void *stream)
 {
     return launch_ot_any<0>(t, Mp, nullptr, y, g, dtype, flags, (hipStream_t)stream);
+}
+
+int launch_output_rows(const nova_transforms *t, const void *Z, void *y, const Geometry &g, int flags, void *stream)
+{
+    if (!t->symmetric) return (int)hipErrorInvalidValue;
+    hipStream_t s = (hipStream_t)stream;
+#define NOVA_ROWS(N, R) launch_ot<N, R, f16, float, 0, true>(t, Z, nullptr, y, g, flags, s)
+    if (t->r == 3) {
+        switch (t->n) {
+        case 4: return NOVA_ROWS(4, 3);
+        case 6: return NOVA_ROWS(6, 3);
+        case 8: return NOVA_ROWS(8, 3);
+        case 10: return NOVA_ROWS(10, 3);
+        }
+    } else if (t->r == 5) {
+        switch (t->n) {
+        case 6: return NOVA_ROWS(6, 5);
+        case 8: return NOVA_ROWS(8, 5);
+        case 10: return NOVA_ROWS(10, 5);
+        }
+    }
+#undef NOVA_ROWS
+    return (int)hipErrorInvalidValue;
 }
 
 int few_channels_limit() { return kFewChannels; }

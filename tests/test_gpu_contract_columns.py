@@ -1,0 +1,56 @@
+"""Calls whose products leave the contraction with their columns transformed (m planes of n instead of M) against the
+separate stage calls: the same operations in the same order, so the results are equal bit for bit.  The sizes sit at the
+edges of its 64 x 64 (one block of output channels: 128 x 32) tiles and of its channel loop."""
+import pytest
+import torch
+
+from paper_2512_18453_amd import nova, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+CASES = [
+    # m, r, N, C, K, H, W
+    (2, 3, 5, 33, 70, 60, 100), (2, 3, 9, 5, 32, 90, 90),
+    (4, 3, 9, 40, 100, 61, 62), (4, 3, 2, 256, 64, 121, 124), (4, 3, 30, 8, 20, 75, 66),
+    (6, 3, 17, 96, 130, 45, 47), (6, 3, 32, 70, 64, 44, 48), (6, 3, 6, 200, 256, 60, 65),
+    (8, 3, 34, 65, 96, 50, 52), (8, 3, 120, 128, 64, 32, 40),
+    (2, 5, 10, 100, 64, 33, 50), (4, 5, 20, 48, 96, 35, 35), (6, 5, 70, 20, 64, 30, 40),
+]
+
+
+@pytest.mark.parametrize("m,r,N,C,K,H,W", CASES)
+def test_equals_the_stages(m, r, N, C, K, H, W):
+    size = m + r - 3
+    t = nova.nova_make_transforms(synth.point_set("standard" if size == 2 else "nova", size), m, r)
+    gen = torch.Generator(device=DEV).manual_seed(m * 1000 + C)
+    x = torch.randn((N, C, H, W), device=DEV, generator=gen).half()
+    U = nova.nova_filter_transform(t, (torch.randn((K, C, r, r), device=DEV, generator=gen) * (2.0 / (r * r * C)) ** 0.5).half())
+    V = nova.nova_input_transform(t, x)
+    M = nova.nova_contract(t, U, V, N, C, H, W, K)
+    planes = nova.nova_product_bytes(N, K, H, W, m, nova.NOVA_F16, 0, r)
+    for flags in (0, nova.NOVA_FLAG_RELU, nova.NOVA_FLAG_RELU | nova.NOVA_FLAG_POOL2):
+        if flags & nova.NOVA_FLAG_POOL2 and (H % 2 or W % 2):
+            continue
+        want = nova.nova_output_transform(t, M, N, K, H, W, torch.float16, flags)
+        nbytes = nova.nova_conv2d_workspace_bytes(N, C, H, W, K, m, nova.NOVA_F16, flags, N, r)
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)                # NaN, if anything reads it
+        got = nova.nova_winograd_conv2d(t, x, U, K, flags=flags, workspace=ws)
+        some = nova.nova_winograd_conv2d(t, x, U, K, flags=flags, images_per_slab=2)
+        torch.cuda.synchronize()
+        assert torch.isfinite(want).all() and torch.equal(got, want) and torch.equal(some, want), flags
+        tail = planes // t.n * (t.n - m)                                               # the planes that are not written
+        assert bool((ws[nbytes - tail:] == 0xFF).all()), "not this path"
+
+
+def test_values_that_are_not_finite():
+    t = nova.nova_make_transforms(synth.point_set("nova", 4), 4, 3)
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    x = torch.randn((9, 40, 61, 62), device=DEV, generator=gen).half()
+    x[1, 3, 7, 9], x[5, 30, 20, 11] = float("inf"), float("nan")
+    U = nova.nova_filter_transform(t, (torch.randn((100, 40, 3, 3), device=DEV, generator=gen) * 0.1).half())
+    V = nova.nova_input_transform(t, x)
+    M = nova.nova_contract(t, U, V, 9, 40, 61, 62, 100)
+    want, got = nova.nova_output_transform(t, M, 9, 100, 61, 62, torch.float16), nova.nova_winograd_conv2d(t, x, U, 100)
+    torch.cuda.synchronize()
+    assert torch.equal(got.nan_to_num(nan=7.0), want.nan_to_num(nan=7.0)) and not torch.isfinite(got).all()
