@@ -302,10 +302,17 @@ static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, cons
     const int by_element = x_elems < N - R + 1 || (long long)kFewIn * g.H * g.W >= (1LL << 30) ? 1 : 0;
     auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, false, kMaxNone>
                              : input_transform_kernel<N, R, T, false, kFewIn, false, false, kMaxNone>;
+    int threads = B::THREADS;
+    // (as in launch_it; us for the whole call without / with: 3 -> 64 @48x18 batch 12 F(8,3) 21.0 / 18.4, 4 -> 41 @44x14 batch 32
+    // F(6,3) 13.8 / 12.3, but 3 -> 10 @24x57 batch 12 F(2,3) 8.5 / 9.0)
+    if (N > 4 && t->symmetric && blocks <= device_cu_count()) {
+        kern = input_transform_kernel<N, R, T, true, kFewIn, true, false, kMaxNone>;
+        threads = TileBlock<N, T, kFewIn, true>::THREADS;
+    }
     const PackFilters<T> pack = {(const T *)U, (T *)Uc, U ? (long long)g.n * g.n * g.Kp : 0};
-    const long long pack_blocks = (pack.rows + B::THREADS - 1) / B::THREADS;
+    const long long pack_blocks = (pack.rows + threads - 1) / threads;
     if (blocks + pack_blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks + pack_blocks)), dim3(B::THREADS), B::LDS_BYTES, stream, (const T *)x, (T *)Vc, g.C, g.H, g.W,
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks + pack_blocks)), dim3(threads), B::LDS_BYTES, stream, (const T *)x, (T *)Vc, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, 1, (unsigned)blocks, (int)g.T, (int)blocks, B::TB, (int)g.T, x_elems, by_element,
                        (float *)nullptr, 0, pack, coef);
     return (int)hipGetLastError();

@@ -142,6 +142,8 @@ int launch_input_transform_few(const nova_transforms *t, const void *x, void *Vc
                                const void *U, void *Uc, int dtype, void *stream);
 int launch_output_transform_few(const nova_transforms *t, const void *V, const void *Uc, void *y,
                                 const Geometry &g, int dtype, int flags, void *stream);
+// ... in binary16 with points in the paired order
+int launch_few_channels_f16(const nova_transforms *t, const void *Vc, const void *Uc, void *y, const Geometry &g, int flags, void *stream);
 // INT8 operands in the Winograd domain: symmetric quantisation of a blocked tensor [positions][channel
 // blocks][rows][32] with one scale (kind 0), one per row index (1) or one per position (2); integer
 // contraction, raw (int32) or de-quantised (binary32) with the scales of the same kind

@@ -134,76 +134,6 @@ __device__ __forceinline__ void outputs_rows_first(F &&m_at, T (&out)[N - R + 1]
         for (int q = 0; q < M; ++q) out[p][q] = round_twice(RELU && Y[p][q] < 0.0f ? 0.0f : Y[p][q], (T *)nullptr);
 }
 
-// COUNT elements to an element-aligned address
-template <typename T, int COUNT>
-__device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
-{
-    constexpr int WORDS = COUNT * (int)sizeof(T) / 4;
-    typedef unsigned int piece4 __attribute__((ext_vector_type(4), aligned(2)));
-    typedef unsigned int piece2 __attribute__((ext_vector_type(2), aligned(2)));
-    typedef unsigned int piece1 __attribute__((aligned(2)));
-    if constexpr (COUNT * (int)sizeof(T) % 4 != 0) {
-#pragma unroll
-        for (int e = 0; e < COUNT; ++e) dst[e] = v[e];
-    } else {
-        unsigned w[WORDS];
-        __builtin_memcpy(w, v, WORDS * 4);
-        unsigned char *at = reinterpret_cast<unsigned char *>(dst);
-        constexpr int FOURS = WORDS / 4 * 4;
-#pragma unroll
-        for (int e = 0; e < FOURS; e += 4) *reinterpret_cast<piece4 *>(at + 4 * e) = piece4{w[e], w[e + 1], w[e + 2], w[e + 3]};
-        if constexpr (WORDS - FOURS >= 2) *reinterpret_cast<piece2 *>(at + 4 * FOURS) = piece2{w[FOURS], w[FOURS + 1]};
-        if constexpr ((WORDS - FOURS) % 2 == 1) *reinterpret_cast<piece1 *>(at + 4 * (WORDS - 1)) = w[WORDS - 1];
-    }
-}
-
-// Rows [P0, P0 + ROWS) of a tile's outputs, rounded, to the image plane at `plane` (or 2 x 2 max-pooled: H, W, m even,
-// so no window straddles two tiles).
-template <typename T, int M, int P0, int ROWS>
-__device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W, bool pool)
-{
-    if (pool) {
-        const int Hp = H / 2, Wp = W / 2, h0 = (tr * M + P0) / 2, w0 = tc * (M / 2);
-        T *at = plane + (long long)h0 * Wp + w0;
-#pragma unroll
-        for (int p = 0; p < ROWS / 2; ++p) {
-            if (h0 + p >= Hp) continue;
-            T best[M / 2];
-#pragma unroll
-            for (int s = 0; s < M / 2; ++s) {
-                const float v0 = (float)out[2 * p][2 * s], v1 = (float)out[2 * p][2 * s + 1];
-                const float v2 = (float)out[2 * p + 1][2 * s], v3 = (float)out[2 * p + 1][2 * s + 1];
-                float top = v0;                                   // a NaN in the window wins
-                top = (v1 > top || v1 != v1) ? v1 : top;
-                top = (v2 > top || v2 != v2) ? v2 : top;
-                top = (v3 > top || v3 != v3) ? v3 : top;
-                best[s] = (T)top;                                 // one of the four values: exact
-            }
-            if (w0 + M / 2 <= Wp) {
-                store_row<T, M / 2>(at + (long long)p * Wp, best);
-            } else {
-#pragma unroll
-                for (int s = 0; s < M / 2; ++s)
-                    if (w0 + s < Wp) at[(long long)p * Wp + s] = best[s];
-            }
-        }
-    } else {
-        const int h0 = tr * M + P0, w0 = tc * M;
-        T *at = plane + (long long)h0 * W + w0;
-#pragma unroll
-        for (int p = 0; p < ROWS; ++p) {
-            if (h0 + p >= H) continue;
-            if (w0 + M <= W) {
-                store_row<T, M>(at + (long long)p * W, out[p]);
-            } else {
-#pragma unroll
-                for (int s = 0; s < M; ++s)
-                    if (w0 + s < W) at[(long long)p * W + s] = out[p][s];
-            }
-        }
-    }
-}
-
 // The outputs of part `part` (wave-uniform) of the SPLIT that share a pair: whole pairs of rows, so that pooling
 // stays within a part.
 template <int N, int R, typename T, int SPLIT, bool RELU, bool ROWS_FIRST, int I, typename F>

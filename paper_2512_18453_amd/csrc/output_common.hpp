@@ -297,6 +297,82 @@ __device__ __forceinline__ void store_output_block(const T *lds, T *__restrict__
     }
 }
 
+// COUNT elements to an element-aligned address; NT: with the streaming cache hint
+#define NOVA_STORE(type, at, value)                                                              \
+    do {                                                                                         \
+        type *nova_at_ = reinterpret_cast<type *>(at);                                           \
+        if constexpr (NT) __builtin_nontemporal_store(value, nova_at_); else *nova_at_ = value;  \
+    } while (0)
+template <typename T, int COUNT, bool NT = false>
+__device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
+{
+    constexpr int WORDS = COUNT * (int)sizeof(T) / 4;
+    typedef unsigned int piece4 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef unsigned int piece2 __attribute__((ext_vector_type(2), aligned(2)));
+    typedef unsigned int piece1 __attribute__((aligned(2)));
+    if constexpr (COUNT * (int)sizeof(T) % 4 != 0) {
+#pragma unroll
+        for (int e = 0; e < COUNT; ++e) dst[e] = v[e];
+    } else {
+        unsigned w[WORDS];
+        __builtin_memcpy(w, v, WORDS * 4);
+        unsigned char *at = reinterpret_cast<unsigned char *>(dst);
+        constexpr int FOURS = WORDS / 4 * 4;
+#pragma unroll
+        for (int e = 0; e < FOURS; e += 4) NOVA_STORE(piece4, at + 4 * e, (piece4{w[e], w[e + 1], w[e + 2], w[e + 3]}));
+        if constexpr (WORDS - FOURS >= 2) NOVA_STORE(piece2, at + 4 * FOURS, (piece2{w[FOURS], w[FOURS + 1]}));
+        if constexpr ((WORDS - FOURS) % 2 == 1) NOVA_STORE(piece1, at + 4 * (WORDS - 1), w[WORDS - 1]);
+    }
+}
+#undef NOVA_STORE
+
+// Rows [P0, P0 + ROWS) of a tile's outputs, rounded, to the image plane at `plane` (or 2 x 2 max-pooled: H, W, m even,
+// so no window straddles two tiles).
+template <typename T, int M, int P0, int ROWS>
+__device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W, bool pool)
+{
+    if (pool) {
+        const int Hp = H / 2, Wp = W / 2, h0 = (tr * M + P0) / 2, w0 = tc * (M / 2);
+        T *at = plane + (long long)h0 * Wp + w0;
+#pragma unroll
+        for (int p = 0; p < ROWS / 2; ++p) {
+            if (h0 + p >= Hp) continue;
+            T best[M / 2];
+#pragma unroll
+            for (int s = 0; s < M / 2; ++s) {
+                const float v0 = (float)out[2 * p][2 * s], v1 = (float)out[2 * p][2 * s + 1];
+                const float v2 = (float)out[2 * p + 1][2 * s], v3 = (float)out[2 * p + 1][2 * s + 1];
+                float top = v0;                                   // a NaN in the window wins
+                top = (v1 > top || v1 != v1) ? v1 : top;
+                top = (v2 > top || v2 != v2) ? v2 : top;
+                top = (v3 > top || v3 != v3) ? v3 : top;
+                best[s] = (T)top;                                 // one of the four values: exact
+            }
+            if (w0 + M / 2 <= Wp) {
+                store_row<T, M / 2>(at + (long long)p * Wp, best);
+            } else {
+#pragma unroll
+                for (int s = 0; s < M / 2; ++s)
+                    if (w0 + s < Wp) at[(long long)p * Wp + s] = best[s];
+            }
+        }
+    } else {
+        const int h0 = tr * M + P0, w0 = tc * M;
+        T *at = plane + (long long)h0 * W + w0;
+#pragma unroll
+        for (int p = 0; p < ROWS; ++p) {
+            if (h0 + p >= H) continue;
+            if (w0 + M <= W) {
+                store_row<T, M>(at + (long long)p * W, out[p]);
+            } else {
+#pragma unroll
+                for (int s = 0; s < M; ++s)
+                    if (w0 + s < W) at[(long long)p * W + s] = out[p][s];
+            }
+        }
+    }
+}
+
 template <int N, int R>
 static void fill_out_coef(const nova_transforms *t, OutCoef<N, R> &k)
 {

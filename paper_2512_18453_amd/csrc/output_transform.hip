@@ -280,6 +280,7 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
         }
     };
     if constexpr (COLUMNS_DONE) kern = pick(std::true_type{});
+    else if constexpr (CF > 0 && sizeof(T) == 2) kern = pick(std::false_type{});       // (paired points: few_channels.hip)
     else kern = t->symmetric ? pick(std::true_type{}) : pick(std::false_type{});
     if constexpr (CF > 0)
         hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes, stream,
@@ -361,6 +362,7 @@ size_t few_channels_filter_bytes(const Geometry &g, int dtype)
 int launch_output_transform_few(const nova_transforms *t, const void *V, const void *Uc, void *y,
                                 const Geometry &g, int dtype, int flags, void *stream)
 {
+    if (dtype == NOVA_F16 && t->symmetric) return launch_few_channels_f16(t, V, Uc, y, g, flags, stream);
     return launch_ot_any<kFewChannels>(t, V, Uc, y, g, dtype, flags, (hipStream_t)stream);
 }
 
