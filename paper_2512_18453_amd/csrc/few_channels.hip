@@ -179,7 +179,7 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
         }
     } else {
         // 2 x 2 max-pool (H, W, m even): the wave with the odd rows hands their pairwise maxima over
-        auto larger = [](f16 a, f16 b) __attribute__((always_inline)) { return (float)b > (float)a || b != b ? b : a; };      // a NaN wins
+        auto larger = [](f16 a, f16 b) __attribute__((always_inline)) { return __builtin_elementwise_maximum(a, b); };      // a NaN wins
         f16 row_max[4][MH][MH];
 #pragma unroll
         for (int e = 0; e < 4; ++e)

@@ -4,11 +4,10 @@
 // M never exists in memory: Y = A^T [ sum_c U * V ] A is formed per (tile, channel) pair from
 // matrix-unit results that stay in registers (Sec. 2.1 steps 3 and 4).
 //
-// A workgroup of 4 waves takes a block of up to 16 tiles (trb tile rows x twc tile columns, the shape
-// that wastes the fewest of the 16 slots over the image) and 32 output channels; a wave takes 8 of those
-// channels.  Two workgroups share a compute unit (80 KB of LDS and at most 256 registers each), so that the
-// head and the tail of one -- waiting for the first operands, converting, staging and storing the results,
-// 40 % of its life -- overlap the other's main loop (8 waves as one workgroup per unit: 3-19 % slower).
+// A workgroup of 4 waves takes 16 consecutive tiles of the batch (whatever tile rows and images they belong to) and 32
+// output channels; a wave takes 8 of those channels.  Two workgroups share a compute unit (80 KB of LDS and at most 256
+// registers each), so that the head and the tail of one -- waiting for the first operands, converting and storing
+// the results -- overlap the other's main loop (8 waves as one workgroup per unit: 3-19 % slower).
 // Per Winograd-domain position xi a wave forms a 16 x 16 block (v_mfma_f32_16x16x32_f16, binary32
 // accumulation over the input channels) of which only 8 rows are used: the matrix unit leaves each lane 4 results (rows
 // 4 * (lane / 16) + 0..3 of column lane % 16), and the transform state of a (tile, channel) pair is
@@ -38,13 +37,17 @@
 // pattern that a 128-bit fragment read of rows lane % 16 takes fastest (timed: 2.9 clocks per wave-wide
 // read against 4.5 without it or with (row / 4) % 4, which is the right one for rows lane % 32); the
 // loads fix each lane's place in LDS, so a lane fetches the piece that belongs there.
-// At the end the m x m results of all pairs go through LDS as a [32 channels][rows][columns] block and
-// leave as in the separate output transform, with its ReLU / max-pool options.
+// At the end a lane holds whole m x m blocks and stores their rows itself, neighbouring tiles in neighbouring lanes, with the ReLU /
+// max-pool options of the separate output transform.  (As a [32 channels][rows][columns] block through LDS, with the 16 tile
+// slots as trb x twc tiles of one image -- 14 of 16 used at 224, 112 and 56 pixels -- 64 -> 64 @224x224, 16 images, pooled,
+// F(8,3) took 80 us, this way 69.)  What bounds it: LDS, 1700 of a row's 5500 clocks per workgroup and two workgroups to a
+// unit (every wave reads 4 KB of operands per position for 128 pairs), and 2000 vector instructions per wave.
 #include "output_common.hpp"
 
 namespace nova {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 constexpr int kFusedTiles = 16;        // tiles per workgroup: the columns of the matrix instruction
@@ -74,11 +77,11 @@ struct FoldCoef {
     float c[(N / 2) * (N - R + 1)];
 };
 
-template <int N, int R, int STG>
+template <int N, int R>
 __global__ void __launch_bounds__(64 * kFusedWaves, 2)
 fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16 *__restrict__ y,
-                             int K, int H, int W, int tiles_h, int tiles_w, int Kp, long long Ttot, int k_groups,
-                             int relu, int one_pass, OutShape sh, OutCoef<N, R> coef, FoldCoef<N, R> fold)
+                             int K, int H, int W, int tiles_h, int tiles_w, int Kp, int Ttot, int k_groups,
+                             int flags, OutCoef<N, R> coef, FoldCoef<N, R> fold)
 {
     constexpr int M = N - R + 1;
     constexpr int CB = kFusedCB;
@@ -98,17 +101,10 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
     const int lane = (int)(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    // block -> (image, tile rows, tile group, group of 64 output channels); the channel groups of one
-    // tile group are neighbours and run on the same XCD, so that V is fetched into one L2 only
-    unsigned bid = xcd_local_block_id(blockIdx.x, gridDim.x);
-    const int kg = bid % k_groups; bid /= k_groups;
-    const int row_groups = (tiles_h + sh.trb - 1) / sh.trb;
-    const int tg = bid % sh.groups; bid /= sh.groups;
-    const int tr = (bid % row_groups) * sh.trb; bid /= row_groups;
-    const int img = bid;
-    const int tc0 = tg * sh.twc;
-    // tile j of the group: row j / twc, column j % twc of a block of trb x twc tiles
-    const long long t0 = ((long long)img * tiles_h + tr) * tiles_w + tc0;
+    // block -> (16 consecutive tiles of the batch, group of 32 output channels); the channel groups of the same
+    // tiles are neighbours and run on the same XCD, so that V is fetched into one L2 only
+    const unsigned bid = xcd_local_block_id(blockIdx.x, gridDim.x);
+    const int kg = (int)(bid % (unsigned)k_groups), t0 = (int)(bid / (unsigned)k_groups) * kFusedTiles;
     const int k0 = kg * kFusedChannels, kw0 = k0 + wave * kFusedWaveChannels;
 
     // ---- direct loads.  A 64-byte row r of a chunk holds its four 16-byte pieces in the places
@@ -118,8 +114,7 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
     // U: one load = one position (8 channels each of the two channel blocks): lane l -> block l / 32,
     //    row (l / 4) % 8, place l % 4.
     const int v_row_l = lane >> 2, v_piece_l = (lane & 3) ^ ((v_row_l >> 1) & 3);
-    long long v_t = t0 + (long long)(v_row_l / sh.twc) * tiles_w + v_row_l % sh.twc;
-    if (v_t > Ttot - 1) v_t = Ttot - 1;               // rows past the end: reread the last tile (never used)
+    const int v_t = t0 + v_row_l < Ttot ? t0 + v_row_l : Ttot - 1;      // rows past the end: reread the last tile (never used)
     const unsigned v_lane_off = (unsigned)(((unsigned)v_t * kChanBlock + (unsigned)v_piece_l * 8u) * sizeof(f16));
     const size_t v_cb_stride = (size_t)Ttot * kChanBlock;          // elements per channel block of a position
     const size_t u_cb_stride = (size_t)Kp * kChanBlock;
@@ -304,35 +299,28 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
         for (int q = 0; q < M; ++q) Y[e][M - 1][q] = fma32(coef.inf, last[q], Y[e][M - 1][q]);
     }
 
-    // ---- the results leave through LDS: all 64 channels at once if the block fits, else 32 at a time
-    f16 *stage = reinterpret_cast<f16 *>(lds_raw);
-    const int tile = lane & 15;
-    const int jr = tile / sh.twc, jc = tile - jr * sh.twc;
-    const bool active = tile < sh.twb && tc0 + jc < tiles_w && tr + jr < tiles_h;
-    const float floor_at = relu ? 0.0f : -__builtin_inff();          // val < floor ? floor : val keeps a NaN
-    constexpr int KB = kFusedChannels / kChanBlock;
-    const int per_pass = one_pass ? KB : 1;
-#pragma unroll 1
-    for (int pass = 0; pass < KB; pass += per_pass) {
-        __syncthreads();              // the operand buffers (first pass) or the block before have been read
-        if (active && (one_pass || (wave >> 2) == pass)) {
+    // ---- the results leave from registers: rows of m elements, neighbouring tiles in neighbouring lanes
+    const int t = t0 + (lane & 15);
+    if (t >= Ttot) return;
+    const int trow = t / tiles_w, tc = t - trow * tiles_w, img = trow / tiles_h, tr = trow - img * tiles_h;
+    const bool relu = (flags & NOVA_FLAG_RELU) != 0, pool = (flags & NOVA_FLAG_POOL2) != 0;
+    const long long plane = pool ? (long long)(H / 2) * (W / 2) : (long long)H * W;
+    f16 *at = y + ((long long)img * K + kw0 + 2 * (lane >> 4)) * plane;            // (K is a multiple of 32: every channel exists)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int k_in = (one_pass ? wave : (wave & 3)) * kFusedWaveChannels + 2 * (lane >> 4) + e;
-                f16 *dst = stage + k_in * sh.k_pitch + jr * M * sh.cols_pitch + jc * M;
+    for (int e = 0; e < 2; ++e) {
+        f16 out[M][M];
 #pragma unroll
-                for (int p = 0; p < M; ++p) {
-                    float o[M];
+        for (int p = 0; p < M; ++p)
 #pragma unroll
-                    for (int q = 0; q < M; ++q) o[q] = Y[e][p][q] < floor_at ? floor_at : Y[e][p][q];
-                    store_block_row<M>(dst + p * sh.cols_pitch, o);
-                }
+            for (int q = 0; q < M; q += 2) {
+                // (rounded in a step of its own, as round_twice does)
+                asm volatile("" : "+v"(Y[e][p][q]), "+v"(Y[e][p][q + 1]));
+                half2v pair = {(f16)Y[e][p][q], (f16)Y[e][p][q + 1]};
+                if (relu) pair = __builtin_elementwise_maximum(pair, half2v{(f16)0.0f, (f16)0.0f});         // NaN stays NaN
+                out[p][q] = pair[0];
+                out[p][q + 1] = pair[1];
             }
-        }
-        __syncthreads();
-        for (int blk = 0; blk < per_pass; ++blk)
-            store_output_block<f16, M, STG>(stage + blk * kChanBlock * sh.k_pitch, y, img, k0 / kChanBlock + pass + blk, tr, tc0,
-                                            K, H, W, tiles_w, sh);
+        store_tile_rows<f16, M, 0, M, true>(out, at + e * plane, tr, tc, H, W, pool);
     }
 }
 
@@ -341,7 +329,6 @@ static int launch_fused_shape(const nova_transforms *t, const void *U, const voi
                               hipStream_t stream)
 {
     constexpr int M = N - R + 1;
-    constexpr int PE = 8;
     constexpr int CB = kFusedCB;
     OutCoef<N, R> coef;
     fill_out_coef<N, R>(t, coef);
@@ -349,57 +336,19 @@ static int launch_fused_shape(const nova_transforms *t, const void *U, const voi
     for (int p = 0; p < M; ++p) fold.c[p] = p == 0 ? coef.zero : 0.0f;
     for (int d = 1; d < N / 2; ++d)
         for (int p = 0; p < M; ++p) fold.c[d * M + p] = coef.pw[(d - 1) * M + p];
-    // The 16 tile slots of a workgroup are a block of trb x twc tiles.  Chosen: the block shape with the lowest
-    // estimated cost per tile of the image -- slots launched (ragged last blocks and twc * trb < 16 waste some)
-    // times a factor 1 + 1.2 / twc for narrow blocks (short runs of V and of y; fitted to timings: 4 x 4 blocks
-    // cost 1.14-1.22 times what full rows of 10-14 tiles cost per slot) -- among those whose output block leaves
-    // in 16-byte stores (its width a whole number of pieces, or one block spanning the image width).
-    const bool aligned = ((uintptr_t)y % 16) == 0;
-    int twb = 1, trb = 1;
-    double best = -1.0;
-    for (int tc = 1; tc <= kFusedTiles && tc <= g.tiles_w; ++tc)
-        for (int tr = 1; tr * tc <= kFusedTiles && tr <= g.tiles_h; ++tr) {
-            const int across = ceil_div(g.tiles_w, tc), down = ceil_div(g.tiles_h, tr);
-            const bool fast = aligned && (across == 1 || (g.W % PE == 0 && (tc * M) % PE == 0));
-            const double used = (double)g.tiles_w * g.tiles_h / ((double)across * down * kFusedTiles);
-            const double merit = used / (1.0 + 1.2 / tc) * (fast ? 1.0 : 0.5);
-            if (merit > best * (1.0 + 1e-9)) { best = merit; twb = tc; trb = tr; }
-        }
-    OutShape sh;
-    sh.groups = ceil_div(g.tiles_w, twb);
-    const size_t stage_bytes = out_shape<N, R, f16>(twb, trb, sh);
-    const size_t loop_bytes = (size_t)2 * N * CB * kFusedTiles * 64 + (size_t)kFusedWaves * N * CB * kFusedWaveChannels * 64;
-    constexpr int KB = kFusedChannels / kChanBlock;
-    const int one_pass = KB * stage_bytes <= 160 * 1024 ? 1 : 0;      // all blocks of 32 channels staged together
-    const size_t out_bytes = one_pass ? KB * stage_bytes : stage_bytes;
-    const size_t lds_bytes = out_bytes > loop_bytes ? out_bytes : loop_bytes;
-    if (lds_bytes > 160 * 1024 || sh.twb > kFusedTiles) return (int)hipErrorInvalidValue;
+    constexpr size_t lds_bytes = (size_t)2 * N * CB * kFusedTiles * 64 + (size_t)kFusedWaves * N * CB * kFusedWaveChannels * 64;
+    static_assert(2 * lds_bytes <= 160 * 1024, "two workgroups per compute unit");
     // 32-bit byte offsets inside one position of V
     if ((size_t)CB * g.T * kChanBlock * sizeof(f16) >= ((size_t)1 << 32)) return (int)hipErrorInvalidValue;
-    const bool vec = g.W % PE == 0 && aligned && (sh.groups == 1 || (twb * M) % PE == 0);
-    const bool flat = !vec && aligned && sh.groups == 1 && g.W >= 2 && sh.rows * g.W + 2 * (PE - 1) >= 2 * PE &&
-                      (long long)sh.rows * g.W < (1 << 15);
-    if (flat) {
-        sh.pieces = (sh.rows * g.W + 2 * (PE - 1)) / PE;
-        sh.piece_magic = (unsigned)((((unsigned long long)1 << 32) + sh.pieces - 1) / sh.pieces);
-        sh.w_magic = (unsigned)((((unsigned long long)1 << 32) + g.W - 1) / g.W);
-    }
-    sh.pool = (flags & NOVA_FLAG_POOL2) ? 1 : 0;
     const int k_groups = g.Kp / kFusedChannels;
-    const long long blocks = (long long)sh.groups * ceil_div(g.tiles_h, trb) * k_groups * g.N;
+    const long long blocks = (g.T + kFusedTiles - 1) / kFusedTiles * k_groups;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
-    auto kern = vec ? fused_contract_output_kernel<N, R, kStoreVec>
-              : flat ? fused_contract_output_kernel<N, R, kStoreFlat> : fused_contract_output_kernel<N, R, kStoreScalar>;
-    static bool raised[3] = {false, false, false};          // more than 64 KiB of dynamic LDS: asked for once per kernel
-    const int which = vec ? 0 : flat ? 1 : 2;
-    if (!raised[which]) {
-        NOVA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         160 * 1024));
-        raised[which] = true;
-    }
+    auto kern = fused_contract_output_kernel<N, R>;
+    if (lds_bytes > 64 * 1024)
+        NOVA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * kFusedWaves), lds_bytes, stream,
-                       (const f16 *)U, (const f16 *)V, (f16 *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w, g.Kp, g.T, k_groups,
-                       (flags & NOVA_FLAG_RELU) ? 1 : 0, one_pass, sh, coef, fold);
+                       (const f16 *)U, (const f16 *)V, (f16 *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w, g.Kp, (int)g.T, k_groups,
+                       flags, coef, fold);
     return (int)hipGetLastError();
 }
 

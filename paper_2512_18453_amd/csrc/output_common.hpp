@@ -328,7 +328,7 @@ __device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
 
 // Rows [P0, P0 + ROWS) of a tile's outputs, rounded, to the image plane at `plane` (or 2 x 2 max-pooled: H, W, m even,
 // so no window straddles two tiles).
-template <typename T, int M, int P0, int ROWS>
+template <typename T, int M, int P0, int ROWS, bool NT = false>
 __device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W, bool pool)
 {
     if (pool) {
@@ -340,16 +340,12 @@ __device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plan
             T best[M / 2];
 #pragma unroll
             for (int s = 0; s < M / 2; ++s) {
-                const float v0 = (float)out[2 * p][2 * s], v1 = (float)out[2 * p][2 * s + 1];
-                const float v2 = (float)out[2 * p + 1][2 * s], v3 = (float)out[2 * p + 1][2 * s + 1];
-                float top = v0;                                   // a NaN in the window wins
-                top = (v1 > top || v1 != v1) ? v1 : top;
-                top = (v2 > top || v2 != v2) ? v2 : top;
-                top = (v3 > top || v3 != v3) ? v3 : top;
-                best[s] = (T)top;                                 // one of the four values: exact
+                // (elementwise maximum: a NaN in the window wins)
+                best[s] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(out[2 * p][2 * s], out[2 * p + 1][2 * s]),
+                                                        __builtin_elementwise_maximum(out[2 * p][2 * s + 1], out[2 * p + 1][2 * s + 1]));
             }
             if (w0 + M / 2 <= Wp) {
-                store_row<T, M / 2>(at + (long long)p * Wp, best);
+                store_row<T, M / 2, NT>(at + (long long)p * Wp, best);
             } else {
 #pragma unroll
                 for (int s = 0; s < M / 2; ++s)
@@ -363,7 +359,7 @@ __device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plan
         for (int p = 0; p < ROWS; ++p) {
             if (h0 + p >= H) continue;
             if (w0 + M <= W) {
-                store_row<T, M>(at + (long long)p * W, out[p]);
+                store_row<T, M, NT>(at + (long long)p * W, out[p]);
             } else {
 #pragma unroll
                 for (int s = 0; s < M; ++s)
