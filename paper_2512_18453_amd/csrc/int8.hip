@@ -309,41 +309,30 @@ contract_i8_kernel(const signed char *__restrict__ Uq, const VT *__restrict__ Vq
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int i = 0; i < MB; ++i)
-                acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bf[j], af[i], acc[j][i], 0, 0, 0);
+                acc[j][i] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[i], bf[j], acc[j][i], 0, 0, 0);
         if (cb + 1 < c_blocks) store_lds(buf ^ 1);
         __syncthreads();
     }
 
-    // D[row = k][col = t]: lane holds t = lane%32 and channels k = 8*(e/4) + 4*(lane/32) + e%4
-    const int k_base = (lane >> 5) * 4;
+    // D[row = t][col = k]: lane holds channel lane % 32 of a block and tiles 8 (e / 4) + 4 (lane / 32) + e % 4; a store covers two
+    // whole 128-byte rows of M
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         const int kb = (k0 >> 5) + wn * NB + j;
         if (kb >= k_blocks) continue;
-        float both[16];
+        float both = 0.0f;
         if constexpr (DEQUANT) {
+            const int k = kb * kChanBlock + frag_row;
+            both = u_scales[scale_kind == 1 ? (k < K ? k : K - 1) : scale_kind == 2 ? xi : 0] * sv;
+        }
+        int *plane = reinterpret_cast<int *>(Mo) + ((size_t)xi * k_blocks + kb) * (size_t)Tp * kChanBlock + frag_row;
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int k = kb * kChanBlock + (e >> 2) * 8 + k_base + (e & 3);
-                both[e] = u_scales[scale_kind == 1 ? (k < K ? k : K - 1) : scale_kind == 2 ? xi : 0] * sv;
+                const int t = t0 + (wm * MB + i) * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+                if (t < T) plane[(size_t)t * kChanBlock] = DEQUANT ? __float_as_int((float)acc[j][i][e] * both) : acc[j][i][e];
             }
-        }
-        const size_t plane = ((size_t)xi * k_blocks + kb) * (size_t)Tp * kChanBlock + k_base;
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            const int t = t0 + (wm * MB + i) * 32 + frag_row;
-            if (t >= T) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                int4v out;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if constexpr (DEQUANT) out[e] = __float_as_int((float)acc[j][i][4 * q + e] * both[4 * q + e]);
-                    else out[e] = acc[j][i][4 * q + e];
-                }
-                *reinterpret_cast<int4v *>(reinterpret_cast<int *>(Mo) + plane + (size_t)t * kChanBlock + q * 8) = out;
-            }
-        }
     }
 }
 
