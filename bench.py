@@ -123,6 +123,8 @@ def main():
     # ---- per-stage timing inside the pipeline, same launch configuration (one launch = one slab):
     # the three stage entry points are called in sequence, as nova_winograd_conv2d does, with an
     # event between them, so each kernel sees the cache state it sees in the timed region above
+    # (on the headline workload; the call runs layers with little work as one kernel and others with the column half of
+    # the output transform in the contraction, and the figures below are then those of the separate calls)
     tiles = -(-H // m) * (-(-W // m))
     T_slab = slab_imgs * tiles
     cb, kb = -(-C // 32) * 32, -(-K // 32) * 32

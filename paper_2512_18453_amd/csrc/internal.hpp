@@ -126,7 +126,7 @@ bool fused_contract_output_preferred(const nova_transforms *t, const Geometry &g
 int launch_fused_contract_output(const nova_transforms *t, const void *U, const void *V, void *y, const Geometry &g,
                                  int dtype, int flags, void *stream);
 // The whole layer in one kernel, for layers with little work: layer_tiles names the workgroup shape nova_winograd_conv2d
-// runs it with (0: it does not); domain_bytes: of V and M of the separate kernels.  The results are those of the separate
+// runs it with (0: it does not); domain_bytes: of V and what follows it in the separate kernels.  The results are those of the separate
 // kernels bit for bit.
 int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t domain_bytes);
 int launch_layer(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int dtype, int flags, int tiles,

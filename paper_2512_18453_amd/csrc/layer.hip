@@ -322,11 +322,12 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 // that is well below the estimate for the separate kernels.  Estimates (us), fitted to 386 layers of 2 to 3500
 // tiles, 5 to 260 -> 5 to 512 channels, timed both ways on one MI355X (sd 5-16 %):
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
-//   separate kernels  kStages + 0.3 per MB of V and M (+ 14 per GFLOP in binary32; no M with 64 input channels in one kernel)
-// Over these layers the rule is 1.31 times faster than the separate kernels (best choice every time: 1.32), and in
-// three slower, by 9 to 17 %.  us, separate / one kernel: 16 -> 16 @32x32 F(4,3) binary32 12.3 / 6.7; 40 -> 70 @45x61 batch 8
-// F(6,3) binary32 29.5 / 16.7; 48 -> 96 5x5 @35x35 batch 16 27.6 / 16.7; 64 -> 64 @56x56 batch 8 F(6,3) 17.4 / 14.0; 64 ->
-// 128 @112x112 F(4,3) 18.7 / 10.4; not taken: 256 -> 256 @56x56 F(4,3) 18.2 / 22, 512 -> 512 @28x28 17 / 38.
+//   separate kernels  kStages + 0.3 per MB of what they write between them (+ 10 per GFLOP in binary32)
+// The margin is 0.92, and 0.8 from 30 us on, where the estimates are widest: of 235 other layers of 100 to 12000 tiles two are 4 %
+// or more slower than the separate kernels this way (with 0.92 throughout four), and all together 1.23 times faster.
+// us, separate / one kernel: 16 -> 16 @32x32 F(4,3) binary32 12.3 / 6.7; 40 -> 70 @45x61 batch 8 F(6,3) binary32 29.5 / 16.7; 48
+// -> 96 5x5 @35x35 batch 16 27.6 / 16.7; 64 -> 64 @56x56 batch 8 F(6,3) 17.4 / 14.0; 64 -> 128 @112x112 F(4,3) 18.7 / 10.4; not
+// taken: 256 -> 256 @56x56 F(4,3) 18.2 / 22, 512 -> 512 @28x28 17 / 38.
 struct LayerTimes { double turn[2], once[2], stages; };          // [8 tiles, 16 tiles]
 static const LayerTimes &layer_times(int n, bool half)
 {
@@ -345,8 +346,8 @@ int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t d
     const LayerTimes &lt = layer_times(g.n, half);
     const int turns = ceil_div(g.C, half ? 32 : 16), k_groups = ceil_div(g.K, half && g.n < 10 ? 32 : 16);
     double best = lt.stages + 0.3e-6 * (double)domain_bytes;
-    if (!half) best += 14e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
-    best *= 0.92;
+    if (!half) best += 10e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
+    best *= best < 30.0 ? 0.92 : 0.8;
     int tiles = 0;
     for (int i = 0; i < (g.n < 10 ? 2 : 1); ++i) {
         const long long groups = (g.T + 8 * (i + 1) - 1) / (8 * (i + 1)) * k_groups;
