@@ -159,18 +159,21 @@ contract_tile_kernel(const ST *__restrict__ U, const ST *__restrict__ V, MT *__r
 #pragma unroll
                     for (int i = 0; i < MB; ++i) acc[0][j][i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[0][i], uf[0][j], acc[0][j][i], 0, 0, 0);
             } else {
+                // (the two chains in turn, so that one's instruction does not wait for the one before)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 2; ++e)
 #pragma unroll
                     for (int q = 0; q < READS; ++q) {
                         if (q == 1 && left <= 8) continue;
 #pragma unroll
-                        for (int j = 0; j < NB; ++j)
+                        for (int ch = 0; ch < 2; ++ch)
 #pragma unroll
-                            for (int i = 0; i < MB; ++i) {
-                                float16v &sum = acc[e / 2 % CHAINS][j][i];
-                                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[q][i][e], uf[q][j][e], sum, 0, 0, 0);
-                            }
+                            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                                for (int i = 0; i < MB; ++i) {
+                                    float16v &sum = acc[ch % CHAINS][j][i];
+                                    sum = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[q][i][2 * ch + e], uf[q][j][2 * ch + e], sum, 0, 0, 0);
+                                }
                     }
             }
         }

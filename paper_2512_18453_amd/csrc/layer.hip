@@ -59,7 +59,9 @@ template <> struct Products<float> {
     static __device__ __forceinline__ void add(float4v (&acc)[CHAINS], const frag &u, const float4v &v)
     {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e / 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[e], v[e], acc[e / 2], 0, 0, 0);
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int ch = 0; ch < CHAINS; ++ch) acc[ch] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[2 * ch + e], v[2 * ch + e], acc[ch], 0, 0, 0);
     }
 };
 
