@@ -235,9 +235,9 @@ size_t nova_conv2d_workspace_bytes(int N, int C, int H, int W, int K, int m, int
  * y = conv r x r (x, w), stride 1, zero border (r-1)/2 (3 x 3 with border 1 is the paper's case; the
  * 5 x 5 extension takes border 2, "same" output size), through F(m x m, r x r) with the handle's matrices:
  * input transform -> n*n channel contractions -> output transform, enqueued on `stream`.
- * With C <= 4 the contraction is done inside the output transform, as a binary32 multiply-add chain
- * over the channels (products of two stored values are exact in binary32), instead of on the matrix
- * unit; the result agrees with nova_contract + nova_output_transform to rounding, not bit for bit.
+ * With C <= 4 the products are formed inside the output transform -- on the matrix unit, 4 channels long (binary16, points in
+ * the paired order), or as a binary32 multiply-add chain over the channels (products of two stored values are exact in
+ * binary32) -- and the result agrees with nova_contract + nova_output_transform to rounding, not bit for bit.
  * x: device [N][C][H][W]; U: from nova_filter_transform with the same handle, K, C, dtype;
  * y: device [N][K][H][W]; all of dtype.  H, W >= 1 arbitrary: the image is zero-extended to
  * whole tiles and the result cropped.  workspace: device, at least

@@ -11,7 +11,8 @@
 // output index) or difference (odd output index), which halves the multiplications.  Binary32
 // arithmetic, one rounding to the storage format at the store; optional fused ReLU.
 //
-// Few input channels (C <= 4, the first layer of an image network): the products are not read
+// Few input channels (C <= 4, the first layer of an image network; binary32 or points in another order than the paired one, for
+// the rest few_channels.hip): the products are not read
 // from M but formed here, M[xi][t][k] = sum_c V[xi][t][c] U[xi][k][c] as a binary32 multiply-add
 // chain over c (the factors are exact in binary32), from V in a compact layout Vc [n*n][T][4] and a packed copy
 // Uc [n*n][Kp][4] of the first four channels of U.  M, n*n*T*K values that would be written and
