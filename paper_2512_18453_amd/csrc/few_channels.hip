@@ -179,47 +179,51 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
         }
     } else {
         // 2 x 2 max-pool (H, W, m even): the wave with the odd rows hands their pairwise maxima over
-        auto larger = [](f16 a, f16 b) __attribute__((always_inline)) { return __builtin_elementwise_maximum(a, b); };      // a NaN wins
-        f16 row_max[4][MH][MH];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int pi = 0; pi < MH; ++pi)
-#pragma unroll
-                for (int q = 0; q < MH; ++q) row_max[e][pi][q] = larger(out[e][pi][2 * q], out[e][pi][2 * q + 1]);
-        f16 *handed = reinterpret_cast<f16 *>(lds_raw) + (wave >> 1) * (4 * MH * MH * 64) + lane;
-        static_assert(2 * 4 * MH * MH * 64 * 2 <= N2 * (kFewTiles + kFewGroup) * 8, "what is handed over takes the operands' place");
-        __syncthreads();                      // the operands have been read
-        if (half == 1) {
+        auto pooled = [&](auto zeros) __attribute__((always_inline)) {
+            auto larger = [](f16 a, f16 b) __attribute__((always_inline)) { return larger_of<decltype(zeros)::value>(a, b); };
+            f16 row_max[4][MH][MH];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
                 for (int pi = 0; pi < MH; ++pi)
 #pragma unroll
-                    for (int q = 0; q < MH; ++q) handed[((e * MH + pi) * MH + q) * 64] = row_max[e][pi][q];
-        }
-        __syncthreads();
-        if (half == 0 && active) {
-            const int Hp = H / 2, Wp = W / 2, w0 = tc * MH;
+                    for (int q = 0; q < MH; ++q) row_max[e][pi][q] = larger(out[e][pi][2 * q], out[e][pi][2 * q + 1]);
+            f16 *handed = reinterpret_cast<f16 *>(lds_raw) + (wave >> 1) * (4 * MH * MH * 64) + lane;
+            static_assert(2 * 4 * MH * MH * 64 * 2 <= N2 * (kFewTiles + kFewGroup) * 8, "what is handed over takes the operands' place");
+            __syncthreads();                      // the operands have been read
+            if (half == 1) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                f16 *plane = y + (((long long)img * K + k0 + e) * Hp + tr * MH) * Wp + w0;
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int pi = 0; pi < MH; ++pi) {
-                    if (k0 + e >= K || tr * MH + pi >= Hp) continue;
-                    f16 best[MH];
+                    for (int pi = 0; pi < MH; ++pi)
 #pragma unroll
-                    for (int q = 0; q < MH; ++q) best[q] = larger(row_max[e][pi][q], handed[((e * MH + pi) * MH + q) * 64]);
-                    if (w0 + MH <= Wp) {
-                        store_row<f16, MH, true>(plane + (long long)pi * Wp, best);
-                    } else {
+                        for (int q = 0; q < MH; ++q) handed[((e * MH + pi) * MH + q) * 64] = row_max[e][pi][q];
+            }
+            __syncthreads();
+            if (half == 0 && active) {
+                const int Hp = H / 2, Wp = W / 2, w0 = tc * MH;
 #pragma unroll
-                        for (int q = 0; q < MH; ++q)
-                            if (w0 + q < Wp) plane[(long long)pi * Wp + q] = best[q];
+                for (int e = 0; e < 4; ++e) {
+                    f16 *plane = y + (((long long)img * K + k0 + e) * Hp + tr * MH) * Wp + w0;
+#pragma unroll
+                    for (int pi = 0; pi < MH; ++pi) {
+                        if (k0 + e >= K || tr * MH + pi >= Hp) continue;
+                        f16 best[MH];
+#pragma unroll
+                        for (int q = 0; q < MH; ++q) best[q] = larger(row_max[e][pi][q], handed[((e * MH + pi) * MH + q) * 64]);
+                        if (w0 + MH <= Wp) {
+                            store_row<f16, MH, true>(plane + (long long)pi * Wp, best);
+                        } else {
+#pragma unroll
+                            for (int q = 0; q < MH; ++q)
+                                if (w0 + q < Wp) plane[(long long)pi * Wp + q] = best[q];
+                        }
                     }
                 }
             }
-        }
+        };
+        if (relu) pooled(std::false_type{});                // (no -0 is left)
+        else pooled(std::true_type{});
     }
 }
 

@@ -320,7 +320,7 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
                 out[p][q] = pair[0];
                 out[p][q + 1] = pair[1];
             }
-        store_tile_rows<f16, M, 0, M, true>(out, at + e * plane, tr, tc, H, W, pool);
+        store_tile_rows<f16, M, 0, M, true>(out, at + e * plane, tr, tc, H, W, pool, !relu);
     }
 }
 

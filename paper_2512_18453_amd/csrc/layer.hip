@@ -139,18 +139,19 @@ __device__ __forceinline__ void outputs_rows_first(F &&m_at, T (&out)[N - R + 1]
 // The outputs of part `part` (wave-uniform) of the SPLIT that share a pair: whole pairs of rows, so that pooling
 // stays within a part.
 template <int N, int R, typename T, int SPLIT, bool RELU, bool ROWS_FIRST, int I, typename F>
-__device__ __forceinline__ void output_part(int part, F &&m_at, const OutCoef<N, R> &coef, T *plane, int tr, int tc, int H, int W, bool pool)
+__device__ __forceinline__ void output_part(int part, F &&m_at, const OutCoef<N, R> &coef, T *plane, int tr, int tc, int H, int W, bool pool,
+                                            bool zeros)
 {
     constexpr int M = N - R + 1;
     if constexpr (I + 1 < SPLIT) {
-        if (part != I) return output_part<N, R, T, SPLIT, RELU, ROWS_FIRST, I + 1>(part, m_at, coef, plane, tr, tc, H, W, pool);
+        if (part != I) return output_part<N, R, T, SPLIT, RELU, ROWS_FIRST, I + 1>(part, m_at, coef, plane, tr, tc, H, W, pool, zeros);
     }
     constexpr int P0 = 2 * ((M / 2 * I + SPLIT - 1) / SPLIT), ROWS = 2 * ((M / 2 * (I + 1) + SPLIT - 1) / SPLIT) - P0;
     static_assert(ROWS >= 2 && (!ROWS_FIRST || SPLIT == 1), "parts");
     T out[ROWS][M];
     if constexpr (ROWS_FIRST) outputs_rows_first<N, R, T, RELU>(m_at, out, coef);
     else outputs_columns_first<N, R, T, RELU, P0, ROWS>(m_at, out, coef);
-    store_tile_rows<T, M, P0, ROWS>(out, plane, tr, tc, H, W, pool);
+    store_tile_rows<T, M, P0, ROWS>(out, plane, tr, tc, H, W, pool, zeros);
 }
 
 // Where the transform's values go: the thread's word in the row of its tile, position by position.
@@ -258,6 +259,7 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
     // ---- M to LDS: [position][KB channels][TB tiles], the channels of a block in the order e * 4 + piece in which
     // the lanes hold them (channel 4 * piece + e)
     const bool round_m = sizeof(T) == 2 && (flags & NOVA_FLAG_M_F16);
+    const bool zeros = !RELU || round_m;                    // (a sum of products that were rounded to -0 passes the ReLU as -0)
     if (TB == 16 || (lane & 15) < TB) {
 #pragma unroll
         for (int i = 0; i < OWN; ++i)
@@ -283,7 +285,8 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
         const float *m_pair = m_lds + pair;
         auto m_at = [&](int a, int b) __attribute__((always_inline)) { return m_pair[(a * N + b) * (KB * TB)]; };
         output_part<N, R, T, SPLIT, RELU, ROWS_FIRST, 0>(SPLIT > 1 ? __builtin_amdgcn_readfirstlane(item / (KB * TB)) : 0, m_at, coef.out,
-                                                        y + ((long long)img * K + k) * (pool ? (long long)(H / 2) * (W / 2) : (long long)H * W), tr, tc, H, W, pool);
+                                                        y + ((long long)img * K + k) * (pool ? (long long)(H / 2) * (W / 2) : (long long)H * W), tr, tc, H, W, pool,
+                                                        zeros);
     }
 }
 

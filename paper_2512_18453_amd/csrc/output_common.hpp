@@ -326,32 +326,49 @@ __device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
 }
 #undef NOVA_STORE
 
-// Rows [P0, P0 + ROWS) of a tile's outputs, rounded, to the image plane at `plane` (or 2 x 2 max-pooled: H, W, m even,
-// so no window straddles two tiles).
+// The larger of two values, of which a is the earlier one of its window: a NaN wins, and of a zero of either sign the
+// earlier stays, as in the separate output transform's comparisons one after the other (elementwise maximum alone makes
+// +0 of the two).  ZEROS: whether zeros of both signs can meet; where a ReLU leaves +0 only, the maximum alone will do.
+template <bool ZEROS, typename T>
+__device__ __forceinline__ T larger_of(T a, T b)
+{
+    const T top = __builtin_elementwise_maximum(a, b);
+    if constexpr (ZEROS) return top == a ? a : top;
+    return top;
+}
+
+// Rows [P0, P0 + ROWS) of a tile's outputs, rounded, 2 x 2 max-pooled to the image plane at `plane` (H, W, m even, so no
+// window straddles two tiles).
+template <typename T, int M, int P0, int ROWS, bool NT, bool ZEROS>
+__device__ __forceinline__ void store_pooled_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W)
+{
+    const int Hp = H / 2, Wp = W / 2, h0 = (tr * M + P0) / 2, w0 = tc * (M / 2);
+    T *at = plane + (long long)h0 * Wp + w0;
+#pragma unroll
+    for (int p = 0; p < ROWS / 2; ++p) {
+        if (h0 + p >= Hp) continue;
+        T best[M / 2];
+#pragma unroll
+        for (int s = 0; s < M / 2; ++s)
+            best[s] = larger_of<ZEROS>(larger_of<ZEROS>(out[2 * p][2 * s], out[2 * p][2 * s + 1]),
+                                       larger_of<ZEROS>(out[2 * p + 1][2 * s], out[2 * p + 1][2 * s + 1]));
+        if (w0 + M / 2 <= Wp) {
+            store_row<T, M / 2, NT>(at + (long long)p * Wp, best);
+        } else {
+#pragma unroll
+            for (int s = 0; s < M / 2; ++s)
+                if (w0 + s < Wp) at[(long long)p * Wp + s] = best[s];
+        }
+    }
+}
+
+// Rows [P0, P0 + ROWS) of a tile's outputs, rounded, to the image plane at `plane`, or pooled; zeros: as ZEROS above.
 template <typename T, int M, int P0, int ROWS, bool NT = false>
-__device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W, bool pool)
+__device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plane, int tr, int tc, int H, int W, bool pool, bool zeros)
 {
     if (pool) {
-        const int Hp = H / 2, Wp = W / 2, h0 = (tr * M + P0) / 2, w0 = tc * (M / 2);
-        T *at = plane + (long long)h0 * Wp + w0;
-#pragma unroll
-        for (int p = 0; p < ROWS / 2; ++p) {
-            if (h0 + p >= Hp) continue;
-            T best[M / 2];
-#pragma unroll
-            for (int s = 0; s < M / 2; ++s) {
-                // (elementwise maximum: a NaN in the window wins)
-                best[s] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(out[2 * p][2 * s], out[2 * p + 1][2 * s]),
-                                                        __builtin_elementwise_maximum(out[2 * p][2 * s + 1], out[2 * p + 1][2 * s + 1]));
-            }
-            if (w0 + M / 2 <= Wp) {
-                store_row<T, M / 2, NT>(at + (long long)p * Wp, best);
-            } else {
-#pragma unroll
-                for (int s = 0; s < M / 2; ++s)
-                    if (w0 + s < Wp) at[(long long)p * Wp + s] = best[s];
-            }
-        }
+        if (zeros) store_pooled_rows<T, M, P0, ROWS, NT, true>(out, plane, tr, tc, H, W);
+        else store_pooled_rows<T, M, P0, ROWS, NT, false>(out, plane, tr, tc, H, W);
     } else {
         const int h0 = tr * M + P0, w0 = tc * M;
         T *at = plane + (long long)h0 * W + w0;

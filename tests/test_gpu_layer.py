@@ -108,3 +108,33 @@ def test_values_that_are_not_finite(bad, m, C, K):
             want, got = by_stages(t, x, U, K, flags), nova.nova_winograd_conv2d(t, x, U, K, flags=flags)
             torch.cuda.synchronize()
             assert torch.equal(got.nan_to_num(nan=7.0), want.nan_to_num(nan=7.0)) and not torch.isfinite(got).all()
+
+
+def pooled_as_stated(y):
+    # the first of the largest in the order of the image: a zero keeps the sign that the first zero had
+    a = y.float().cpu()
+    best = a[..., 0::2, 0::2]
+    for v in (a[..., 0::2, 1::2], a[..., 1::2, 0::2], a[..., 1::2, 1::2]):
+        best = torch.where(v > best, v, best)
+    return best.to(y.dtype)
+
+
+@pytest.mark.parametrize("m,C,K,N,H,W", [(4, 20, 24, 2, 20, 22), (6, 64, 32, 2, 20, 22), (8, 20, 24, 1, 18, 26),          # one kernel
+                                         (6, 64, 64, 8, 112, 112), (8, 64, 32, 4, 200, 168),                             # fused 64-channel kernel
+                                         (4, 3, 40, 2, 30, 26), (8, 3, 40, 2, 30, 26),                                   # first layer
+                                         (8, 128, 64, 120, 32, 40), (8, 300, 64, 8, 48, 48)])                             # columns; separate kernels
+def test_signs_of_zeros_under_pooling(m, C, K, N, H, W):
+    # results so small that binary16 rounds most of them to a zero, of either sign
+    t = nova.nova_make_transforms(points_for(m, 3), m, 3)
+    gen = torch.Generator(device=DEV).manual_seed(31 * m + C)
+    x = (torch.randn((N, C, H, W), device=DEV, generator=gen) * 2.0 ** -8).half()
+    w = (torch.randn((K, C, 3, 3), device=DEV, generator=gen) * 2.0 ** -17 / (9.0 * C) ** 0.5).half()
+    U = nova.nova_filter_transform(t, w)
+    for flags in (0, nova.NOVA_FLAG_RELU, nova.NOVA_FLAG_M_F16, nova.NOVA_FLAG_RELU | nova.NOVA_FLAG_M_F16):
+        plain = nova.nova_winograd_conv2d(t, x, U, K, flags=flags)
+        want = pooled_as_stated(plain).view(torch.int16)
+        got = nova.nova_winograd_conv2d(t, x, U, K, flags=flags | nova.NOVA_FLAG_POOL2).cpu().view(torch.int16)
+        assert (want == 0).any() and (want > 0).any() and (flags & nova.NOVA_FLAG_RELU or (want == -32768).any())
+        assert torch.equal(got, want), (flags, int((got != want).sum()))
+        if C > 4:
+            assert torch.equal(by_stages(t, x, U, K, flags | nova.NOVA_FLAG_POOL2).cpu().view(torch.int16), want), flags
