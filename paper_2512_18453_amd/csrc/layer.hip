@@ -174,7 +174,7 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
     constexpr int CH = sizeof(T) == 2 ? 32 : 16;            // input channels per turn
     using B = TileWindows<N, T, CH, TB, RS>;
     using P = Products<T>;
-    constexpr int M = N - R + 1, CPT = B::CPT, THREADS = B::THREADS, WAVES = THREADS / 64;
+    constexpr int M = N - R + 1, THREADS = B::THREADS, WAVES = THREADS / 64;
     constexpr int KF = KB / 16, OWN = N * N / WAVES;         // 16-channel blocks; positions of a wave
     // threads that share a pair's output rows: as many as there are, at most one per two rows
     constexpr int SPLIT = ROWS_FIRST || THREADS < 2 * KB * TB ? 1 : THREADS / (KB * TB) < M / 2 ? THREADS / (KB * TB) : M / 2;
