@@ -18,6 +18,8 @@
 // output_transform.hip) took 110.  On the way: as below but operands read column by column when needed 67, cropping and
 // comparisons per store and a select for the ReLU 72.
 // The matrix unit's sum of 4 products is nearer to 64 bits than the chain's (relative error 2.3e-8 against 2.7e-8).
+#include <algorithm>
+
 #include "output_common.hpp"
 
 namespace nova {
@@ -93,7 +95,7 @@ __device__ __forceinline__ void few_outputs(const half4 *u, const half4 *v, floa
 template <int N, int R, bool ROUND_M, bool POOL>
 __global__ void __launch_bounds__(256, 2)
 few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 *__restrict__ y, int K, int H, int W, int tiles_h, int tiles_w,
-                    int Kp, int Ttot, int k_groups, int relu, OutCoef<N, R> coef)
+                    int Kp, int Ttot, int k_groups, int relu, int narrow, OutCoef<N, R> coef)
 {
     constexpr int M = N - R + 1, MH = M / 2, N2 = N * N, THREADS = 256;
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -153,6 +155,18 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
                 out[e][pi][q + 1] = pair[1];
             }
     if constexpr (!POOL) {
+        if (narrow) {                             // the results leave through LDS
+            f16 *block = reinterpret_cast<f16 *>(lds_raw);
+            __syncthreads();                      // the operands have been read
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int pi = 0; pi < MH; ++pi)
+                    TileRowsInLds<M>::put(block, (wave >> 1) * 16 + 4 * (lane >> 4) + e, lane & 15, 2 * pi + half, out[e][pi]);
+            __syncthreads();
+            TileRowsInLds<M>::store(block, y, kg * kFewGroup, K, t0, Ttot, tiles_h, tiles_w, H, W);
+            return;
+        }
         const int w0 = tc * M, h0 = tr * M;
         f16 *plane = y + (((long long)img * K + k0) * H + h0) * W + w0;
         if (__all(active && k0 + 4 <= K && h0 + M <= H && w0 + M <= W)) {             // nothing to crop in the whole wave
@@ -239,8 +253,17 @@ static int launch_few(const nova_transforms *t, const void *Vc, const void *Uc, 
     const bool round_m = (flags & NOVA_FLAG_M_F16) != 0, pool = (flags & NOVA_FLAG_POOL2) != 0;
     auto kern = round_m ? (pool ? few_channels_kernel<N, R, true, true> : few_channels_kernel<N, R, true, false>)
                         : (pool ? few_channels_kernel<N, R, false, true> : few_channels_kernel<N, R, false, false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), (size_t)N * N * (kFewTiles + kFewGroup) * 8, stream, (const f16 *)Vc, (const f16 *)Uc,
-                       (f16 *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w, g.Kp, (int)g.T, k_groups, (flags & NOVA_FLAG_RELU) ? 1 : 0, coef);
+    // Results through LDS (TileRowsInLds): time of the call with it against rows straight from registers, 280 layers of 2 to
+    // 224 columns: where tiles overhang the right edge 1.05 to 3.2 times as fast in up to 30 columns, up to 40 still 1.0 to 1.65 but
+    // for F(6,3), whose 12-byte rows store as fast then (0.93 to 1.01); up to two whole tiles 0.97 to 2.6 (F(2,3) 0.92); 0.7 to
+    // 1.2 in more.  (Pooled as well it gained 0.98 to 1.07.)
+    const bool narrow = !pool && g.W <= (g.m == 6 ? 30 : 40) && (g.W % g.m != 0 || (g.m > 2 && g.tiles_w <= 2));
+    constexpr int M = N - R + 1, OPERANDS = N * N * (kFewTiles + kFewGroup) * 8;
+    const int lds_bytes = narrow ? std::max(OPERANDS, TileRowsInLds<M>::BYTES) : OPERANDS;
+    if (lds_bytes > 64 * 1024)
+        NOVA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), (size_t)lds_bytes, stream, (const f16 *)Vc, (const f16 *)Uc,
+                       (f16 *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w, g.Kp, (int)g.T, k_groups, (flags & NOVA_FLAG_RELU) ? 1 : 0, narrow ? 1 : 0, coef);
     return (int)hipGetLastError();
 }
 

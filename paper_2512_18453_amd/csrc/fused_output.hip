@@ -81,7 +81,7 @@ template <int N, int R>
 __global__ void __launch_bounds__(64 * kFusedWaves, 2)
 fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16 *__restrict__ y,
                              int K, int H, int W, int tiles_h, int tiles_w, int Kp, int Ttot, int k_groups,
-                             int flags, OutCoef<N, R> coef, FoldCoef<N, R> fold)
+                             int flags, int narrow, OutCoef<N, R> coef, FoldCoef<N, R> fold)
 {
     constexpr int M = N - R + 1;
     constexpr int CB = kFusedCB;
@@ -299,16 +299,8 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
         for (int q = 0; q < M; ++q) Y[e][M - 1][q] = fma32(coef.inf, last[q], Y[e][M - 1][q]);
     }
 
-    // ---- the results leave from registers: rows of m elements, neighbouring tiles in neighbouring lanes
-    const int t = t0 + (lane & 15);
-    if (t >= Ttot) return;
-    const int trow = t / tiles_w, tc = t - trow * tiles_w, img = trow / tiles_h, tr = trow - img * tiles_h;
     const bool relu = (flags & NOVA_FLAG_RELU) != 0, pool = (flags & NOVA_FLAG_POOL2) != 0;
-    const long long plane = pool ? (long long)(H / 2) * (W / 2) : (long long)H * W;
-    f16 *at = y + ((long long)img * K + kw0 + 2 * (lane >> 4)) * plane;            // (K is a multiple of 32: every channel exists)
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        f16 out[M][M];
+    auto round_tile = [&](int e, f16 (&out)[M][M]) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < M; ++p)
 #pragma unroll
@@ -320,6 +312,33 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
                 out[p][q] = pair[0];
                 out[p][q + 1] = pair[1];
             }
+    };
+    // ---- narrow images: the results leave through LDS (K is a multiple of 32: every channel exists)
+    if (narrow) {
+        f16 *block = reinterpret_cast<f16 *>(lds_raw);
+        __syncthreads();                      // the operands have been read
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            f16 out[M][M];
+            round_tile(e, out);
+#pragma unroll
+            for (int p = 0; p < M; ++p)
+                TileRowsInLds<M>::put(block, wave * kFusedWaveChannels + 2 * (lane >> 4) + e, lane & 15, p, out[p]);
+        }
+        __syncthreads();
+        TileRowsInLds<M>::store(block, y, k0, K, t0, Ttot, tiles_h, tiles_w, H, W);
+        return;
+    }
+    // ---- the results leave from registers: rows of m elements, neighbouring tiles in neighbouring lanes
+    const int t = t0 + (lane & 15);
+    if (t >= Ttot) return;
+    const int trow = t / tiles_w, tc = t - trow * tiles_w, img = trow / tiles_h, tr = trow - img * tiles_h;
+    const long long plane = pool ? (long long)(H / 2) * (W / 2) : (long long)H * W;
+    f16 *at = y + ((long long)img * K + kw0 + 2 * (lane >> 4)) * plane;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        f16 out[M][M];
+        round_tile(e, out);
         store_tile_rows<f16, M, 0, M, true>(out, at + e * plane, tr, tc, H, W, pool, !relu);
     }
 }
@@ -338,17 +357,22 @@ static int launch_fused_shape(const nova_transforms *t, const void *U, const voi
         for (int p = 0; p < M; ++p) fold.c[d * M + p] = coef.pw[(d - 1) * M + p];
     constexpr size_t lds_bytes = (size_t)2 * N * CB * kFusedTiles * 64 + (size_t)kFusedWaves * N * CB * kFusedWaveChannels * 64;
     static_assert(2 * lds_bytes <= 160 * 1024, "two workgroups per compute unit");
+    static_assert(TileRowsInLds<M>::BYTES <= lds_bytes, "results take the operands' place");
     // 32-bit byte offsets inside one position of V
     if ((size_t)CB * g.T * kChanBlock * sizeof(f16) >= ((size_t)1 << 32)) return (int)hipErrorInvalidValue;
     const int k_groups = g.Kp / kFusedChannels;
     const long long blocks = (g.T + kFusedTiles - 1) / kFusedTiles * k_groups;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
+    // Results through LDS (TileRowsInLds): time of the call with it against rows straight from registers, 400 layers of 2
+    // to 230 columns: up to 18 columns 0.96 to 2.7 times as fast (geometric mean 1.35), up to 24 columns 0.95 to 1.15, in more 0.76 to
+    // 1.1; pooled (half as many columns, a quarter of y) 0.93 to 0.97.  256 output channels @111x5 batch 60 F(8,3), whole call: 68.2 -> 36.1 us.
+    const bool narrow = g.W <= 24 && !(flags & NOVA_FLAG_POOL2);
     auto kern = fused_contract_output_kernel<N, R>;
     if (lds_bytes > 64 * 1024)
         NOVA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * kFusedWaves), lds_bytes, stream,
                        (const f16 *)U, (const f16 *)V, (f16 *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w, g.Kp, (int)g.T, k_groups,
-                       flags, coef, fold);
+                       flags, narrow ? 1 : 0, coef, fold);
     return (int)hipGetLastError();
 }
 

@@ -386,6 +386,50 @@ __device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plan
     }
 }
 
+// Results of 16 consecutive tiles and 32 channels (M x M binary16 values of each) that leave through LDS,
+// [channel][tile][row][column], for narrow images: there neighbouring tiles are neighbours in few rows of y, so a store of one
+// row per lane, the tiles in neighbouring lanes, touches a memory line of its own with almost every lane.  Here the
+// rows of a tile go to neighbouring lanes, and rows of narrow images lie one behind the other.
+template <int M>
+struct TileRowsInLds {
+    static constexpr int TILES = 16, CHANNELS = 32;
+    static constexpr int PITCH = M * M + (M == 8 ? 8 : M == 4 ? 4 : 0);           // values of a tile: 16 tiles' rows in different banks
+    static constexpr int BYTES = CHANNELS * TILES * PITCH * 2;
+    static constexpr int ALIGN = M == 8 ? 16 : M == 4 ? 8 : 4;                    // bytes, of a row
+    static constexpr int SLOTS = M > 4 ? 8 : M;                                   // lanes per tile
+    static_assert(M == 2 || M == 4 || M == 6 || M == 8, "tile size");
+
+    __device__ __forceinline__ static void put(f16 *block, int channel, int tile, int row, const f16 (&v)[M])
+    {
+        f16 *to = block + (channel * TILES + tile) * PITCH + row * M;
+        __builtin_memcpy(__builtin_assume_aligned(to, ALIGN), v, M * 2);
+    }
+
+    // By 256 threads, after a barrier
+    __device__ __forceinline__ static void store(const f16 *block, f16 *y, int k0, int K, int t0, int Ttot, int tiles_h, int tiles_w, int H, int W)
+    {
+        const int tid = (int)threadIdx.x, row = tid % SLOTS, tile = tid / SLOTS % TILES;
+        const int t = t0 + tile, trow = t / tiles_w, tc = t - trow * tiles_w, img = trow / tiles_h, tr = trow - img * tiles_h;
+        const int h = tr * M + row, w0 = tc * M, left = W - w0;
+        if (t >= Ttot || row >= M || h >= H) return;
+        constexpr int STEP = 256 / (SLOTS * TILES);                               // channels at a time
+#pragma unroll 4
+        for (int c = tid / (SLOTS * TILES); c < CHANNELS; c += STEP) {
+            if (k0 + c >= K) break;
+            f16 v[M];
+            __builtin_memcpy(v, __builtin_assume_aligned(block + (c * TILES + tile) * PITCH + row * M, ALIGN), M * 2);
+            f16 *to = y + (((long long)img * K + k0 + c) * H + h) * W + w0;
+            if (left >= M) {
+                store_row<f16, M>(to, v);
+            } else {
+#pragma unroll
+                for (int q = 0; q < M - 1; ++q)
+                    if (q < left) to[q] = v[q];
+            }
+        }
+    }
+};
+
 template <int N, int R>
 static void fill_out_coef(const nova_transforms *t, OutCoef<N, R> &k)
 {
