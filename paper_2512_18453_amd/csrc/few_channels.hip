@@ -98,6 +98,9 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
                     int Kp, int Ttot, int k_groups, int relu, int narrow, OutCoef<N, R> coef)
 {
     constexpr int M = N - R + 1, MH = M / 2, N2 = N * N, THREADS = 256;
+    // Streaming hint for the rows, but not for those of 12 bytes: 3 -> 64 @224x224 batch 32 F(6,3) 66 us without, 72 as 8 + 4 bytes
+    // with it, 128 with it on 12 (the fused 64-channel kernel, whose y is the smaller part of its traffic: 335, 349, 303)
+    constexpr bool kHint = M != 6;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     half4 *Vs = reinterpret_cast<half4 *>(lds_raw), *Us = Vs + N2 * kFewTiles;        // [position][16 tiles], [position][32 channels]
 
@@ -173,7 +176,7 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                for (int pi = 0; pi < MH; ++pi) store_row<f16, M, true>(plane + ((long long)e * H + 2 * pi + half) * W, out[e][pi]);
+                for (int pi = 0; pi < MH; ++pi) store_row<f16, M, kHint>(plane + ((long long)e * H + 2 * pi + half) * W, out[e][pi]);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -183,7 +186,7 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
                     if (!active || k0 + e >= K || h0 + p >= H) continue;
                     f16 *row = plane + ((long long)e * H + p) * W;
                     if (w0 + M <= W) {
-                        store_row<f16, M, true>(row, out[e][pi]);
+                        store_row<f16, M, kHint>(row, out[e][pi]);
                     } else {
 #pragma unroll
                         for (int q = 0; q < M; ++q)

@@ -308,6 +308,7 @@ __device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
 {
     constexpr int WORDS = COUNT * (int)sizeof(T) / 4;
     typedef unsigned int piece4 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef unsigned int piece3 __attribute__((ext_vector_type(3), aligned(2)));
     typedef unsigned int piece2 __attribute__((ext_vector_type(2), aligned(2)));
     typedef unsigned int piece1 __attribute__((aligned(2)));
     if constexpr (COUNT * (int)sizeof(T) % 4 != 0) {
@@ -320,8 +321,9 @@ __device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
         constexpr int FOURS = WORDS / 4 * 4;
 #pragma unroll
         for (int e = 0; e < FOURS; e += 4) NOVA_STORE(piece4, at + 4 * e, (piece4{w[e], w[e + 1], w[e + 2], w[e + 3]}));
-        if constexpr (WORDS - FOURS >= 2) NOVA_STORE(piece2, at + 4 * FOURS, (piece2{w[FOURS], w[FOURS + 1]}));
-        if constexpr ((WORDS - FOURS) % 2 == 1) NOVA_STORE(piece1, at + 4 * (WORDS - 1), w[WORDS - 1]);
+        if constexpr (WORDS - FOURS == 3) NOVA_STORE(piece3, at + 4 * FOURS, (piece3{w[FOURS], w[FOURS + 1], w[FOURS + 2]}));
+        if constexpr (WORDS - FOURS == 2) NOVA_STORE(piece2, at + 4 * FOURS, (piece2{w[FOURS], w[FOURS + 1]}));
+        if constexpr (WORDS - FOURS == 1) NOVA_STORE(piece1, at + 4 * (WORDS - 1), w[WORDS - 1]);
     }
 }
 #undef NOVA_STORE
