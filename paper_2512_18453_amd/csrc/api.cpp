@@ -227,7 +227,8 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     const size_t x_bytes = (size_t)N * C * H * W * dtype_size(dtype);
     const size_t y_bytes = ((flags & NOVA_FLAG_POOL2) ? (size_t)N * K * (H / 2) * (W / 2) : (size_t)N * K * H * W) * dtype_size(dtype);
     if (!overlap(x, x_bytes, y, y_bytes) && !overlap(U, nova_filter_bytes(K, C, m, r, dtype), y, y_bytes)) {
-        const int tiles = layer_tiles(t, whole, dtype, v_bytes(whole, dtype) + second_part(whole, columns));
+        // (rows of M past the last tile are not written)
+        const int tiles = layer_tiles(t, whole, dtype, v_bytes(whole, dtype) + second_part(whole, columns) / whole.Tp * whole.T);
         if (tiles > 0) return hip_result(launch_layer(t, x, U, y, whole, dtype, flags, tiles, stream));
     }
 

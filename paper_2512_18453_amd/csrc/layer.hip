@@ -324,20 +324,22 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 }
 
 // Which layers run as one kernel, and with how many tiles per workgroup: the shape with the lowest estimate, if
-// that is well below the estimate for the separate kernels.  Estimates (us), fitted to 386 layers of 2 to 3500
-// tiles, 5 to 260 -> 5 to 512 channels, timed both ways on one MI355X (sd 5-16 %):
+// that is well below the estimate for the separate kernels.  Estimates (us):
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
 //   separate kernels  kStages + 0.3 per MB of what they write between them (+ 10 per GFLOP in binary32)
-// The margin is 0.92, and 0.8 from 30 us on, where the estimates are widest: of 235 other layers of 100 to 12000 tiles two are 4 %
-// or more slower than the separate kernels this way (with 0.92 throughout four), and all together 1.23 times faster.
+// Fitted to 386 layers of 2 to 3500 tiles, 5 to 260 -> 5 to 512 channels, n = 4 and n = 10 in binary32 again to 1200 layers of 1
+// to 900 tiles and up to 520 channels, all timed both ways on one MI355X (sd 5-9 %, n = 4 20-30 %).  The margin is 0.92, and 0.8
+// from 30 us on, where the estimates are widest.  Of those 1200 and 1400 layers drawn after the fit 1191 are taken, geometric mean 1.57
+// times as fast as the separate kernels; seven are slower by more than 2 %, two of them by more than 4 % (18 -> 128 5x5 @38x4
+// batch 7 F(6,5) binary32 20.5 / 16.9 us, 256 -> 256 @8x8 batch 2 F(2,3) 12.7 / 11.4).
 // us, separate / one kernel: 16 -> 16 @32x32 F(4,3) binary32 12.3 / 6.7; 40 -> 70 @45x61 batch 8 F(6,3) binary32 29.5 / 16.7; 48
 // -> 96 5x5 @35x35 batch 16 27.6 / 16.7; 64 -> 64 @56x56 batch 8 F(6,3) 17.4 / 14.0; 64 -> 128 @112x112 F(4,3) 18.7 / 10.4; not
 // taken: 256 -> 256 @56x56 F(4,3) 18.2 / 22, 512 -> 512 @28x28 17 / 38.
 struct LayerTimes { double turn[2], once[2], stages; };          // [8 tiles, 16 tiles]
 static const LayerTimes &layer_times(int n, bool half)
 {
-    static const LayerTimes kHalf[] = {{{0.7, 1.0}, {1.2, 1.9}, 11.1}, {{1.9, 2.3}, {3.1, 3.6}, 13.0}, {{3.6, 4.3}, {4.3, 6.1}, 15.8}, {{4.6, 0}, {5.4, 0}, 20.5}};
-    static const LayerTimes kFull[] = {{{0.3, 0.5}, {2.8, 3.0}, 11.3}, {{1.7, 1.7}, {2.0, 2.5}, 13.4}, {{3.2, 3.6}, {2.6, 2.6}, 15.6}, {{5.9, 0}, {5.0, 0}, 19.9}};
+    static const LayerTimes kHalf[] = {{{0.84, 0.98}, {1.5, 2.2}, 11.1}, {{1.9, 2.3}, {3.1, 3.6}, 13.0}, {{3.6, 4.3}, {4.3, 6.1}, 15.8}, {{4.6, 0}, {5.4, 0}, 20.5}};
+    static const LayerTimes kFull[] = {{{0.73, 0.79}, {1.15, 1.8}, 11.3}, {{1.7, 1.7}, {2.0, 2.5}, 13.4}, {{3.2, 3.6}, {2.6, 2.6}, 15.6}, {{6.1, 0}, {5.0, 0}, 19.9}};
     return (half ? kHalf : kFull)[n / 2 - 2];
 }
 

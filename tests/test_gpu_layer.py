@@ -110,6 +110,18 @@ def test_values_that_are_not_finite(bad, m, C, K):
             assert torch.equal(got.nan_to_num(nan=7.0), want.nan_to_num(nan=7.0)) and not torch.isfinite(got).all()
 
 
+@pytest.mark.parametrize("m,r,dtype,N,C,K,H,W", [(6, 5, torch.float16, 13, 97, 512, 4, 4), (2, 3, torch.float16, 5, 416, 320, 12, 12),
+                                                 (6, 5, torch.float32, 4, 36, 361, 6, 68), (2, 3, torch.float32, 33, 352, 128, 4, 4)])
+def test_faster_as_separate_kernels(m, r, dtype, N, C, K, H, W):
+    # few tiles in many rows of M that are never written, or many blocks of input channels: 1.2 to 1.3 times as long as one kernel
+    t = nova.nova_make_transforms(points_for(m, r), m, r)
+    x = torch.ones((N, C, H, W), device=DEV, dtype=dtype)
+    U = nova.nova_filter_transform(t, torch.ones((K, C, r, r), device=DEV, dtype=dtype) / C)
+    ws = workspace(t, x, K, 0)
+    nova.nova_winograd_conv2d(t, x, U, K, workspace=ws)
+    assert (ws != 0xFF).any()
+
+
 def pooled_as_stated(y):
     # the first of the largest in the order of the image: a zero keeps the sign that the first zero had
     a = y.float().cpu()
