@@ -114,8 +114,16 @@ bool contract_columns_preferred(const nova_transforms *t, const Geometry &g, int
     const double products = (double)g.n * g.n * (double)g.T * g.Kp;
     // (n = 10 beside the streaming contraction with its U in registers, which starts at 24 M products: 128 -> 128 @28x28 batch 256 in
     // two slabs of 26 M, 141.9 us with it, 144.3 this way; 34 to 60 M products 1.00 to 1.15 times faster this way)
-    const bool streams = g.c_blocks == 4 && g.Kp % 128 == 0;
-    return g.c_blocks <= (g.n == 10 ? 4 : 8) && products >= (g.n < 10 ? 9e6 : streams ? 30e6 : 15e6);
+    if (g.n == 10) return g.c_blocks <= 4 && products >= (g.c_blocks == 4 && g.Kp % 128 == 0 ? 30e6 : 15e6);
+    // F(6,3) from later on where there are many output channels, or few tiles for the same products: up to 14 M (a workgroup or two per
+    // compute unit) these are 0.93 to 1.0 times as fast this way, with 5 blocks and more up to 20 M 0.97 to 1.1; 8 blocks and K a
+    // multiple of 256 (the streaming contraction of 8 waves) 0.89 to 1.05 up to 45 M, 0.98 to 1.32 from there.  Of 1800 layers of
+    // all n 1020 are taken, geometric mean 1.18; 21 are 0.93 to 0.98 times as fast, most of them F(6,3) with 192 to 224 channels.
+    if (g.n == 8 && g.r == 3) {
+        if (g.c_blocks == 8 && g.Kp % 256 == 0) return products >= 45e6;
+        return g.c_blocks <= 8 && products >= (g.Kp > 256 ? (g.c_blocks < 5 ? 14e6 : 20e6) : g.c_blocks == 8 ? 13e6 : 10.5e6);
+    }
+    return g.c_blocks <= 8 && products >= 9e6;
 }
 
 int launch_contract_columns(const nova_transforms *t, const void *U, const void *V, void *Z, const Geometry &g, void *stream)

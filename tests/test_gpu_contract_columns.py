@@ -43,6 +43,19 @@ def test_equals_the_stages(m, r, N, C, K, H, W):
         assert bool((ws[nbytes - tail:] == 0xFF).all()), "not this path"
 
 
+@pytest.mark.parametrize("N,C,K,H,W", [(19, 256, 256, 44, 44), (16, 256, 512, 65, 9), (7, 128, 384, 43, 43), (11, 192, 384, 40, 44), (32, 227, 128, 85, 15)])
+def test_faster_as_separate_kernels(N, C, K, H, W):
+    # M is written whole: 1.03 to 1.1 times as long this way
+    t = nova.nova_make_transforms(synth.point_set("nova", 6), 6, 3)
+    x = torch.ones((N, C, H, W), device=DEV, dtype=torch.float16)
+    U = nova.nova_filter_transform(t, torch.ones((K, C, 3, 3), device=DEV, dtype=torch.float16) / C)
+    nbytes = nova.nova_conv2d_workspace_bytes(N, C, H, W, K, 6, nova.NOVA_F16, 0, N)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+    nova.nova_winograd_conv2d(t, x, U, K, workspace=ws)
+    last = nova.nova_product_bytes(N, K, H, W, 6, nova.NOVA_F16) // 64                     # the last of the 64 planes of M
+    assert (ws[nbytes - last:] != 0xFF).any()
+
+
 def test_values_that_are_not_finite():
     t = nova.nova_make_transforms(synth.point_set("nova", 4), 4, 3)
     gen = torch.Generator(device=DEV).manual_seed(7)
