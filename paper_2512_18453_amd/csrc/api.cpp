@@ -217,6 +217,11 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     };
     if (slab_bytes(1, false) > workspace_bytes) return NOVA_ENOSPC;
     int imgs = images_per_slab(true);
+    // (With many input channels and few output channels V is most of a slab; where x and V together do not fit the last-level
+    // cache, V would come back from memory: no larger slabs than the separate kernels' then.  221 -> 62 @42x169 batch 25 F(4,3), 78 MB of x
+    // and 191 MB of V: 142 us in one slab, 126 in two; separate kernels, in two, 131.)
+    const Geometry filled = make_geometry(imgs, C, H, W, K, m, r);
+    if ((size_t)imgs * C * H * W * dtype_size(dtype) + first_part_bytes(filled, dtype) > kDefaultSlabBytes) imgs = images_per_slab(false);
     const bool columns = !fused && contract_columns_preferred(t, make_geometry(imgs, C, H, W, K, m, r), dtype, flags);
     if (!columns) imgs = images_per_slab(false);
     const size_t v_part = align256(first_part_bytes(make_geometry(imgs, C, H, W, K, m, r), dtype));
