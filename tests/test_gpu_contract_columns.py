@@ -68,6 +68,18 @@ def test_slabs_no_larger_than_the_cache():
     assert (ws[ws.numel() // 3 * 2:] == 0xFF).all()
 
 
+def test_slabs_no_larger_than_the_cache():
+    # 25 images, 79 MB of x and 191 MB of V, fit the workspace with m of n planes, 22 with M whole: two slabs of 13
+    t = nova.nova_make_transforms(synth.point_set("nova", 4), 4, 3)
+    N, C, K, H, W = 25, 224, 60, 42, 169
+    x = torch.ones((N, C, H, W), device=DEV, dtype=torch.float16)
+    U = nova.nova_filter_transform(t, torch.ones((K, C, 3, 3), device=DEV, dtype=torch.float16) / C)
+    ws = torch.full((nova.nova_conv2d_workspace_bytes(N, C, H, W, K, 4, nova.NOVA_F16),), 0xFF, dtype=torch.uint8, device=DEV)
+    assert ws.numel() > nova.nova_input_bytes(N, C, H, W, 4, nova.NOVA_F16) + nova.nova_product_bytes(N, K, H, W, 4, nova.NOVA_F16) // 6 * 4
+    nova.nova_winograd_conv2d(t, x, U, K, workspace=ws)
+    assert (ws[ws.numel() // 3 * 2:] == 0xFF).all()
+
+
 def test_values_that_are_not_finite():
     t = nova.nova_make_transforms(synth.point_set("nova", 4), 4, 3)
     gen = torch.Generator(device=DEV).manual_seed(7)

@@ -64,3 +64,19 @@ def test_values_that_are_not_finite(bad):
         want = torch.clamp(clean, min=0) if flags else clean
         assert torch.equal(got[same], want[same])
         assert got.isnan().any() and (flags or not torch.isfinite(got[~same]).any())
+
+
+@pytest.mark.parametrize("scale_x,scale_w", [(2.0 ** -24, 1.0), (1.0, 2.0 ** -24)])
+@pytest.mark.parametrize("C,W", [(3, 25), (4, 70)])
+def test_subnormal_operands(scale_x, scale_w, C, W):
+    # F(2,3) with points 0, 1, -1 and filters in multiples of 4: V, U, every product, partial sum and result is a whole
+    # multiple of 2^-24 below 2^11 of them, exact in binary16 (V or U subnormal), so nothing may be flushed to zero
+    t = nova.nova_make_transforms(synth.point_set("standard", 2), 2, 3)
+    gen = torch.Generator(device=DEV).manual_seed(C)
+    x = torch.randint(-13, 14, (2, C, 21, W), device=DEV, generator=gen).double()
+    w = 4.0 * torch.randint(-1, 2, (35, C, 3, 3), device=DEV, generator=gen).double()
+    want = torch.nn.functional.conv2d(x.cpu(), w.cpu(), padding=1) * (scale_x * scale_w)
+    U = nova.nova_filter_transform(t, (w * scale_w).half())
+    y = nova.nova_winograd_conv2d(t, (x * scale_x).half(), U, 35)
+    torch.cuda.synchronize()
+    assert want.abs().max() < 2.0 ** -13 and (want != 0).any() and torch.equal(y.double().cpu(), want)

@@ -1,6 +1,6 @@
 """The whole layer in one kernel (calls with little work) against the separate stage calls: the same operations in
-the same order, so the results are equal bit for bit.  The sizes sit at the edges of its workgroups: 8 or 16 tiles,
-16 or 32 output channels, blocks of 32 (binary16) or 16 (binary32) input channels."""
+the same order, so the results are equal bit for bit.  The sizes sit at the edges of its workgroups: 8 tiles (CASES, nearly all)
+or 16 (CASES_OF_16_TILES), 16 or 32 output channels, blocks of 32 (binary16) or 16 (binary32) input channels."""
 import pytest
 import torch
 
@@ -18,6 +18,20 @@ CASES = [
     (8, 3, 1, 11, 82, 25, 12), (8, 3, 2, 64, 32, 24, 40), (8, 3, 9, 48, 15, 8, 8), (8, 3, 1, 7, 33, 3, 3),
     (2, 5, 2, 20, 40, 17, 18), (4, 5, 4, 48, 96, 35, 35), (4, 5, 1, 9, 16, 4, 5), (6, 5, 3, 28, 42, 34, 24), (6, 5, 1, 33, 17, 13, 7),
 ]
+
+F16, F32 = torch.float16, torch.float32
+CASES_OF_16_TILES = [
+    # as the rule has it on 256 compute units: 16 q + 1 and 16 q + 15 tiles of every kernel, the listed 5 x 5 workload, and
+    # 64 input channels of F(6,3) in binary16, whose outputs are transformed rows first
+    (2, 3, 19, 6, 33, 49, 5, F16), (2, 3, 11, 5, 16, 53, 14, F16), (2, 3, 11, 8, 33, 5, 65, F32), (2, 3, 7, 17, 33, 13, 30, F32),
+    (4, 3, 17, 12, 33, 19, 51, F16), (4, 3, 11, 5, 16, 49, 68, F16), (4, 3, 17, 5, 17, 19, 52, F32), (4, 3, 9, 10, 96, 52, 10, F32),
+    (2, 5, 11, 12, 33, 66, 5, F16), (2, 5, 7, 12, 16, 21, 53, F16), (2, 5, 7, 9, 33, 29, 18, F32), (2, 5, 9, 9, 17, 34, 13, F32),
+    (6, 3, 11, 6, 33, 65, 51, F16), (6, 3, 17, 18, 48, 53, 37, F16), (6, 3, 17, 5, 64, 66, 14, F32), (6, 3, 13, 14, 96, 13, 49, F32),
+    (4, 5, 5, 11, 33, 68, 49, F16), (4, 5, 19, 5, 17, 34, 51, F16), (4, 5, 17, 5, 64, 42, 9, F32), (4, 5, 15, 8, 33, 25, 25, F32),
+    (4, 5, 16, 48, 96, 35, 35, F16), (6, 3, 17, 64, 64, 50, 49, F16), (6, 3, 15, 64, 64, 51, 51, F16),
+]
+# 64 input channels in binary16, 8 tiles, outputs transformed rows first
+ROWS_FIRST = [(6, 3, 3, 64, 32, 14, 18, F16), (6, 3, 8, 64, 64, 56, 56, F16), (8, 3, 2, 64, 32, 24, 40, F16), (8, 3, 1, 64, 64, 40, 33, F16)]
 
 
 def points_for(m, r):
@@ -42,9 +56,7 @@ def by_stages(t, x, U, K, flags):
     return nova.nova_output_transform(t, M, N, K, H, W, x.dtype, flags)
 
 
-@pytest.mark.parametrize("m,r,N,C,K,H,W", CASES)
-@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
-def test_equals_the_stages(m, r, N, C, K, H, W, dtype):
+def equals_the_stages(m, r, N, C, K, H, W, dtype, one_kernel):
     t = nova.nova_make_transforms(points_for(m, r), m, r)
     gen = torch.Generator(device=DEV).manual_seed(m * 1000 + C)
     x = torch.randn((N, C, H, W), device=DEV, generator=gen).to(dtype)
@@ -60,10 +72,22 @@ def test_equals_the_stages(m, r, N, C, K, H, W, dtype):
         got = guard[32:32 + want.numel()].view(want.shape)
         nova.nova_winograd_conv2d(t, x, U, K, y=got, flags=flags, workspace=ws)
         torch.cuda.synchronize()
-        if C <= (40 if dtype == torch.float16 else 28):       # certainly little work (with more channels the rule may go either way)
+        if one_kernel:
             assert bool((ws == 0xFF).all()), "not the one-kernel path"
         assert torch.isfinite(want).all() and torch.equal(got, want), (dtype, flags)
         assert guard[:32].isnan().all() and guard[-32:].isnan().all()
+
+
+@pytest.mark.parametrize("m,r,N,C,K,H,W", CASES)
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_equals_the_stages(m, r, N, C, K, H, W, dtype):
+    # C: certainly little work (with more channels the rule may go either way)
+    equals_the_stages(m, r, N, C, K, H, W, dtype, C <= (40 if dtype == torch.float16 else 28))
+
+
+@pytest.mark.parametrize("m,r,N,C,K,H,W,dtype", CASES_OF_16_TILES + ROWS_FIRST)
+def test_equals_the_stages_in_one_kernel(m, r, N, C, K, H, W, dtype):
+    equals_the_stages(m, r, N, C, K, H, W, dtype, True)
 
 
 def test_unaligned_operands_and_results():

@@ -2,8 +2,9 @@
 array inside the library's device image) against nova_winograd_conv2d on the same inputs.
 
 Both run the same kernels on slabs of whole images, and a tile's result does not depend on which
-slab it is in, so the two outputs are compared bit for bit.  Two calls in a row share the array:
-the second one is smaller and runs on whatever the first left behind.
+slab it is in, so the two outputs are compared bit for bit.  Calls in a row share the array:
+the later ones are smaller and run on whatever the ones before left behind (the second needs no workspace: all of it
+is one kernel).
 """
 import sys
 
@@ -50,6 +51,17 @@ def test_static_workspace_call_equals_workspace_call_twice_in_a_row():
     x, w = synth.make_layer(N, C, K, H, W, seed=92, dtype="f16", x_dist="normal")
     got, want = both_ways(t, x, w, K, nova.NOVA_FLAG_RELU)
     assert np.isfinite(want).all() and np.array_equal(got, want)
+    # another that is too much work for that: its kernels write their workspace
+    N, C, K, H, W = 3, 250, 130, 17, 23
+    say(f"[case] static workspace, ragged call of separate kernels N={N} C={C} K={K} {H}x{W} F({m},3) fp16 relu")
+    x, w = synth.make_layer(N, C, K, H, W, seed=94, dtype="f16", x_dist="normal")
+    got, want = both_ways(t, x, w, K, nova.NOVA_FLAG_RELU)
+    assert np.isfinite(want).all() and np.array_equal(got, want)
+    dirty = torch.full((nova.nova_conv2d_workspace_bytes(N, C, H, W, K, m, nova.NOVA_F16, nova.NOVA_FLAG_RELU),), 0xFF, dtype=torch.uint8, device=DEV)
+    xd, U = torch.from_numpy(x).to(DEV), nova.nova_filter_transform(t, torch.from_numpy(w).to(DEV))
+    again = nova.nova_winograd_conv2d(t, xd, U, K, flags=nova.NOVA_FLAG_RELU, workspace=dirty)
+    torch.cuda.synchronize()
+    assert np.array_equal(again.cpu().numpy(), want) and bool((dirty != 0xFF).any())
     # third: the few-channel path (no M) in binary32, F(4,3)
     t4 = nova.nova_make_transforms(synth.point_set("nova", 4), 4, 3)
     N, C, K, H, W = 2, 3, 20, 30, 26
