@@ -222,21 +222,22 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     const bool aligned = ((uintptr_t)y % 16) == 0;
     sh.groups = ceil_div(g.tiles_w, twb_max);
     int twb = ceil_div(g.tiles_w, sh.groups);           // tiles of one tile row per group
-    if ((sizeof(T) == 2 || M >= 4) && sh.groups > 1 && g.W % PE == 0 && aligned && !(flags & NOVA_FLAG_POOL2)) {
+    if (CF == 0 && (sizeof(T) == 2 || M >= 4) && sh.groups > 1 && g.W % PE == 0 && aligned && !(flags & NOVA_FLAG_POOL2)) {
         // Several groups per row: their width decides how the rows leave -- in 16-byte pieces if it is a whole number
         // of them, and without sharing a 64-byte sector between two workgroups if it is a whole number of
         // those; last groups narrower than the others leave lanes idle.  Taken: the evenly cut width or a
         // vectorisable one, by the lowest estimate of slots launched * (1 + 2 / width) * 1.2 for shared sectors
-        // * 1.3 for element stores (1.5 where no M is read and the stores weigh more).  us per launch, even
+        // * 1.3 for element stores.  us per launch, even
         // cut / this rule: 64 ch @224x224 batch 4 F(6,3) 30.9 / 22.6, F(4,3) 34.7 / 27.4, 128 ch @96x96 batch 8 F(4,3)
-        // 25.2 / 20.7; whole call 3 -> 64 @224x224 batch 32 F(8,3) 172 / 138.  (Pooled rows are a quarter of the
-        // bytes: 20.7 / 24.3, hence not for them.)
+        // 25.2 / 20.7.  (Pooled rows are a quarter of the bytes: 20.7 / 24.3, hence not for them.  Nor where the products are formed
+        // here, 3 -> 64 @224x224 batch 32, whole call: binary32 F(8,3) 194 / 218, F(4,3) 145 / 148, binary16 with points in
+        // another order F(8,3) 172 / 172, F(6,3) 127 / 128.)
         double best = 0.0;
         const int even = twb;
         for (int c = 1; c <= twb_max; ++c) {
             const bool pieces = (c * M) % PE == 0;
             if (!pieces && c != even) continue;
-            const double stores = !pieces ? (CF > 0 ? 1.5 : 1.3) : (c * M * (int)sizeof(T)) % 64 == 0 ? 1.0 : 1.2;
+            const double stores = !pieces ? 1.3 : (c * M * (int)sizeof(T)) % 64 == 0 ? 1.0 : 1.2;
             const double cost = (double)ceil_div(g.tiles_w, c) * c * (1.0 + 2.0 / c) * stores;
             if (best == 0.0 || cost < best) { best = cost; twb = c; }
         }
