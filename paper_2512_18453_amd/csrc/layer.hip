@@ -11,11 +11,13 @@
 // LDS to the threads that transform it, one (tile, channel) pair each, and their m x m results leave as rows of m
 // elements, neighbouring tiles in neighbouring lanes.
 // Every value is formed by the same operations in the same order as by the kernels for larger layers, so the
-// results are the same bits: V by the contract of the input transform; M in ascending channels (the matrix
+// results are the same bits (the sign of a pooled zero among them, larger_of): V by the contract of the input transform; M in ascending channels (the matrix
 // unit's sums do not depend on the shape of the instruction; binary32: two chains, in the order contract.hip gives);
 // the output transform columns first, or, for the layers that
 // otherwise run contraction and output transform as one kernel (64 input channels, ROWS_FIRST), in its order.
 // The windows are transformed again for every KB output channels, which is why large layers do not come here.
+#include <algorithm>
+
 #include "input_common.hpp"
 #include "output_common.hpp"
 
@@ -179,7 +181,9 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
     // threads that share a pair's output rows: as many as there are, at most one per two rows
     constexpr int SPLIT = ROWS_FIRST || THREADS < 2 * KB * TB ? 1 : THREADS / (KB * TB) < M / 2 ? THREADS / (KB * TB) : M / 2;
     constexpr int V_POS = TB * 64;                          // bytes of V of one position
-    // filters are asked for before the transform where the registers hold both
+    // filters are asked for before the transform where the registers hold both.  Scratch per lane: 44 bytes (10 registers) for n = 8 with
+    // 16 tiles in binary16, whose 1024 threads have 128 registers each; n = 10, 168 registers: 20 bytes (4) in binary16, 108 (30, r = 3)
+    // and 72 (17, r = 5) in binary32; none elsewhere
     constexpr bool EARLY = N < 8 || (N == 8 && (TB == 8 || sizeof(T) == 4));
     static_assert(B::GP == 16 && N * N % WAVES == 0 && KB % 16 == 0 && (TB == 8 || TB == 16), "workgroup shape");
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -324,22 +328,23 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 }
 
 // Which layers run as one kernel, and with how many tiles per workgroup: the shape with the lowest estimate, if
-// that is well below the estimate for the separate kernels.  Estimates (us):
+// that is below 0.94 of the estimate for the separate kernels (0.85 from 30 us on, where the estimates are widest).  Estimates (us):
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
-//   separate kernels  kStages + 0.3 per MB of what they write between them (+ 10 per GFLOP in binary32)
-// Fitted to 386 layers of 2 to 3500 tiles, 5 to 260 -> 5 to 512 channels, n = 4 and n = 10 in binary32 again to 1200 layers of 1
-// to 900 tiles and up to 520 channels, all timed both ways on one MI355X (sd 5-9 %, n = 4 20-30 %).  The margin is 0.92, and 0.8
-// from 30 us on, where the estimates are widest.  Of those 1200 and 1400 layers drawn after the fit 1191 are taken, geometric mean 1.57
-// times as fast as the separate kernels; seven are slower by more than 2 %, two of them by more than 4 % (18 -> 128 5x5 @38x4
-// batch 7 F(6,5) binary32 20.5 / 16.9 us, 256 -> 256 @8x8 batch 2 F(2,3) 12.7 / 11.4).
+//                     (n = 4, where several workgroups share a compute unit: at least 3 + turns * 1.3, binary32 1.0, the serial chain)
+//   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
+// Fitted to 2600 layers of 1 to 12000 tiles, 5 to 520 -> 1 to 520 channels, timed both ways on one MI355X (sd 6-13 %, one kernel n = 4
+// 20-30 %): 1295 are taken, geometric mean 1.54 times as fast as the separate kernels; nine are slower by more than 2 %, two of
+// them by more than 10 % (18 -> 128 5x5 @38x4 batch 7 F(6,5) binary32 20.5 / 16.9 us, 300 -> 33 @7x109 batch 32 F(6,3) binary32 78.7 / 70.9).
 // us, separate / one kernel: 16 -> 16 @32x32 F(4,3) binary32 12.3 / 6.7; 40 -> 70 @45x61 batch 8 F(6,3) binary32 29.5 / 16.7; 48
 // -> 96 5x5 @35x35 batch 16 27.6 / 16.7; 64 -> 64 @56x56 batch 8 F(6,3) 17.4 / 14.0; 64 -> 128 @112x112 F(4,3) 18.7 / 10.4; not
 // taken: 256 -> 256 @56x56 F(4,3) 18.2 / 22, 512 -> 512 @28x28 17 / 38.
-struct LayerTimes { double turn[2], once[2], stages; };          // [8 tiles, 16 tiles]
+struct LayerTimes { double turn[2], once[2], stages, per_mb; };          // [8 tiles, 16 tiles]
 static const LayerTimes &layer_times(int n, bool half)
 {
-    static const LayerTimes kHalf[] = {{{0.84, 0.98}, {1.5, 2.2}, 11.1}, {{1.9, 2.3}, {3.1, 3.6}, 13.0}, {{3.6, 4.3}, {4.3, 6.1}, 15.8}, {{4.6, 0}, {5.4, 0}, 20.5}};
-    static const LayerTimes kFull[] = {{{0.73, 0.79}, {1.15, 1.8}, 11.3}, {{1.7, 1.7}, {2.0, 2.5}, 13.4}, {{3.2, 3.6}, {2.6, 2.6}, 15.6}, {{6.1, 0}, {5.0, 0}, 19.9}};
+    static const LayerTimes kHalf[] = {{{0.78, 0.94}, {1.45, 2.2}, 12.4, 0.40}, {{1.85, 2.15}, {3.6, 3.75}, 13.6, 0.40},
+                                       {{3.3, 4.95}, {4.9, 5.4}, 15.6, 0.43}, {{4.55, 0}, {5.9, 0}, 20.3, 0.38}};
+    static const LayerTimes kFull[] = {{{0.74, 0.86}, {1.06, 1.6}, 12.5, 0.37}, {{1.7, 1.8}, {2.6, 2.9}, 14.2, 0.35},
+                                       {{3.3, 3.6}, {3.2, 3.5}, 15.9, 0.33}, {{6.1, 0}, {5.1, 0}, 19.4, 0.35}};
     return (half ? kHalf : kFull)[n / 2 - 2];
 }
 
@@ -352,14 +357,15 @@ int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t d
     const bool half = dtype == NOVA_F16;
     const LayerTimes &lt = layer_times(g.n, half);
     const int turns = ceil_div(g.C, half ? 32 : 16), k_groups = ceil_div(g.K, half && g.n < 10 ? 32 : 16);
-    double best = lt.stages + 0.3e-6 * (double)domain_bytes;
-    if (!half) best += 10e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
-    best *= best < 30.0 ? 0.92 : 0.8;
+    double best = lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes;
+    if (!half) best += 11e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
+    best *= best < 30.0 ? 0.94 : 0.85;
     int tiles = 0;
     for (int i = 0; i < (g.n < 10 ? 2 : 1); ++i) {
         const long long groups = (g.T + 8 * (i + 1) - 1) / (8 * (i + 1)) * k_groups;
         const long long rounds = (groups + device_cu_count() - 1) / device_cu_count();
-        const double time = 2.0 + (double)rounds * (turns * lt.turn[i] + lt.once[i]);
+        double time = 2.0 + (double)rounds * (turns * lt.turn[i] + lt.once[i]);
+        if (g.n == 4) time = std::max(time, 3.0 + turns * (half ? 1.3 : 1.0));
         if (time < best) { best = time; tiles = 8 * (i + 1); }
     }
     return tiles;
