@@ -222,8 +222,10 @@ int nova_filter_transform(const nova_transforms *t, const void *w, int K, int C,
 /*
  * Workspace for nova_winograd_conv2d.  The call processes the batch in slabs of whole images so
  * that V and M of a slab stay cache resident; the slab size follows from the workspace it is
- * given (as many slabs as the largest size that fits would need, evened out: 16 + 16 images, not 20 + 12).  images_per_slab = 0 asks for the library's default (as many images as fit 256 MiB of
- * V and M, at least one), N for the whole batch in one pass.  Returns 0 for invalid arguments.
+ * given (as many slabs as the largest size that fits would need, evened out: 16 + 16 images, not 20 + 12).  images_per_slab = 0
+ * asks for the library's default (as many images as fit 256 MiB of V and M, at least one), N for the whole batch in one pass.
+ * That many images fit; a call may put more of them into a slab where it keeps less than M (below, nova_conv2d_path), and
+ * a call that runs as one kernel neither reads nor writes the workspace.  Returns 0 for invalid arguments.
  * With C <= 4 (the first layer of an image network) the call keeps no M: the output transform forms
  * the products itself, and the workspace holds V in a compact 4-channel layout and a packed copy of the
  * filters' first four channels.
@@ -338,8 +340,10 @@ int nova_winograd_conv2d_int8(const nova_transforms *t, const void *x, const voi
  * NOVA_PATH_STAGES (input transform, contraction, output transform), NOVA_PATH_FEW_CHANNELS (at most 4
  * input channels: compact V, the products formed inside the output transform) or NOVA_PATH_FUSED_OUTPUT
  * (input transform, then the kernel above: taken wherever it is supported).  Negative: an error code.
- * (A call with little work runs the whole layer as one kernel instead, with the same results bit for bit, and
- * then leaves its workspace as it was.)
+ * The shape decides that much; the batch and the workspace decide two variants of these, with the same results bit for
+ * bit.  A call with little work runs the whole layer as one kernel and leaves its workspace as it was (with more than 4 input
+ * channels).  NOVA_PATH_STAGES in binary16 with many products per slab: the contraction keeps, in the place of M, m of every n
+ * of its planes with the columns of the output transform done, so that more images fit a slab.
  * Host only.
  */
 enum { NOVA_PATH_STAGES = 0, NOVA_PATH_FEW_CHANNELS = 1, NOVA_PATH_FUSED_OUTPUT = 2 };

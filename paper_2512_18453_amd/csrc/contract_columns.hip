@@ -7,7 +7,7 @@
 // one 1D transform per row.  Products and sums are those of the separate kernels in the same order, so the results
 // are the same bits.
 //
-// The channel loop is the tiled contraction's (contract_loop.hpp), here without a break over the n positions.  A lane holds one
+// The channel loop (contract_loop.hpp) runs without a break over the n positions.  A lane holds one
 // channel of a block and 16 tiles, so a store covers two whole 128-byte rows of Z.
 #include "contract_loop.hpp"
 #include "output_common.hpp"
@@ -92,8 +92,10 @@ template <int N, int R>
 static int launch_columns_n(const nova_transforms *t, const void *U, const void *V, void *Z, const Geometry &g, hipStream_t s)
 {
     // 64 x 64 by 4 waves, a ring of 4: us for the whole call, ring of 3 / 4 / 5 and 128 x 64 by 8 waves, 128 -> 128 @112x112 batch 32
-    // F(6,3): 233.7 / 232.3 / 231.6 / 238.8, 256 -> 256 @56x56 batch 32 F(8,3): 133 / 128 / 126 / 145.  (Two channel blocks per stage
-    // with the next fragments read ahead, 64 KB of LDS: 241 and 130 -- two workgroups per compute unit instead of three or four.)
+    // F(6,3): 233.7 / 232.3 / 231.6 / 238.8, 256 -> 256 @56x56 batch 32 F(8,3): 133 / 128 / 126 / 145.  (Rings of
+    // 4 and 5 differ by less than the runs do; with 5, 40 KB, n = 4 would lose the fifth workgroup per compute unit that its 89
+    // registers allow.  Two channel blocks per stage with the next fragments read ahead, 64 KB of LDS: 241 and 130 -- two workgroups
+    // per compute unit instead of three or four.)
     // One block of output channels: 128 x 32, none of it padding.
     if (g.Kp == 32) return launch_columns<N, R, 128, 32, 4, 1, 4, 2>(t, U, V, Z, g, s);
     return launch_columns<N, R, 64, 64, 2, 2, 4, 2>(t, U, V, Z, g, s);

@@ -1,5 +1,6 @@
-// The channel loop of the binary16 contraction kernels that work on tiles of BM rows of V (winograd tiles) by BN rows of U
-// (output channels), on v_mfma_f32_32x32x16_f16 with WM x WN waves.
+// The channel loop of contract_columns.hip: tiles of BM rows of V (winograd tiles) by BN rows of U (output channels), binary16, on
+// v_mfma_f32_32x32x16_f16 with WM x WN waves.  (The tiled contraction of contract.hip has a ring of its own; with this loop in its
+// place it was 0.8 to 1.0 times as fast: there workgroups per compute unit count for more than instructions per stage.)
 //
 // A stage is one block of 32 channels: (BM + BN) rows of 64 bytes each, XOR-swizzled by 16-byte slot (slot ^ (row / 4) % 4: the 16
 // rows that a 128-bit fragment read touches in one phase fall into different bank groups).  Stages arrive in a

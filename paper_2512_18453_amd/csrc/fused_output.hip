@@ -110,7 +110,7 @@ fused_contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ 
     // ---- direct loads.  A 64-byte row r of a chunk holds its four 16-byte pieces in the places
     // piece ^ ((r / 2) % 4); lane l of a load writes 16 bytes at its base + 16 l.
     // V: one load = one chunk (16 tiles of one channel block): lane l -> row l / 4, place l % 4; the
-    //    N * CB chunks of a row are dealt out to the waves, chunk = wave + 8 s.
+    //    N * CB chunks of a row are dealt out to the waves, chunk = wave + 4 s.
     // U: one load = one position (8 channels each of the two channel blocks): lane l -> block l / 32,
     //    row (l / 4) % 8, place l % 4.
     const int v_row_l = lane >> 2, v_piece_l = (lane & 3) ^ ((v_row_l >> 1) & 3);
