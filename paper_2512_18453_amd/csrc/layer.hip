@@ -331,6 +331,8 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 // that is below 0.94 of the estimate for the separate kernels (0.85 from 30 us on, where the estimates are widest).  Estimates (us):
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
 //                     (n = 4, where several workgroups share a compute unit: at least 3 + turns * 1.3, binary32 1.0, the serial chain)
+//                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows leave
+//                     element by element (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
 //   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
 // Fitted to 2600 layers of 1 to 12000 tiles, 5 to 520 -> 1 to 520 channels, timed both ways on one MI355X (sd 6-13 %, one kernel n = 4
 // 20-30 %): 1295 are taken, geometric mean 1.54 times as fast as the separate kernels; nine are slower by more than 2 %, two of
@@ -360,12 +362,14 @@ int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t d
     double best = lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes;
     if (!half) best += 11e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
     best *= best < 30.0 ? 0.94 : 0.85;
+    const double cut = std::max(0.0, (double)g.N * g.K * g.H * (g.W % g.m) - 2e6);
     int tiles = 0;
     for (int i = 0; i < (g.n < 10 ? 2 : 1); ++i) {
         const long long groups = (g.T + 8 * (i + 1) - 1) / (8 * (i + 1)) * k_groups;
         const long long rounds = (groups + device_cu_count() - 1) / device_cu_count();
         double time = 2.0 + (double)rounds * (turns * lt.turn[i] + lt.once[i]);
         if (g.n == 4) time = std::max(time, 3.0 + turns * (half ? 1.3 : 1.0));
+        time += 3e-6 * cut;
         if (time < best) { best = time; tiles = 8 * (i + 1); }
     }
     return tiles;
