@@ -99,7 +99,7 @@ few_channels_kernel(const f16 *__restrict__ Vc, const f16 *__restrict__ Uc, f16 
 {
     constexpr int M = N - R + 1, MH = M / 2, N2 = N * N, THREADS = 256;
     // Streaming hint for the rows, but not for those of 12 bytes: 3 -> 64 @224x224 batch 32 F(6,3) 66 us without, 72 as 8 + 4 bytes
-    // with it, 128 with it on 12 (the fused 64-channel kernel, whose y is the smaller part of its traffic: 335, 349, 303)
+    // with it, 128 with it on 12 (the fused 64-channel kernel decides by the size of V and y)
     constexpr bool kHint = M != 6;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     half4 *Vs = reinterpret_cast<half4 *>(lds_raw), *Us = Vs + N2 * kFewTiles;        // [position][16 tiles], [position][32 channels]

@@ -60,3 +60,19 @@ def test_first_layer(m, r, N, C, K, H, W):
         return nova.nova_winograd_conv2d(t, x, U, K, y=y, flags=flags)
     for flags in (0, nova.NOVA_FLAG_RELU, nova.NOVA_FLAG_M_F16):
         compare(call, x, K, flags)
+
+
+def test_rows_of_12_bytes_with_and_without_the_streaming_hint():
+    # F(6,3): V and y of the batch exceed the last-level cache (stores with the hint), those of one image do not
+    t = transforms(6, 3)
+    N, K, H, W = 62, 64, 112, 110
+    gen = torch.Generator(device=DEV).manual_seed(12)
+    x = torch.randn((N, 64, H, W), device=DEV, generator=gen).half()
+    U = nova.nova_filter_transform(t, (torch.randn((K, 64, 3, 3), device=DEV, generator=gen) * 0.06).half())
+    V = nova.nova_input_transform(t, x)
+    y = nova.nova_contract_output_fused(t, U, V, N, 64, H, W, K)
+    assert V.numel() * V.element_size() + y.numel() * 2 > 256 << 20
+    for i in (0, 30, 61):
+        one = nova.nova_contract_output_fused(t, U, nova.nova_input_transform(t, x[i:i + 1].contiguous()), 1, 64, H, W, K)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0].view(torch.int16), y[i].view(torch.int16))
