@@ -512,6 +512,7 @@ def test_fp16_error_per_tile_size_and_point_set():
 
 
 def test_slabs_and_workspace_errors():
+    # (this layer is one kernel whatever the slabs; the slab loop itself: test_gpu_workspace.py)
     say("[case] slab loop and workspace checks")
     points = synth.point_set("nova", 4)
     x, w = synth.make_layer(5, 32, 32, 12, 12, seed=2, dtype="f16")
@@ -927,6 +928,7 @@ def test_poisoned_workspace_and_output_do_not_leak(m, N, C, K, H, W, dtype):
     # The workspace (V, M, their padding rows and channels) and y are filled with NaN bit patterns
     # before the call: whatever the kernels read they must have written first, and cropped regions
     # (tile padding, channel padding, rows of M beyond T) must not reach y.  Two slab sizes.
+    # (The smallest of these layers run as one kernel, without the workspace; larger ones: test_gpu_workspace.py)
     say(f"[case] poisoned workspace F({m},3) {dtype} N={N} C={C} K={K} H={H} W={W}")
     points = synth.point_set("nova", m)
     t = nova.nova_make_transforms(points, m, 3)
@@ -951,6 +953,7 @@ def test_graph_capture_replays_match_eager():
     # the conv call enqueues kernels only (no allocation, no memset, no synchronisation), so it can be
     # captured in a graph; every replay, with eager work and synchronisation in between, must give
     # what the eager call gives for the input that is in the buffer at that time
+    # (one kernel; graphs of several: test_gpu_workspace.py)
     say("[case] graph capture of nova_winograd_conv2d")
     points = synth.point_set("nova", 6)
     t = nova.nova_make_transforms(points, 6, 3)
