@@ -204,6 +204,11 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
         const Geometry sg = make_geometry((int)count, C, H, W, K, m, r);
         return align256(first_part_bytes(sg, dtype)) + align256(second_part(sg, columns));
     };
+    // (as many slabs as that size needs, but of equal size: 20 + 12 images run slower than 16 + 16)
+    auto even_slabs = [&](long long count) {
+        const long long slab_count = (N + count - 1) / count;
+        return (int)((N + slab_count - 1) / slab_count);
+    };
     // largest slab (whole images) whose parts fit the workspace; slab_bytes grows with the count
     auto images_per_slab = [&](bool columns) {
         long long lo = 1, hi = N;                    // invariant: lo fits
@@ -211,9 +216,7 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
             const long long mid = (lo + hi + 1) / 2;
             if (slab_bytes(mid, columns) <= workspace_bytes) lo = mid; else hi = mid - 1;
         }
-        // (as many slabs as that size needs, but of equal size: 20 + 12 images run slower than 16 + 16)
-        const long long slab_count = (N + lo - 1) / lo;
-        return (int)((N + slab_count - 1) / slab_count);
+        return even_slabs(lo);
     };
     if (slab_bytes(1, false) > workspace_bytes) return NOVA_ENOSPC;
     int imgs = images_per_slab(true);
@@ -222,16 +225,32 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     // and 191 MB of V: 142 us in one slab, 126 in two; separate kernels, in two, 131.)
     const Geometry filled = make_geometry(imgs, C, H, W, K, m, r);
     if ((size_t)imgs * C * H * W * dtype_size(dtype) + first_part_bytes(filled, dtype) > kDefaultSlabBytes) imgs = images_per_slab(false);
-    const bool columns = !fused && contract_columns_preferred(t, make_geometry(imgs, C, H, W, K, m, r), dtype, flags);
-    if (!columns) imgs = images_per_slab(false);
+    // Contraction and output transform in one kernel: slabs of V alone, x and V of one within the last-level cache (128 -> 128 @112x112 batch
+    // 32 F(4,3), 103 MB of x and 231 of V: 237 us in one slab, 189 in two, 203 in three; 96 -> 128 @120x120 batch 64, 575 MB: 445, 417, 344, 371
+    // in one to four).  It reads U while it writes y.
+    const size_t x_bytes = (size_t)N * C * H * W * dtype_size(dtype);
+    const size_t y_bytes = ((flags & NOVA_FLAG_POOL2) ? (size_t)N * K * (H / 2) * (W / 2) : (size_t)N * K * H * W) * dtype_size(dtype);
+    const bool separate = !overlap(x, x_bytes, y, y_bytes) && !overlap(U, nova_filter_bytes(K, C, m, r, dtype), y, y_bytes);
+    bool contract_output = false;
+    if (!fused && !few_channels(C) && separate) {
+        long long lo = 1, hi = N;
+        while (lo < hi) {
+            const long long mid = (lo + hi + 1) / 2;
+            const size_t v = first_part_bytes(make_geometry((int)mid, C, H, W, K, m, r), dtype);
+            if (align256(v) <= workspace_bytes && x_bytes / N * mid + v <= kDefaultSlabBytes) lo = mid; else hi = mid - 1;
+        }
+        const int slab = even_slabs(lo);
+        contract_output = contract_output_preferred(t, make_geometry(slab, C, H, W, K, m, r), dtype, flags);
+        if (contract_output) imgs = slab;
+    }
+    const bool columns = !fused && !contract_output && contract_columns_preferred(t, make_geometry(imgs, C, H, W, K, m, r), dtype, flags);
+    if (!columns && !contract_output) imgs = images_per_slab(false);
     const size_t v_part = align256(first_part_bytes(make_geometry(imgs, C, H, W, K, m, r), dtype));
 
     // Little work: one kernel for the whole call, which leaves the workspace alone.  (It reads x and U while it writes
     // y; the separate kernels have read both before, so a call whose y overlaps one of them stays with those.)
     const Geometry whole = make_geometry(N, C, H, W, K, m, r);
-    const size_t x_bytes = (size_t)N * C * H * W * dtype_size(dtype);
-    const size_t y_bytes = ((flags & NOVA_FLAG_POOL2) ? (size_t)N * K * (H / 2) * (W / 2) : (size_t)N * K * H * W) * dtype_size(dtype);
-    if (!overlap(x, x_bytes, y, y_bytes) && !overlap(U, nova_filter_bytes(K, C, m, r, dtype), y, y_bytes)) {
+    if (separate && !contract_output) {
         // (rows of M past the last tile are not written)
         const int tiles = layer_tiles(t, whole, dtype, v_bytes(whole, dtype) + second_part(whole, columns) / whole.Tp * whole.T);
         if (tiles > 0) return hip_result(launch_layer(t, x, U, y, whole, dtype, flags, tiles, stream));
@@ -253,10 +272,14 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
             continue;
         }
         // (kDefaultSlabBytes: the size of the last-level cache)
-        const bool stream_x = !fused && (size_t)nb * C * H * W * es + v_bytes(g, dtype) + second_part(g, columns) > kDefaultSlabBytes;
+        const bool stream_x = !fused && !contract_output && (size_t)nb * C * H * W * es + v_bytes(g, dtype) + second_part(g, columns) > kDefaultSlabBytes;
         if (int err = launch_input_transform(t, xs, Vbuf, g, dtype, stream, stream_x)) return hip_result(err);
         if (fused) {
             if (int err = launch_fused_contract_output(t, U, Vbuf, ys, g, dtype, flags, stream)) return hip_result(err);
+            continue;
+        }
+        if (contract_output) {
+            if (int err = launch_contract_output(t, U, Vbuf, ys, g, flags, stream)) return hip_result(err);
             continue;
         }
         if (columns) {

@@ -119,7 +119,11 @@ int launch_output_transform(const nova_transforms *t, const void *M, void *y, co
 bool contract_columns_preferred(const nova_transforms *t, const Geometry &g, int dtype, int flags);
 int launch_contract_columns(const nova_transforms *t, const void *U, const void *V, void *Z, const Geometry &g, void *stream);
 int launch_output_rows(const nova_transforms *t, const void *Z, void *y, const Geometry &g, int flags, void *stream);
-// Contraction and output transform in one kernel (no M), for the shapes fused_contract_output_applies names;
+// Contraction and output transform in one kernel (no M), results as by the separate kernels; nova_winograd_conv2d takes it for the slabs
+// contract_output_preferred names.
+bool contract_output_preferred(const nova_transforms *t, const Geometry &g, int dtype, int flags);
+int launch_contract_output(const nova_transforms *t, const void *U, const void *V, void *y, const Geometry &g, int flags, void *stream);
+// The same for C = 64, for the shapes fused_contract_output_applies names;
 // nova_winograd_conv2d takes it for those fused_contract_output_preferred names
 bool fused_contract_output_applies(const nova_transforms *t, const Geometry &g, int dtype, int flags);
 bool fused_contract_output_preferred(const nova_transforms *t, const Geometry &g, int dtype, int flags);
