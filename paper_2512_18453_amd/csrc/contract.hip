@@ -471,16 +471,21 @@ static int launch_stream(const void *U, const void *V, void *Mo, const Geometry 
 // F(8,3) batch 256 30.7 against 36.0 and 41.8 for 128 x 64 and 64 x 64, batch 128 15.8 against 20.3 and 17.4), but not
 // for 64 output channels or fewer, where half of them would be padding (whole calls, 128 x 128 / the tile taken instead:
 // 256 -> 64 @56x56 F(6,3) batch 16 42.7 / 41.0, 512 -> 64 @60x60 F(8,3) batch 7 44.7 / 43.3; the contraction alone there
-// 12.9 / 11.5); 128 x 64 in other large layers (164 -> 33 @98x29 batch 43 F(4,3), 20 M, 38.4 against 41.4; 64 -> 64
+// 12.9 / 11.5), nor for 64 tiles or fewer, where half of the rows would be (512 -> 512 @7x7 F(8,3), 9 images 11.9 / 10.7, 40 13.2 / 12.8;
+// 241 -> 512 with 9 tiles 7.9 / 7.2); 128 x 64 in other large layers (164 -> 33 @98x29 batch 43 F(4,3), 20 M, 38.4 against 41.4; 64 -> 64
 // @112x112 batch 32 F(4,3), 58 M, 56.0 against 59.7).  One block of output channels: 128 x 32, none of it padding.
 template <typename MT>
 static int launch_c16_tiled(const void *U, const void *V, void *Mo, const Geometry &g, hipStream_t s)
 {
     if (g.Kp == 32) return launch_tile<128, 32, 4, 1, 3, f16, MT>(U, V, Mo, g, s);
     const double positions = (double)g.n * g.n;
-    if (g.c_blocks >= 8 && g.Kp > 64 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
+    if (g.c_blocks >= 8 && g.Kp > 64 && g.T > 64 && positions * ceil_div((int)g.T, 128) * ceil_div(g.Kp, 128) >= 400)
         return launch_tile<128, 128, 2, 4, 3, f16, MT>(U, V, Mo, g, s);
     if (positions * (double)g.T * g.Kp >= 16e6) return launch_tile<128, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);
+    // Long channel loops on a chip that few workgroups leave half empty: a ring of 5, more in flight per workgroup.  With U from
+    // memory (the 13-layer stack on one image, 118 MB of U, eight layers of 512 channels or to them) 209.7 us with 3, 203.5 with 4, 203.2 with 5; with U in
+    // the last-level cache the same (0.99 to 1.0 up to 384 workgroups, 0.96 from there on, 0.92 from 1000 on).
+    if (g.c_blocks >= 8 && positions * ceil_div((int)g.T, 64) * ceil_div(g.Kp, 64) <= 384) return launch_tile<64, 64, 2, 2, 5, f16, MT>(U, V, Mo, g, s);
     return launch_tile<64, 64, 2, 2, 3, f16, MT>(U, V, Mo, g, s);
 }
 
