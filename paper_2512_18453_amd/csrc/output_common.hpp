@@ -137,19 +137,88 @@ struct OutShape {
     int groups;       // tile groups per tile row
     int cols_pitch;   // LDS elements per output row of the group
     int k_pitch;      // LDS elements per channel
-    int pieces;       // flat stores: 16-byte pieces that can touch one channel's run of rows * W elements
-    unsigned piece_magic, w_magic, rows_magic;     // ceil(2^32 / d) for d = pieces, W, rows
+    int images;       // images per group (of which it takes all tiles then), in LDS one behind the other like further channels
+    int batch;        // images of the call
+    unsigned rows_magic, line_magic;               // ceil(2^32 / d) for d = rows, pieces of a row (0 for 1)
     int pool;         // 1: 2 x 2 max-pool while storing (H, W even)
     unsigned half_rows_magic;                      // ceil(2^32 / (rows / 2)), rows / 2 >= 2
 };
 
+// COUNT elements to an element-aligned address; NT: with the streaming cache hint
+#define NOVA_STORE(type, at, value)                                                              \
+    do {                                                                                         \
+        type *nova_at_ = reinterpret_cast<type *>(at);                                           \
+        if constexpr (NT) __builtin_nontemporal_store(value, nova_at_); else *nova_at_ = value;  \
+    } while (0)
+template <typename T, int COUNT, bool NT = false>
+__device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
+{
+    constexpr int WORDS = COUNT * (int)sizeof(T) / 4;
+    typedef unsigned int piece4 __attribute__((ext_vector_type(4), aligned(2)));
+    typedef unsigned int piece3 __attribute__((ext_vector_type(3), aligned(2)));
+    typedef unsigned int piece2 __attribute__((ext_vector_type(2), aligned(2)));
+    typedef unsigned int piece1 __attribute__((aligned(2)));
+    if constexpr (COUNT * (int)sizeof(T) % 4 != 0) {
+#pragma unroll
+        for (int e = 0; e < COUNT; ++e) dst[e] = v[e];
+    } else {
+        unsigned w[WORDS];
+        __builtin_memcpy(w, v, WORDS * 4);
+        unsigned char *at = reinterpret_cast<unsigned char *>(dst);
+        constexpr int FOURS = WORDS / 4 * 4;
+#pragma unroll
+        for (int e = 0; e < FOURS; e += 4) NOVA_STORE(piece4, at + 4 * e, (piece4{w[e], w[e + 1], w[e + 2], w[e + 3]}));
+        if constexpr (WORDS - FOURS == 3) NOVA_STORE(piece3, at + 4 * FOURS, (piece3{w[FOURS], w[FOURS + 1], w[FOURS + 2]}));
+        if constexpr (WORDS - FOURS == 2) NOVA_STORE(piece2, at + 4 * FOURS, (piece2{w[FOURS], w[FOURS + 1]}));
+        if constexpr (WORDS - FOURS == 1) NOVA_STORE(piece1, at + 4 * (WORDS - 1), w[WORDS - 1]);
+    }
+}
+#undef NOVA_STORE
+
+// The first `left` of COUNT elements (COUNT <= 8)
+template <typename T, int COUNT>
+__device__ __forceinline__ void store_row_part(T *dst, const T (&v)[COUNT], int left)
+{
+    if (left >= COUNT) {
+        store_row<T, COUNT>(dst, v);
+        return;
+    }
+    // pieces of 4, 2 and 1 elements; the values move up behind each
+    T rest[COUNT];
+#pragma unroll
+    for (int e = 0; e < COUNT; ++e) rest[e] = v[e];
+    if constexpr (COUNT > 4) {
+        if (left & 4) {
+            const T four[4] = {rest[0], rest[1], rest[2], rest[3]};
+            store_row<T, 4>(dst, four);
+            dst += 4;
+#pragma unroll
+            for (int e = 0; e + 4 < COUNT; ++e) rest[e] = rest[e + 4];
+        }
+    }
+    if constexpr (COUNT > 2) {
+        if (left & 2) {
+            const T two[2] = {rest[0], rest[1]};
+            store_row<T, 2>(dst, two);
+            dst += 2;
+            rest[0] = rest[2];
+        }
+    }
+    if (left & 1) dst[0] = rest[0];
+}
 // How the block leaves LDS.
-//   kStoreScalar  any W, any group: element by element, lanes along W
-//   kStoreVec     W (and the group width) a multiple of a 16-byte piece, y 16-byte aligned
-//   kStoreFlat    the group spans the image width (narrow images) and y is 16-byte aligned: the rows
-//                 of one channel are one contiguous run of y, written in aligned 16-byte pieces
-//                 whatever W is (element stores at its two ragged ends)
-enum { kStoreScalar = 0, kStoreVec = 1, kStoreFlat = 2 };
+//   kStoreRows    a tile's row of M elements per thread, the tiles of an image row in neighbouring lanes: any W, any group, any alignment
+//   kStoreVec     W (and the group width) a multiple of a 16-byte piece, y 16-byte aligned: whole aligned pieces
+enum { kStoreRows = 0, kStoreVec = 1 };
+// Elements that a thread takes at a time (F(6,r) in binary32: a row as 16 + 8 bytes per lane 0.82 to 1.2 times as fast as 16-byte pieces,
+// two threads of 12 bytes 0.92 to 1.25)
+template <typename T, int M> constexpr int kRowPiece = sizeof(T) == 4 && M == 6 ? 3 : M;
+
+// kStoreRows was two ways: element by element, or, where a group spans the width, a channel's rows as one run of aligned 16-byte pieces
+// gathered element by element (100 instructions a piece).  The output transform alone, 270 widths that are no whole number of pieces,
+// their time against this one's: binary16 1.1 to 1.3 (up to 1.7 in wide images; F(2,3) on binary16 products 0.9 to 1.3), binary32
+// 1.05 to 1.15 (F(6,3) @50 columns 0.92).  512 ch @7x7 batch 256 F(8,3) 18.4 -> 16.6 us, 256 ch @14x14 with
+// products in binary16 23.6 -> 19.1.  With the streaming hint F(2,r) and F(4,r) 0.8 to 1.0, others the same.
 
 // The [32 channels][rows][columns] block of a group, staged in LDS (channel pitch sh.k_pitch, row pitch
 // sh.cols_pitch), to y [N][K][H][W] (or its 2 x 2 max-pooled form): lanes along W.  Called by all
@@ -243,90 +312,23 @@ __device__ __forceinline__ void store_output_block(const T *lds, T *__restrict__
             u32x4 *dst = reinterpret_cast<u32x4 *>(y + (((size_t)img * K + k) * H + h) * W + w0 + q * PE);
             __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y}, dst);    // y is not read again by this call
         }
-    } else if constexpr (STG == kStoreFlat) {
-        // the group spans the width: rows h0 .. h1-1 of one channel are one run of y
-        const int h0 = tr * M;
-        int h1 = h0 + sh.rows; if (h1 > H) h1 = H;
-        const int run = (h1 - h0) * W;
-        const int slots = kChanBlock * sh.pieces;
-        for (int s = threadIdx.x; s < slots; s += (int)blockDim.x) {
-            const int kk = (int)__umulhi((unsigned)s, sh.piece_magic);
-            const int kq = s - kk * sh.pieces;
-            const int k = kb * kChanBlock + kk;
-            if (k >= K) continue;
-            const long long e0 = (((long long)img * K + k) * H + h0) * W;         // first element of the run
-            const long long p0 = (e0 & ~(long long)(PE - 1)) + (long long)kq * PE;   // piece, aligned in y
-            const int rel = (int)(p0 - e0);                                        // -(PE-1) .. run-1 if needed
-            if (rel >= run) continue;
-            // (row, column) of the piece's first element inside the run, then step along it
-            const int q = rel < 0 ? 0 : rel;
-            int hr = (int)__umulhi((unsigned)q, sh.w_magic);
-            int w = q - hr * W;
-            const T *src = lds + kk * sh.k_pitch;
-            T val[PE];
-#pragma unroll
-            for (int e = 0; e < PE; ++e) {
-                const int pos = rel + e;
-                val[e] = (T)0.0f;
-                if (pos >= 0 && pos < run) {
-                    val[e] = src[hr * sh.cols_pitch + w];
-                    if (++w == W) { w = 0; ++hr; }
-                }
-            }
-            if (rel >= 0 && rel + PE <= run) {
-                u32x4 piece;
-                __builtin_memcpy(&piece, val, 16);
-                __builtin_nontemporal_store(piece, reinterpret_cast<u32x4 *>(y + p0));
-            } else {
-#pragma unroll
-                for (int e = 0; e < PE; ++e)
-                    if (rel + e >= 0 && rel + e < run) y[p0 + e] = val[e];
-            }
-        }
     } else {
-        const unsigned magic = (unsigned)((((unsigned long long)1 << 32) + cols - 1) / cols);
-        const int slots = kChanBlock * sh.rows * cols;
+        constexpr int P = kRowPiece<T, M>;
+        const int per_line = sh.twc * (M / P);
+        const int slots = sh.images * kChanBlock * sh.rows * per_line;
         for (int s = threadIdx.x; s < slots; s += (int)blockDim.x) {
-            const int line = cols > 1 ? (int)__umulhi((unsigned)s, magic) : s;
-            const int q = s - line * cols;
-            const int kk = (int)__umulhi((unsigned)line, sh.rows_magic), p = line - kk * sh.rows;
-            const int k = kb * kChanBlock + kk, h = tr * M + p;
-            if (k >= K || h >= H) continue;
-            y[(((size_t)img * K + k) * H + h) * W + w0 + q] = lds[kk * sh.k_pitch + p * sh.cols_pitch + q];
+            const int line = per_line > 1 ? (int)__umulhi((unsigned)s, sh.line_magic) : s;
+            const int w = (s - line * per_line) * P;
+            const int plane = (int)__umulhi((unsigned)line, sh.rows_magic), p = line - plane * sh.rows;
+            const int k = kb * kChanBlock + plane % kChanBlock, h = tr * M + p, image = img + plane / kChanBlock;
+            if (k >= K || h >= H || w >= cols || image >= sh.batch) continue;
+            T v[P];
+            __builtin_memcpy(v, __builtin_assume_aligned(lds + plane * sh.k_pitch + p * sh.cols_pitch + w, P * sizeof(T) % 8 == 0 ? 8 : 4), P * sizeof(T));
+            T *to = y + (((size_t)image * K + k) * H + h) * W + w0 + w;
+            store_row_part<T, P>(to, v, cols - w);
         }
     }
 }
-
-// COUNT elements to an element-aligned address; NT: with the streaming cache hint
-#define NOVA_STORE(type, at, value)                                                              \
-    do {                                                                                         \
-        type *nova_at_ = reinterpret_cast<type *>(at);                                           \
-        if constexpr (NT) __builtin_nontemporal_store(value, nova_at_); else *nova_at_ = value;  \
-    } while (0)
-template <typename T, int COUNT, bool NT = false>
-__device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
-{
-    constexpr int WORDS = COUNT * (int)sizeof(T) / 4;
-    typedef unsigned int piece4 __attribute__((ext_vector_type(4), aligned(2)));
-    typedef unsigned int piece3 __attribute__((ext_vector_type(3), aligned(2)));
-    typedef unsigned int piece2 __attribute__((ext_vector_type(2), aligned(2)));
-    typedef unsigned int piece1 __attribute__((aligned(2)));
-    if constexpr (COUNT * (int)sizeof(T) % 4 != 0) {
-#pragma unroll
-        for (int e = 0; e < COUNT; ++e) dst[e] = v[e];
-    } else {
-        unsigned w[WORDS];
-        __builtin_memcpy(w, v, WORDS * 4);
-        unsigned char *at = reinterpret_cast<unsigned char *>(dst);
-        constexpr int FOURS = WORDS / 4 * 4;
-#pragma unroll
-        for (int e = 0; e < FOURS; e += 4) NOVA_STORE(piece4, at + 4 * e, (piece4{w[e], w[e + 1], w[e + 2], w[e + 3]}));
-        if constexpr (WORDS - FOURS == 3) NOVA_STORE(piece3, at + 4 * FOURS, (piece3{w[FOURS], w[FOURS + 1], w[FOURS + 2]}));
-        if constexpr (WORDS - FOURS == 2) NOVA_STORE(piece2, at + 4 * FOURS, (piece2{w[FOURS], w[FOURS + 1]}));
-        if constexpr (WORDS - FOURS == 1) NOVA_STORE(piece1, at + 4 * (WORDS - 1), w[WORDS - 1]);
-    }
-}
-#undef NOVA_STORE
 
 // The larger of two values, of which a is the earlier one of its window: a NaN wins, and of a zero of either sign the
 // earlier stays, as in the separate output transform's comparisons one after the other (elementwise maximum alone makes
@@ -458,7 +460,9 @@ static size_t out_shape(int twb, int trb, OutShape &sh)
     // writing one (row, column) fall into different banks
     if ((kp / 4) % 2 == 0) kp += 4;
     sh.k_pitch = kp;
-    sh.pieces = 1; sh.piece_magic = 0; sh.w_magic = 0;
+    const int per_line = twb * (M / kRowPiece<T, M>);
+    sh.line_magic = per_line > 1 ? (unsigned)((((unsigned long long)1 << 32) + per_line - 1) / per_line) : 0;
+    sh.images = 1;
     sh.pool = 0;
     sh.half_rows_magic = sh.rows / 2 > 1 ? (unsigned)((((unsigned long long)1 << 32) + sh.rows / 2 - 1) / (sh.rows / 2)) : 0;
     return (size_t)kChanBlock * kp * sizeof(T);

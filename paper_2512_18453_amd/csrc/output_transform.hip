@@ -3,8 +3,8 @@
 // a multiple of 128; the extra rows are never read).
 //
 // One workgroup takes one image, one tile row, a group of TWB neighbouring tiles (for narrow
-// images, where a tile row has few tiles: TRB neighbouring tile rows of full width) and one block of
-// 32 output channels; thread = one tile x one channel, so the n*n loads of a half-wave are 128
+// images, where a tile row has few tiles: TRB neighbouring tile rows of full width; for images of one to four tiles: several
+// images) and one block of 32 output channels; thread = one tile x one channel, so the n*n loads of a half-wave are 128
 // (fp32 M) contiguous bytes each and a workgroup reads TWB*128 contiguous bytes per xi.  The
 // m x m results go through LDS so that the global stores run along W.
 // For points given as 0, +a, -a, ... the rows of +a and -a enter only through their sum (even
@@ -47,7 +47,7 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
     const int tg = bid % sh.groups; bid /= sh.groups;
     const int tr = (bid % row_groups) * sh.trb; bid /= row_groups;      // first tile row of the group
     const int kb = bid % k_blocks; bid /= k_blocks;
-    const int img = bid;
+    const int img = bid * sh.images;
     const int tc0 = sh.trb > 1 ? 0 : tg * sh.twb;
 
     if constexpr (CF > 0) {
@@ -78,16 +78,17 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
     }
 
     const int j = threadIdx.x >> 5, k_in = threadIdx.x & 31;
-    int jr = 0, jc = j;                       // tile row and column inside the group
-    if (sh.trb > 1) { jr = j / tiles_w; jc = j - jr * tiles_w; }
-    const bool active = j < sh.twb && tc0 + jc < tiles_w && tr + jr < tiles_h;
+    const int ji = sh.images > 1 ? j / sh.twb : 0, j_in = j - ji * sh.twb;      // image; tile, tile row and column of the group's in it
+    int jr = 0, jc = j_in;
+    if (sh.trb > 1) { jr = j_in / tiles_w; jc = j_in - jr * tiles_w; }
+    const bool active = j < sh.images * sh.twb && img + ji < sh.batch && tc0 + jc < tiles_w && tr + jr < tiles_h;
     // (few-channel path: the results wait in registers, binary16 ones two to a register, until every
     // thread has read its operands)
     typedef typename std::conditional<sizeof(T) == 2, unsigned int, float>::type held_t;
     constexpr int kHeldPer = sizeof(T) == 2 ? 2 : 1;
     held_t held[CF > 0 ? (M * M + kHeldPer - 1) / kHeldPer : 1];
     if (active) {
-        const long long t = ((long long)img * tiles_h + tr + jr) * tiles_w + tc0 + jc;
+        const long long t = ((long long)(img + ji) * tiles_h + tr + jr) * tiles_w + tc0 + jc;
         // plane base of each xi is uniform (scalar registers); the offset inside the plane is per
         // thread and fits 32 bits (checked by the launcher)
         const size_t xi_stride = (size_t)k_blocks * Ttot * kChanBlock;
@@ -129,7 +130,7 @@ output_transform_kernel(const MT *__restrict__ Mp, const T *__restrict__ Vp, con
 #pragma unroll
             for (int p = 0; p < M; ++p) z[p][b] = o[p];
         }
-        T *dst = lds + k_in * sh.k_pitch + jr * M * sh.cols_pitch + jc * M;
+        T *dst = lds + (ji * kChanBlock + k_in) * sh.k_pitch + jr * M * sh.cols_pitch + jc * M;
 #pragma unroll
         for (int p = 0; p < M; ++p) {
             float o[M];
@@ -258,38 +259,35 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     if (CF == 0 && (size_t)g.k_blocks * g.Tp * kChanBlock * sizeof(MT) >= ((size_t)1 << 32)) return (int)hipErrorInvalidValue;
     if (CF > 0 && g.C > CF) return (int)hipErrorInvalidValue;
     const bool vec = g.W % PE == 0 && aligned && (sh.groups == 1 || (twb * M) % PE == 0);
-    // (W >= 2 and at least two pieces: the reciprocals used for the divisions do not exist for 1)
-    const bool flat = !vec && aligned && sh.groups == 1 && g.W >= 2 && sh.rows * g.W + 2 * (PE - 1) >= 2 * PE &&
-                      (long long)sh.rows * g.W < (1 << 15);
-    if (flat) {
-        sh.pieces = (sh.rows * g.W + 2 * (PE - 1)) / PE;
-        sh.piece_magic = (unsigned)((((unsigned long long)1 << 32) + sh.pieces - 1) / sh.pieces);
-        sh.w_magic = (unsigned)((((unsigned long long)1 << 32) + g.W - 1) / g.W);
-    }
     sh.pool = (flags & NOVA_FLAG_POOL2) ? 1 : 0;
-    const int threads = ((sh.twb * 32 + 63) / 64) * 64;
-    const long long blocks = (long long)sh.groups * ceil_div(g.tiles_h, trb) * g.k_blocks * g.N;
+    sh.batch = g.N;
+    // Images of one to four tiles: several to a group, up to 8 tiles (a tile by itself leaves half of its wave idle).  512 ch @7x7 batch 256 F(8,3) 16.6 us
+    // with one image, 15.8 with two, 15.2 with four, 15.1 with eight; 256 ch @14x14 with products in binary16 19.1 with one, 18.4 with two.
+    constexpr int kGroupTiles = 8;
+    if (CF == 0 && !sh.pool && !vec && sh.twb == g.tiles_h * g.tiles_w && sh.twb <= kGroupTiles / 2) {
+        sh.images = kGroupTiles / sh.twb;
+        if (sh.images > g.N) sh.images = g.N;
+        while (sh.images > 1 && sh.images * lds_bytes > 64 * 1024) --sh.images;
+    }
+    const int threads = ((sh.images * sh.twb * 32 + 63) / 64) * 64;
+    const long long blocks = (long long)sh.groups * ceil_div(g.tiles_h, trb) * g.k_blocks * ceil_div(g.N, sh.images);
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     void (*kern)(const MT *, const T *, const T *, T *, int, int, int, int, int, int, long long, OutShape, OutCoef<N, R>);
     const bool relu = (flags & NOVA_FLAG_RELU) != 0;
-    const int stg = vec ? kStoreVec : flat ? kStoreFlat : kStoreScalar;
     auto pick = [&](auto sym) {
         constexpr bool S = decltype(sym)::value;
-        switch (stg) {
-        case kStoreVec:  return relu ? output_transform_kernel<N, R, T, MT, S, kStoreVec, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreVec, false, CF, COLUMNS_DONE>;
-        case kStoreFlat: return relu ? output_transform_kernel<N, R, T, MT, S, kStoreFlat, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreFlat, false, CF, COLUMNS_DONE>;
-        default:         return relu ? output_transform_kernel<N, R, T, MT, S, kStoreScalar, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreScalar, false, CF, COLUMNS_DONE>;
-        }
+        if (vec) return relu ? output_transform_kernel<N, R, T, MT, S, kStoreVec, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreVec, false, CF, COLUMNS_DONE>;
+        return relu ? output_transform_kernel<N, R, T, MT, S, kStoreRows, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreRows, false, CF, COLUMNS_DONE>;
     };
     if constexpr (COLUMNS_DONE) kern = pick(std::true_type{});
     else if constexpr (CF > 0 && sizeof(T) == 2) kern = pick(std::false_type{});       // (paired points: few_channels.hip)
     else kern = t->symmetric ? pick(std::true_type{}) : pick(std::false_type{});
     if constexpr (CF > 0)
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes, stream,
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes * sh.images, stream,
                            (const MT *)nullptr, (const T *)Mp, (const T *)few_u, (T *)y, g.K, g.H, g.W, g.tiles_h, g.tiles_w,
                            g.k_blocks, g.T, sh, coef);
     else
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes, stream,
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes * sh.images, stream,
                            (const MT *)Mp, (const T *)nullptr, (const T *)nullptr, (T *)y, g.K, g.H, g.W, g.tiles_h,
                            g.tiles_w, g.k_blocks, g.Tp, sh, coef);
     return (int)hipGetLastError();
