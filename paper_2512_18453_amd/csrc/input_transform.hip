@@ -27,13 +27,13 @@ namespace nova {
 
 // A workgroup's windows: 32 channels, or 4 for the compact layout of the first layer.  Threads per tile and word --
 // WIDE: one per pair of transform rows (+a, -a), for launches that leave the chip half empty, where a thread's chain
-// of instructions is what takes the time.
+// of instructions is what takes the time; 2: also only 4 tiles, so that they are spread over more compute units.
 template <typename T, int CH> constexpr int kWords = CH * (int)sizeof(T) / 4;
-template <int N, typename T, int CH, bool WIDE>
-struct TileBlock : TileWindows<N, T, CH, CH == 4 ? 64 / kWords<T, CH> : sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8),
-                               WIDE ? N / 2 : N >= 8 ? 2 : 1> {
-    using W = TileWindows<N, T, CH, CH == 4 ? 64 / kWords<T, CH> : sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8),
-                          WIDE ? N / 2 : N >= 8 ? 2 : 1>;
+template <int N, typename T, int CH, int WIDE>
+constexpr int kTilesOf = CH == 4 ? 64 / kWords<T, CH> : WIDE == 2 ? 4 : sizeof(T) == 2 ? (N >= 8 ? 8 : 16) : (N >= 8 ? 4 : 8);
+template <int N, typename T, int CH, int WIDE>
+struct TileBlock : TileWindows<N, T, CH, kTilesOf<N, T, CH, WIDE>, WIDE ? N / 2 : N >= 8 ? 2 : 1> {
+    using W = TileWindows<N, T, CH, kTilesOf<N, T, CH, WIDE>, WIDE ? N / 2 : N >= 8 ? 2 : 1>;
     static constexpr int WAVES_PER_XI = W::TB * W::GP / 64;
 };
 
@@ -88,7 +88,7 @@ struct PackFilters { const T *from; T *to; long long rows; };
 
 // Groups of tiles: a row of row_tiles consecutive t (the whole batch, or one tile row of an image) is cut into
 // groups_per_row groups of `per` tiles.
-template <int N, int R, typename T, bool SYM, int CH, bool WIDE, bool STREAM, int MAXIMA>
+template <int N, int R, typename T, bool SYM, int CH, int WIDE, bool STREAM, int MAXIMA>
 __global__ void __launch_bounds__((TileBlock<N, T, CH, WIDE>::THREADS), 3)     // (three waves per SIMD: as many as the windows in LDS allow)
 input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H, int W, int tiles_h, int tiles_w,
                        int c_blocks, unsigned t_groups, int row_tiles, int groups_per_row, int per, int Ttot, long long x_elems,
@@ -177,7 +177,7 @@ input_transform_kernel(const T *__restrict__ x, T *__restrict__ V, int C, int H,
 template <int N, typename T>
 static int maxima_count(const Geometry &g, int maxima)
 {
-    using B = TileBlock<N, T, kChanBlock, false>;
+    using B = TileBlock<N, T, kChanBlock, 0>;
     const long long blocks = (g.T + B::TB - 1) / B::TB * g.c_blocks;
     const long long count = maxima == kMaxTensor ? blocks * (B::THREADS / 64) : maxima == kMaxPosition ? blocks * B::WAVES_PER_XI * 4 : 0;
     return count > 0x7fffffffLL ? -1 : (int)count;
@@ -187,7 +187,7 @@ template <int N, int R, typename T>
 static int launch_it(const nova_transforms *t, const void *x, void *V, const Geometry &g, bool stream_x, int maxima, float *partials,
                      hipStream_t stream)
 {
-    using B = TileBlock<N, T, kChanBlock, false>;
+    using B = TileBlock<N, T, kChanBlock, 0>;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
     if (g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
@@ -199,34 +199,46 @@ static int launch_it(const nova_transforms *t, const void *x, void *V, const Geo
     // group.  Whole calls, time without / with both, layers whose x, V and M are 300 MB, n = 8 and 10, five pairs of
     // channel counts, by tiles per row: 4 and 5 0.94-0.99, 6 0.98-1.06, 7 0.98-1.08, 8 0.98-1.11, 9 and 10 (two groups)
     // 0.90-0.96, 12 0.93-0.99, 14 0.96-0.99, 15 and 16 0.96-1.03, 21 and 28 0.91-1.00.
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxNone>
-                             : input_transform_kernel<N, R, T, false, kChanBlock, false, false, kMaxNone>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kChanBlock, 0, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kChanBlock, 0, false, kMaxNone>;
     if (maxima != kMaxNone && !t->symmetric) return (int)hipErrorInvalidValue;
-    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxTensor>;
-    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, kChanBlock, false, false, kMaxPosition>;
+    if (maxima == kMaxTensor) kern = input_transform_kernel<N, R, T, true, kChanBlock, 0, false, kMaxTensor>;
+    if (maxima == kMaxPosition) kern = input_transform_kernel<N, R, T, true, kChanBlock, 0, false, kMaxPosition>;
     bool rows = false;
     if constexpr (N >= 8 && sizeof(T) == 2)
         if (stream_x && maxima == kMaxNone && t->symmetric && g.tiles_w > B::TB * 3 / 4 && g.tiles_w <= B::TB) {
-            kern = input_transform_kernel<N, R, T, true, kChanBlock, false, true, kMaxNone>;
+            kern = input_transform_kernel<N, R, T, true, kChanBlock, 0, true, kMaxNone>;
             rows = true;
         }
-    int threads = B::THREADS;
+    int threads = B::THREADS, tiles = B::TB, lds_bytes = B::LDS_BYTES;
     // no more workgroups than compute units: one thread per pair of transform rows.  us per launch, without / with:
     // 512 ch @14x14 F(4,3) 6.2 / 5.2, 33 ch @30x41 batch 3 F(4,3) 7.5 / 5.4, binary32 16 ch @32x32 F(4,3) 5.7 / 4.6,
     // 256 ch @28x28 batch 16 F(8,3) (256 workgroups) 9.4 / 9.0, batch 32 (512) 13.3 / 15.0
     if (!rows && maxima == kMaxNone && t->symmetric && (g.T + B::TB - 1) / B::TB * g.c_blocks <= device_cu_count()) {
-        kern = input_transform_kernel<N, R, T, true, kChanBlock, true, false, kMaxNone>;
-        threads = TileBlock<N, T, kChanBlock, true>::THREADS;
+        kern = input_transform_kernel<N, R, T, true, kChanBlock, 1, false, kMaxNone>;
+        threads = TileBlock<N, T, kChanBlock, 1>::THREADS;
+        // Four tiles per workgroup while those are no more than compute units either (binary16 n = 6: twice as many).  The transform alone, time
+        // with more over time with four, 280 launches: n = 10 1.11-1.52 (up to twice the units 0.97-1.03), n = 8 1.08-1.33 (1.01-1.02), n = 6
+        // 0.99-1.22 (1.05-1.09; more 0.95-1.02), binary32 n = 6 0.93-1.10 (0.95-1.00); n = 4 0.84-1.08, not taken.  512 ch @14x14 F(4,3) 5.2 / 4.3 us.
+        if constexpr (B::TB > 4 && N > 4) {
+            if ((g.T + 3) / 4 * g.c_blocks <= device_cu_count() * (N == 6 && sizeof(T) == 2 ? 2 : 1)) {
+                using S = TileBlock<N, T, kChanBlock, 2>;
+                kern = input_transform_kernel<N, R, T, true, kChanBlock, 2, false, kMaxNone>;
+                threads = S::THREADS;
+                tiles = S::TB;
+                lds_bytes = S::LDS_BYTES;
+            }
+        }
     }
     const int row_tiles = rows ? g.tiles_w : (int)g.T;
-    const int groups_per_row = ceil_div(row_tiles, B::TB);
-    const int per = rows ? row_tiles : B::TB;               // (a row is one group)
+    const int groups_per_row = ceil_div(row_tiles, tiles);
+    const int per = rows ? row_tiles : tiles;               // (a row is one group)
     const long long t_groups = g.T / row_tiles * groups_per_row;
     const long long blocks = t_groups * g.c_blocks;
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     const long long x_elems = (long long)g.N * g.C * g.H * g.W;
     const int by_element = x_elems < N - R + 1 || (long long)kChanBlock * g.H * g.W >= (1LL << 30) ? 1 : 0;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), B::LDS_BYTES, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(threads), lds_bytes, stream, (const T *)x, (T *)V, g.C, g.H, g.W,
                        g.tiles_h, g.tiles_w, g.c_blocks, (unsigned)t_groups, row_tiles, groups_per_row, per, (int)g.T, x_elems,
                        by_element, partials, maxima_count<N, T>(g, maxima), PackFilters<T>{nullptr, nullptr, 0}, coef);
     return (int)hipGetLastError();
@@ -292,7 +304,7 @@ template <int N, int R, typename T>
 static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, const Geometry &g, const void *U, void *Uc,
                          hipStream_t stream)
 {
-    using B = TileBlock<N, T, kFewIn, false>;
+    using B = TileBlock<N, T, kFewIn, 0>;
     if (g.C > kFewIn || g.T > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     InCoef<N> coef;
     fill_in_coef<N>(t, coef);
@@ -300,14 +312,14 @@ static int launch_it_few(const nova_transforms *t, const void *x, void *Vc, cons
     if (blocks <= 0 || blocks > 0x7fffffffLL) return (int)hipErrorInvalidValue;
     const long long x_elems = (long long)g.N * g.C * g.H * g.W;
     const int by_element = x_elems < N - R + 1 || (long long)kFewIn * g.H * g.W >= (1LL << 30) ? 1 : 0;
-    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, false, false, kMaxNone>
-                             : input_transform_kernel<N, R, T, false, kFewIn, false, false, kMaxNone>;
+    auto kern = t->symmetric ? input_transform_kernel<N, R, T, true, kFewIn, 0, false, kMaxNone>
+                             : input_transform_kernel<N, R, T, false, kFewIn, 0, false, kMaxNone>;
     int threads = B::THREADS;
     // (as in launch_it; us for the whole call without / with: 3 -> 64 @48x18 batch 12 F(8,3) 21.0 / 18.4, 4 -> 41 @44x14 batch 32
     // F(6,3) 13.8 / 12.3, but 3 -> 10 @24x57 batch 12 F(2,3) 8.5 / 9.0)
     if (N > 4 && t->symmetric && blocks <= device_cu_count()) {
-        kern = input_transform_kernel<N, R, T, true, kFewIn, true, false, kMaxNone>;
-        threads = TileBlock<N, T, kFewIn, true>::THREADS;
+        kern = input_transform_kernel<N, R, T, true, kFewIn, 1, false, kMaxNone>;
+        threads = TileBlock<N, T, kFewIn, 1>::THREADS;
     }
     const PackFilters<T> pack = {(const T *)U, (T *)Uc, U ? (long long)g.n * g.n * g.Kp : 0};
     const long long pack_blocks = (pack.rows + threads - 1) / threads;
