@@ -250,10 +250,11 @@ int nova::conv2d_with_workspace(const nova_transforms *t, const void *x, const v
     // Little work: one kernel for the whole call, which leaves the workspace alone.  (It reads x and U while it writes
     // y; the separate kernels have read both before, so a call whose y overlaps one of them stays with those.)
     const Geometry whole = make_geometry(N, C, H, W, K, m, r);
-    if (separate && !contract_output) {
+    if (separate) {
         // (rows of M past the last tile are not written)
-        const int tiles = layer_tiles(t, whole, dtype, v_bytes(whole, dtype) + second_part(whole, columns) / whole.Tp * whole.T);
-        if (tiles > 0) return hip_result(launch_layer(t, x, U, y, whole, dtype, flags, tiles, stream));
+        const size_t second = contract_output ? 0 : second_part(whole, columns) / whole.Tp * whole.T;
+        const LayerShape shape = layer_shape(t, whole, dtype, v_bytes(whole, dtype) + second, contract_output);
+        if (shape.tiles > 0) return hip_result(launch_layer(t, x, U, y, whole, dtype, flags, shape, stream));
     }
 
     const size_t es = dtype_size(dtype);

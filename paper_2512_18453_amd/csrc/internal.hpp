@@ -129,11 +129,12 @@ bool fused_contract_output_applies(const nova_transforms *t, const Geometry &g, 
 bool fused_contract_output_preferred(const nova_transforms *t, const Geometry &g, int dtype, int flags);
 int launch_fused_contract_output(const nova_transforms *t, const void *U, const void *V, void *y, const Geometry &g,
                                  int dtype, int flags, void *stream);
-// The whole layer in one kernel, for layers with little work: layer_tiles names the workgroup shape nova_winograd_conv2d
-// runs it with (0: it does not); domain_bytes: of V and what follows it in the separate kernels.  The results are those of the separate
+// The whole layer in one kernel, for layers with little work: layer_shape names the tiles and output channels of a workgroup that nova_winograd_conv2d
+// runs it with (0 tiles: it does not); domain_bytes: of V and what follows it in the separate kernels.  The results are those of the separate
 // kernels bit for bit.
-int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t domain_bytes);
-int launch_layer(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int dtype, int flags, int tiles,
+struct LayerShape { int tiles, channels; };
+LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, size_t domain_bytes, bool contract_output);
+int launch_layer(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int dtype, int flags, LayerShape shape,
                  void *stream);
 // Few input channels (C <= few_channels_limit()): the output transform forms the products itself
 // from V and a packed copy Uc of the filters' first channels (few_channels_filter_bytes).

@@ -184,7 +184,8 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
     // filters are asked for before the transform where the registers hold both.  Scratch per lane: 44 bytes (10 registers) for n = 8 with
     // 16 tiles in binary16, whose 1024 threads have 128 registers each; n = 10, 168 registers: 20 bytes (4) in binary16, 108 (30, r = 3)
     // and 72 (17, r = 5) in binary32; none elsewhere
-    constexpr bool EARLY = N < 8 || (N == 8 && (TB == 8 || sizeof(T) == 4));
+    // (with 64 output channels they come after it: 80 bytes of scratch otherwise, 64 -> 64 @224x224 F(4,3) 16.1 us instead of 14.4)
+    constexpr bool EARLY = KB < 64 && (N < 8 || (N == 8 && (TB == 8 || sizeof(T) == 4)));
     static_assert(B::GP == 16 && N * N % WAVES == 0 && KB % 16 == 0 && (TB == 8 || TB == 16), "workgroup shape");
     extern __shared__ __align__(16) unsigned char lds_raw[];
     unsigned *windows = reinterpret_cast<unsigned *>(lds_raw);
@@ -243,7 +244,11 @@ layer_kernel(const T *__restrict__ x, const T *__restrict__ U, T *__restrict__ y
             for (int i = 0; i < OWN; ++i) {
                 const T *at = uniform_pointer(u_at + (size_t)(i * WAVES) * c_blocks * Kp * kChanBlock);
 #pragma unroll
-                for (int f = 0; f < KF; ++f) uf[i][f] = P::load_filter(at + f * 16 * kChanBlock, (unsigned)lane);
+                for (int f = 0; f < KF; ++f) {
+                    // (U has whole blocks of 32 output channels: of the last 64 there may be only the first, which is read again then)
+                    const int rows = KB <= 32 || kg * KB + f * 16 < Kp ? f * 16 : 0;
+                    uf[i][f] = P::load_filter(at + rows * kChanBlock, (unsigned)lane);
+                }
             }
         };
         if constexpr (EARLY) load_filters();
@@ -314,15 +319,21 @@ static int launch_layer_shape(const nova_transforms *t, const void *x, const voi
     return (int)hipGetLastError();
 }
 
-// Output channels per workgroup
+// Output channels per workgroup.  16 tiles of n = 4 and 6 in binary16 also take 64: the windows are transformed half as often and few
+// layers need a second round of workgroups (64 -> 64 @224x224 F(4,3) 18.4 -> 14.4 us, 48 -> 64 5x5 @25x25 batch 22 F(2,5) 21.5
+// -> 12.7), but a workgroup by itself takes longer.  (Larger n: the products do not fit the LDS or the registers.)
 template <int N, typename T> constexpr int kLayerChannels = sizeof(T) == 2 && N < 10 ? 32 : 16;
+template <int N, typename T> constexpr bool kWideLayers = sizeof(T) == 2 && N < 8;
 
 template <int N, int R, typename T, bool ROWS_FIRST>
-static int launch_layer_n(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int flags, int tiles, hipStream_t s)
+static int launch_layer_n(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int flags, LayerShape shape, hipStream_t s)
 {
+    if constexpr (kWideLayers<N, T>) {
+        if (shape.channels == 64) return launch_layer_shape<N, R, T, 16, 64, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
+    }
     // (16 windows of 10 x 10 and their V do not fit the LDS)
     if constexpr (N < 10) {
-        if (tiles == 16) return launch_layer_shape<N, R, T, 16, kLayerChannels<N, T>, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
+        if (shape.tiles == 16) return launch_layer_shape<N, R, T, 16, kLayerChannels<N, T>, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
     }
     return launch_layer_shape<N, R, T, 8, kLayerChannels<N, T>, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
 }
@@ -334,6 +345,9 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 //                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows leave
 //                     element by element (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
 //   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
+//   64 channels       the same with their own times (n = 4: at least 5 + turns * 1.7, up to four turns), taken below 0.94 of the estimate for 32.  300
+//                     layers of 200 to 16000 tiles: 37 run otherwise than before, 1.2 times as fast in the geometric mean, the slowest 0.94; n = 4
+//                     with more turns 0.88
 // Fitted to 2600 layers of 1 to 12000 tiles, 5 to 520 -> 1 to 520 channels, timed both ways on one MI355X (sd 6-13 %, one kernel n = 4
 // 20-30 %): 1295 are taken, geometric mean 1.54 times as fast as the separate kernels; nine are slower by more than 2 %, two of
 // them by more than 10 % (18 -> 128 5x5 @38x4 batch 7 F(6,5) binary32 20.5 / 16.9 us, 300 -> 33 @7x109 batch 32 F(6,3) binary32 78.7 / 70.9).
@@ -350,45 +364,60 @@ static const LayerTimes &layer_times(int n, bool half)
     return (half ? kHalf : kFull)[n / 2 - 2];
 }
 
-int layer_tiles(const nova_transforms *t, const Geometry &g, int dtype, size_t domain_bytes)
+LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, size_t domain_bytes, bool contract_output)
 {
     // points in the paired order, whole window rows in x, planes within 32-bit offsets
     const long long x_elems = (long long)g.N * g.C * g.H * g.W;
     if (!t->symmetric || g.C <= few_channels_limit() || g.T > 0x7fffffffLL || x_elems < g.m || (long long)kChanBlock * g.H * g.W >= (1LL << 30))
-        return 0;
+        return {0, 0};
     const bool half = dtype == NOVA_F16;
     const LayerTimes &lt = layer_times(g.n, half);
     const int turns = ceil_div(g.C, half ? 32 : 16), k_groups = ceil_div(g.K, half && g.n < 10 ? 32 : 16);
     double best = lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes;
     if (!half) best += 11e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
     best *= best < 30.0 ? 0.94 : 0.85;
+    // Where contraction and output transform would run as one kernel (contract_output.hip) domain_bytes is V alone; only n = 6 was timed
+    // against it: what its stages, 64 input channels each, add.  (96 -> 128 @39x39 batch 16 F(4,3) 22.9 / 18.3 us, 48 -> 64 5x5 @25x25 batch 22 21.5 / 12.7.)
+    if (contract_output) {
+        if (!half || g.n != 6) return {0, 0};
+        best = 0.85 * (lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes + 1.5 * ((g.c_blocks + 1) / 2));
+    }
     const double cut = std::max(0.0, (double)g.N * g.K * g.H * (g.W % g.m) - 2e6);
-    int tiles = 0;
+    const int channels = half && g.n < 10 ? 32 : 16;
+    const auto rounds_of = [&](int tiles, int groups) {
+        return (double)(((g.T + tiles - 1) / tiles * groups + device_cu_count() - 1) / device_cu_count());
+    };
+    LayerShape shape = {0, 0};
     for (int i = 0; i < (g.n < 10 ? 2 : 1); ++i) {
-        const long long groups = (g.T + 8 * (i + 1) - 1) / (8 * (i + 1)) * k_groups;
-        const long long rounds = (groups + device_cu_count() - 1) / device_cu_count();
-        double time = 2.0 + (double)rounds * (turns * lt.turn[i] + lt.once[i]);
+        double time = 2.0 + rounds_of(8 * (i + 1), k_groups) * (turns * lt.turn[i] + lt.once[i]);
         if (g.n == 4) time = std::max(time, 3.0 + turns * (half ? 1.3 : 1.0));
         time += 3e-6 * cut;
-        if (time < best) { best = time; tiles = 8 * (i + 1); }
+        if (time < best) { best = time; shape = {8 * (i + 1), channels}; }
     }
-    return tiles;
+    if (half && g.n < 8 && g.K > 32 && (g.n == 6 || turns <= 4)) {
+        const double once = g.n == 4 ? 1.9 : 5.3, turn = g.n == 4 ? 1.15 : 3.5;
+        double time = 2.0 + rounds_of(16, ceil_div(g.K, 64)) * (turns * turn + once);
+        if (g.n == 4) time = std::max(time, 5.0 + turns * 1.7);
+        time += 3e-6 * cut;
+        if (time < best * (shape.tiles ? 0.94 : 1.0)) shape = {16, 64};
+    }
+    return shape;
 }
 
-int launch_layer(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int dtype, int flags, int tiles,
+int launch_layer(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int dtype, int flags, LayerShape shape,
                  void *stream)
 {
     hipStream_t s = (hipStream_t)stream;
     const bool h = dtype == NOVA_F16;
     const bool rows_first = fused_contract_output_preferred(t, g, dtype, flags);
-#define NOVA_LAYER(N, R) (h ? launch_layer_n<N, R, f16, false>(t, x, U, y, g, flags, tiles, s) \
-                            : launch_layer_n<N, R, float, false>(t, x, U, y, g, flags, tiles, s))
+#define NOVA_LAYER(N, R) (h ? launch_layer_n<N, R, f16, false>(t, x, U, y, g, flags, shape, s) \
+                            : launch_layer_n<N, R, float, false>(t, x, U, y, g, flags, shape, s))
     if (t->r == 3) {
         switch (t->n) {
         case 4: return NOVA_LAYER(4, 3);
         case 6: return NOVA_LAYER(6, 3);
-        case 8: return rows_first ? launch_layer_n<8, 3, f16, true>(t, x, U, y, g, flags, tiles, s) : NOVA_LAYER(8, 3);
-        case 10: return rows_first ? launch_layer_n<10, 3, f16, true>(t, x, U, y, g, flags, tiles, s) : NOVA_LAYER(10, 3);
+        case 8: return rows_first ? launch_layer_n<8, 3, f16, true>(t, x, U, y, g, flags, shape, s) : NOVA_LAYER(8, 3);
+        case 10: return rows_first ? launch_layer_n<10, 3, f16, true>(t, x, U, y, g, flags, shape, s) : NOVA_LAYER(10, 3);
         }
     } else if (t->r == 5) {
         switch (t->n) {
