@@ -319,17 +319,18 @@ static int launch_layer_shape(const nova_transforms *t, const void *x, const voi
     return (int)hipGetLastError();
 }
 
-// Output channels per workgroup.  16 tiles of n = 4 and 6 in binary16 also take 64: the windows are transformed half as often and few
+// Output channels per workgroup.  16 tiles of n = 4 and 6 also take twice as many: the windows are transformed half as often and few
 // layers need a second round of workgroups (64 -> 64 @224x224 F(4,3) 18.4 -> 14.4 us, 48 -> 64 5x5 @25x25 batch 22 F(2,5) 21.5
-// -> 12.7), but a workgroup by itself takes longer.  (Larger n: the products do not fit the LDS or the registers.)
+// -> 12.7, binary32 96 -> 64 @16x16 batch 78 F(4,3) 29.9 -> 23.4), but a workgroup by itself takes longer.  (Larger n: the products do not fit
+// the LDS or the registers; 8 tiles of n = 8 in binary32 with 32 channels 1.5 to 2 times as long.)
 template <int N, typename T> constexpr int kLayerChannels = sizeof(T) == 2 && N < 10 ? 32 : 16;
-template <int N, typename T> constexpr bool kWideLayers = sizeof(T) == 2 && N < 8;
 
 template <int N, int R, typename T, bool ROWS_FIRST>
 static int launch_layer_n(const nova_transforms *t, const void *x, const void *U, void *y, const Geometry &g, int flags, LayerShape shape, hipStream_t s)
 {
-    if constexpr (kWideLayers<N, T>) {
-        if (shape.channels == 64) return launch_layer_shape<N, R, T, 16, 64, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
+    if constexpr (N < 8) {
+        constexpr int WIDE = 2 * kLayerChannels<N, T>;
+        if (shape.channels == WIDE) return launch_layer_shape<N, R, T, 16, WIDE, N / 2, ROWS_FIRST>(t, x, U, y, g, flags, s);
     }
     // (16 windows of 10 x 10 and their V do not fit the LDS)
     if constexpr (N < 10) {
@@ -341,13 +342,14 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 // Which layers run as one kernel, and with how many tiles per workgroup: the shape with the lowest estimate, if
 // that is below 0.94 of the estimate for the separate kernels (0.85 from 30 us on, where the estimates are widest).  Estimates (us):
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
-//                     (n = 4, where several workgroups share a compute unit: at least 3 + turns * 1.3, binary32 1.0, the serial chain)
+//                     (n = 4, where several workgroups share a compute unit: at least 3 + turns * 1.3, binary32 1.0, the serial chain; 16 tiles in
+//                     binary32 3 + turns / 2 + workgroups per compute unit, not rounded, * (0.7 turns + 0.55))
 //                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows leave
 //                     element by element (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
 //   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
-//   64 channels       the same with their own times (n = 4: at least 5 + turns * 1.7, up to four turns), taken below 0.94 of the estimate for 32.  300
-//                     layers of 200 to 16000 tiles: 37 run otherwise than before, 1.2 times as fast in the geometric mean, the slowest 0.94; n = 4
-//                     with more turns 0.88
+//   twice the         the same with their own times (n = 4: at least 5 + turns * 1.7, binary32 3.9 + turns * 1.35; binary16 up to four turns, with more
+//   channels          0.88 times as fast), taken below 0.94 of the estimate without.  600 layers of 200 to 16000 tiles in binary16: 80 run otherwise
+//                     than before, 1.2 times as fast in the geometric mean, the slowest 0.92
 // Fitted to 2600 layers of 1 to 12000 tiles, 5 to 520 -> 1 to 520 channels, timed both ways on one MI355X (sd 6-13 %, one kernel n = 4
 // 20-30 %): 1295 are taken, geometric mean 1.54 times as fast as the separate kernels; nine are slower by more than 2 %, two of
 // them by more than 10 % (18 -> 128 5x5 @38x4 batch 7 F(6,5) binary32 20.5 / 16.9 us, 300 -> 33 @7x109 batch 32 F(6,3) binary32 78.7 / 70.9).
@@ -390,16 +392,18 @@ LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, s
     LayerShape shape = {0, 0};
     for (int i = 0; i < (g.n < 10 ? 2 : 1); ++i) {
         double time = 2.0 + rounds_of(8 * (i + 1), k_groups) * (turns * lt.turn[i] + lt.once[i]);
+        if (g.n == 4 && !half && i == 1) time = 3.0 + 0.5 * turns + (double)((g.T + 15) / 16 * k_groups) / device_cu_count() * (0.7 * turns + 0.55);
         if (g.n == 4) time = std::max(time, 3.0 + turns * (half ? 1.3 : 1.0));
         time += 3e-6 * cut;
         if (time < best) { best = time; shape = {8 * (i + 1), channels}; }
     }
-    if (half && g.n < 8 && g.K > 32 && (g.n == 6 || turns <= 4)) {
-        const double once = g.n == 4 ? 1.9 : 5.3, turn = g.n == 4 ? 1.15 : 3.5;
-        double time = 2.0 + rounds_of(16, ceil_div(g.K, 64)) * (turns * turn + once);
-        if (g.n == 4) time = std::max(time, 5.0 + turns * 1.7);
+    if (g.n < 8 && g.K > channels && (!half || g.n == 6 || turns <= 4)) {
+        static const LayerTimes kWideHalf[] = {{{0, 1.15}, {0, 1.9}, 0, 0}, {{0, 3.5}, {0, 5.3}, 0, 0}}, kWideFull[] = {{{0, 1.3}, {0, 0.9}, 0, 0}, {{0, 2.95}, {0, 3.8}, 0, 0}};
+        const LayerTimes &wide = (half ? kWideHalf : kWideFull)[g.n / 2 - 2];
+        double time = 2.0 + rounds_of(16, ceil_div(g.K, 2 * channels)) * (turns * wide.turn[1] + wide.once[1]);
+        if (g.n == 4) time = std::max(time, half ? 5.0 + turns * 1.7 : 3.9 + turns * 1.35);
         time += 3e-6 * cut;
-        if (time < best * (shape.tiles ? 0.94 : 1.0)) shape = {16, 64};
+        if (time < best * (shape.tiles ? 0.94 : 1.0)) shape = {16, 2 * channels};
     }
     return shape;
 }
