@@ -398,7 +398,7 @@ LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, s
         if (time < best) { best = time; shape = {8 * (i + 1), channels}; }
     }
     if (g.n < 8 && g.K > channels && (!half || g.n == 6 || turns <= 4)) {
-        static const LayerTimes kWideHalf[] = {{{0, 1.15}, {0, 1.9}, 0, 0}, {{0, 3.5}, {0, 5.3}, 0, 0}}, kWideFull[] = {{{0, 1.3}, {0, 0.9}, 0, 0}, {{0, 2.95}, {0, 3.8}, 0, 0}};
+        static const LayerTimes kWideHalf[] = {{{0, 1.15}, {0, 1.9}, 0, 0}, {{0, 3.5}, {0, 5.3}, 0, 0}}, kWideFull[] = {{{0, 1.3}, {0, 0.9}, 0, 0}, {{0, 3.15}, {0, 3.6}, 0, 0}};
         const LayerTimes &wide = (half ? kWideHalf : kWideFull)[g.n / 2 - 2];
         double time = 2.0 + rounds_of(16, ceil_div(g.K, 2 * channels)) * (turns * wide.turn[1] + wide.once[1]);
         if (g.n == 4) time = std::max(time, half ? 5.0 + turns * 1.7 : 3.9 + turns * 1.35);
