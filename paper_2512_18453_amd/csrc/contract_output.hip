@@ -292,12 +292,13 @@ static int launch_co_chunks(const nova_transforms *t, const void *U, const void 
     // wide 1.0 to 2.7 times as fast, 7 and 8 columns 1.0, more 0.87 to 1.0; m = 4 where two or three columns of the last tile are
     // left, up to 18 columns, 1.0 to 1.25, else 0.9 to 1.0; m = 2 0.92 to 1.0.
     const bool narrow = !(flags & NOVA_FLAG_POOL2) && ((M == 6 && g.W <= 8) || (M == 4 && g.W % 4 >= 2 && g.W <= 18));
-    // Streaming hint for the rows: the same within 3 % for 4 and 8 bytes; 12-byte ones as in fused_output.hip (64 -> 192 @36x36 batch 74
-    // with it 1.44 times as long, 0.89 where V and y are 106 MB)
-    auto kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, true>;
+    // Streaming hint for rows of 12 bytes as in fused_output.hip, in images of three tiles or more (80 -> 128 5x5 @13x19 batch 1852, V and y 259 MB,
+    // 366 us with it, 389 without; 72 -> 161 @4x6 batch 14517, 277 MB, 457 / 218).  Shorter rows never: 128 -> 256 @3x4 batch 7006 F(4,3)
+    // 210 us with it, 87 without.  (Pooled rows of m = 6 leave value by value, without it.)
+    auto kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, false>;
     if constexpr (M == 6) {
         constexpr size_t kCacheBytes = (size_t)256 << 20;
-        if (co_v_bytes(g) + (size_t)g.N * g.K * g.H * g.W * sizeof(f16) <= kCacheBytes) kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, false>;
+        if (g.W > 2 * M && co_v_bytes(g) + (size_t)g.N * g.K * g.H * g.W * sizeof(f16) > kCacheBytes) kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, true>;
     }
     constexpr int LDS = S * 4 * (WT + WK) * 1024;
     static_assert(LDS * OCC <= 160 * 1024, "LDS of the workgroups of a compute unit");

@@ -344,8 +344,8 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 //   one kernel        2 + rounds * (turns * kTurn + kOnce), rounds = workgroups per compute unit, turns = blocks of input channels
 //                     (n = 4, where several workgroups share a compute unit: at least 3 + turns * 1.3, binary32 1.0, the serial chain; 16 tiles in
 //                     binary32 3 + turns / 2 + workgroups per compute unit, not rounded, * (0.7 turns + 0.55))
-//                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows leave
-//                     element by element (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
+//                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows left
+//                     element by element when this was fitted and leave in pieces of 4, 2 and 1 now (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
 //   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
 //   twice the         the same with their own times (n = 4: at least 5 + turns * 1.7, binary32 3.9 + turns * 1.35; binary16 up to four turns, with more
 //   channels          0.88 times as fast), taken below 0.94 of the estimate without.  600 layers of 200 to 16000 tiles in binary16: 80 run otherwise

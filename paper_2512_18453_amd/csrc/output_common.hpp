@@ -175,7 +175,8 @@ __device__ __forceinline__ void store_row(T *dst, const T (&v)[COUNT])
 }
 #undef NOVA_STORE
 
-// The first `left` of COUNT elements (COUNT <= 8)
+// The first `left` of COUNT elements (COUNT <= 8).  Rows cut off at the right edge leave this way from every kernel: element by element, four or five
+// of six columns took up to half of a call (5 -> 350 @6x4 batch 1004 F(6,3) 61 us through contract_output.hip, 33 through LDS)
 template <typename T, int COUNT>
 __device__ __forceinline__ void store_row_part(T *dst, const T (&v)[COUNT], int left)
 {
@@ -382,9 +383,7 @@ __device__ __forceinline__ void store_tile_rows(const T (&out)[ROWS][M], T *plan
             if (w0 + M <= W) {
                 store_row<T, M, NT>(at + (long long)p * W, out[p]);
             } else {
-#pragma unroll
-                for (int s = 0; s < M; ++s)
-                    if (w0 + s < W) at[(long long)p * W + s] = out[p][s];
+                store_row_part<T, M>(at + (long long)p * W, out[p], W - w0);
             }
         }
     }
@@ -423,13 +422,7 @@ struct TileRowsInLds {
             f16 v[M];
             __builtin_memcpy(v, __builtin_assume_aligned(block + (c * TILES + tile) * PITCH + row * M, ALIGN), M * 2);
             f16 *to = y + (((long long)img * K + k0 + c) * H + h) * W + w0;
-            if (left >= M) {
-                store_row<f16, M>(to, v);
-            } else {
-#pragma unroll
-                for (int q = 0; q < M - 1; ++q)
-                    if (q < left) to[q] = v[q];
-            }
+            store_row_part<f16, M>(to, v, left);
         }
     }
 };
