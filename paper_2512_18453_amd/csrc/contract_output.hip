@@ -288,10 +288,12 @@ static int launch_co_chunks(const nova_transforms *t, const void *U, const void 
     const int k_groups = g.Kp / (16 * WK);
     const long long blocks = (g.T + 16 * WT - 1) / (16 * WT) * k_groups;
     if (blocks <= 0 || blocks > 0x7fffffffLL || g.c_blocks > 2 * CHUNKS) return (int)hipErrorInvalidValue;
-    // Results through LDS: time of the call with it against rows straight from registers, 200 layers of 2 to 40 columns: m = 6 one tile
-    // wide 1.0 to 2.7 times as fast, 7 and 8 columns 1.0, more 0.87 to 1.0; m = 4 where two or three columns of the last tile are
-    // left, up to 18 columns, 1.0 to 1.25, else 0.9 to 1.0; m = 2 0.92 to 1.0.
-    const bool narrow = !(flags & NOVA_FLAG_POOL2) && ((M == 6 && g.W <= 8) || (M == 4 && g.W % 4 >= 2 && g.W <= 18));
+    // Results through LDS only where rows from registers take two pieces each for the last tile (3 or 5 columns), in images of one or two tiles' width
+    // of whose tile rows more than half exist.  Time of the call with it / from registers, 700 layers: there 0.71 to 1.08 (m = 6, geometric
+    // mean 0.93), 0.75 to 1.03 (m = 4, 0.91); with half of the rows or fewer 1.0 to 1.45 (most of a tile's lanes have no row: 24 -> 60 @2x2
+    // batch 3205 F(6,3) 28.0 us / 21.2); other numbers of columns 1.0 to 1.3; wider images 1.0 to 1.3; m = 2 1.0 to 1.1.
+    const int last_columns = g.W - M * (g.tiles_w - 1);
+    const bool narrow = M > 2 && !(flags & NOVA_FLAG_POOL2) && g.tiles_w <= 2 && last_columns % 2 == 1 && last_columns >= 3 && 2 * g.H > M * g.tiles_h;
     // Streaming hint for rows of 12 bytes as in fused_output.hip, in images of three tiles or more (80 -> 128 5x5 @13x19 batch 1852, V and y 259 MB,
     // 366 us with it, 389 without; 72 -> 161 @4x6 batch 14517, 277 MB, 457 / 218).  Shorter rows never: 128 -> 256 @3x4 batch 7006 F(4,3)
     // 210 us with it, 87 without.  (Pooled rows of m = 6 leave value by value, without it.)
