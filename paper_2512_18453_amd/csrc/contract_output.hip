@@ -12,7 +12,9 @@
 // difference, a pair of columns' z the outputs in the same way (as in few_channels.hip).
 // Stages arrive in a ring of S in LDS, S - 1 ahead, by direct global->LDS loads (a wave loads one of the stage's positions and
 // blocks of 32 channels; rows of 64 bytes, XOR-swizzled by 16-byte piece, piece ^ (row / 2) % 4, for reads of 16 rows), one
-// barrier per stage.  The stages of a column are unrolled, so that every address is a base and an offset known before the loop.
+// barrier per stage.  The stages of a column are unrolled; a stage's addresses are those of its column and an offset.
+// Scratch per lane: 28 to 48 bytes (7 to 12 registers) with m = 6, none elsewhere; outside the stages, but for 5 x 5 with more than 64 input channels,
+// which store and read back 6 or 7 registers for each pair of columns (and wait for all of the ring then).
 // What bounds it: about 1000 clocks per stage with two workgroups per compute unit, of which their loads from L2 take 512, the vector
 // instructions 350; the rest is waiting -- barrier, fragment reads, matrix instructions one after the other.  128 -> 128 @112x112
 // batch 32 F(6,3), pooled: 106 us for 189 MB of V where contraction with columns and row transform took 163, whole call 237 -> 169.
@@ -89,19 +91,28 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
     // of the wave's operands from those of row 0 and channel block 0 of the column (32 bits: the launcher checks)
     constexpr int PER_COLUMN = STEPS * CHUNKS;
     const unsigned v_plane = (unsigned)Ttot * 64u, u_plane = (unsigned)Kp * 64u;
-    auto plane_of = [&](int q, int c) __attribute__((always_inline)) {
-        const int i = q == 0 ? my_pos * (N - 1) : 2 * q - 1 + my_pos;
-        const int cb = 2 * c + my_cb < c_blocks ? 2 * c + my_cb : c_blocks - 1;      // (an odd number of blocks: the last again)
-        return (unsigned)(i * N * c_blocks + cb);
+    const unsigned v_row = v_plane * (unsigned)(N * c_blocks), u_row = u_plane * (unsigned)(N * c_blocks);
+    const unsigned last_block = (unsigned)(2 * (CHUNKS - 1) + my_cb < c_blocks ? 2 * (CHUNKS - 1) + my_cb : c_blocks - 1);   // (an odd number of blocks: the last again)
+    auto offset_of = [&](int stage, unsigned row, unsigned plane) __attribute__((always_inline)) {
+        const int q = stage / CHUNKS, c = stage % CHUNKS;
+        return (unsigned)(q == 0 ? my_pos * (N - 1) : 2 * q - 1 + my_pos) * row + (c == CHUNKS - 1 ? last_block : (unsigned)(2 * c + my_cb)) * plane;
     };
-    unsigned v_stage[PER_COLUMN], u_stage[PER_COLUMN];
+    // Kept in a table; for m = 6 with more than 64 input channels, 16 to 30 scalars too many beside the others (47 to 127 scalar spills), each is worked
+    // out when its loads are issued: 1.02 (F(6,3)) to 1.05 times as fast (F(6,5) up to 192 channels), elsewhere 0.98 to 1.0.
+    constexpr bool TABLE = M < 6 || CHUNKS == 1;
+    unsigned v_stage[TABLE ? PER_COLUMN : 1], u_stage[TABLE ? PER_COLUMN : 1];
+    if constexpr (TABLE) {
 #pragma unroll
-    for (int q = 0; q < STEPS; ++q)
-#pragma unroll
-        for (int c = 0; c < CHUNKS; ++c) {
-            v_stage[q * CHUNKS + c] = (unsigned)__builtin_amdgcn_readfirstlane((int)(plane_of(q, c) * v_plane));
-            u_stage[q * CHUNKS + c] = (unsigned)__builtin_amdgcn_readfirstlane((int)(plane_of(q, c) * u_plane));
+        for (int s = 0; s < PER_COLUMN; ++s) {
+            v_stage[s] = (unsigned)__builtin_amdgcn_readfirstlane((int)offset_of(s, v_row, v_plane));
+            u_stage[s] = (unsigned)__builtin_amdgcn_readfirstlane((int)offset_of(s, u_row, u_plane));
         }
+    }
+    auto stage_offset = [&](const unsigned *table, int s, unsigned row, unsigned plane) __attribute__((always_inline)) {
+        if constexpr (TABLE) return table[s];
+        asm volatile("" : "+s"(row), "+s"(plane));             // (not moved out of the loop over columns: the table again)
+        return offset_of(s, row, plane);
+    };
     const char *v_first = uniform_pointer(reinterpret_cast<const char *>(V) + (size_t)t0 * 64u), *u_first = uniform_pointer(reinterpret_cast<const char *>(U) + (size_t)k0 * 64u);
     const unsigned v_column = v_plane * (unsigned)c_blocks, u_column = u_plane * (unsigned)c_blocks;      // from one column to the next
     const char *v_col = v_first + (size_t)(N - 1) * v_column, *u_col = u_first + (size_t)(N - 1) * u_column;        // of the column loaded now
@@ -109,7 +120,7 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
     const unsigned my_lds = (unsigned)__builtin_amdgcn_readfirstlane((int)(lds_base + (unsigned)(wave * PLANE)));
     // stage `s` of its column to place `slot`; past the last column its stages again, so that the wait counts are constants
     auto issue = [&](int s, int slot) __attribute__((always_inline)) {
-        co_loads(v_col + v_stage[s], v_off, u_col + u_stage[s], u_off, my_lds + (unsigned)(slot * STAGE));
+        co_loads(v_col + stage_offset(v_stage, s, v_row, v_plane), v_off, u_col + stage_offset(u_stage, s, u_row, u_plane), u_off, my_lds + (unsigned)(slot * STAGE));
         if (s == PER_COLUMN - 1) {
             --columns_left;
             const bool first = columns_left == N - 1, more = columns_left > 0;
