@@ -378,11 +378,16 @@ LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, s
     double best = lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes;
     if (!half) best += 11e-9 * 2.0 * g.n * g.n * (double)g.T * g.C * g.Kp;
     best *= best < 30.0 ? 0.94 : 0.85;
-    // Where contraction and output transform would run as one kernel (contract_output.hip) domain_bytes is V alone; only n = 6 was timed
-    // against it: what its stages, 64 input channels each, add.  (96 -> 128 @39x39 batch 16 F(4,3) 22.9 / 18.3 us, 48 -> 64 5x5 @25x25 batch 22 21.5 / 12.7.)
+    // Where contraction and output transform would run as one kernel (contract_output.hip) domain_bytes is V alone; n = 6 and 4 were timed
+    // against it.  n = 6: what its stages, 64 input channels each, add.  (96 -> 128 @39x39 batch 16 F(4,3) 22.9 / 18.3 us, 48 -> 64 5x5 @25x25
+    // batch 22 21.5 / 12.7.)  n = 4: 7.6 + 0.3 per 1000 tiles and block of input channels + 1.5 + 2.75 per block for 1000 of its workgroups + 1.5
+    // per million tiles x output channels (sd 10 %, 207 layers); one kernel below 0.87 of that (of 500 layers 43 that would run there run as one
+    // kernel, 1.19 times as fast, the slowest 0.93: 64 -> 64 @23x24 batch 71 21.4 / 15.9, 48 -> 33 @2x6 batch 2309 17.0 / 10.3).
     if (contract_output) {
-        if (!half || g.n != 6) return {0, 0};
-        best = 0.85 * (lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes + 1.5 * ((g.c_blocks + 1) / 2));
+        if (!half || g.n > 6) return {0, 0};
+        const double groups = 1e-3 * (double)((g.T + 31) / 32 * g.k_blocks);
+        best = g.n == 6 ? 0.85 * (lt.stages + lt.per_mb * 1e-6 * (double)domain_bytes + 1.5 * ((g.c_blocks + 1) / 2))
+                        : 0.87 * (7.6 + 0.3e-3 * (double)g.T * g.c_blocks + groups * (1.5 + 2.75 * g.c_blocks) + 1.5e-6 * (double)g.T * g.K);
     }
     const double cut = std::max(0.0, (double)g.N * g.K * g.H * (g.W % g.m) - 2e6);
     const int channels = half && g.n < 10 ? 32 : 16;
