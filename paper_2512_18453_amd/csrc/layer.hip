@@ -347,7 +347,7 @@ static int launch_layer_n(const nova_transforms *t, const void *x, const void *U
 //                     + 3 per million results beyond the first two million that lie in tiles cut off at the right edge, whose rows left
 //                     element by element when this was fitted and leave in pieces of 4, 2 and 1 now (6 -> 166 @128x5 batch 159 F(6,3), 17 million: 121 in one kernel, 70 apart)
 //   separate kernels  kStages + kPerMB for each MB of V and M (or what is left of M) + 11 per GFLOP in binary32
-//   twice the         the same with their own times (n = 4: at least 5 + turns * 1.7, binary32 3.9 + turns * 1.35; binary16 up to four turns, with more
+//   twice the         the same with their own times (n = 4: at least 6 + turns * 1.9, binary32 3.9 + turns * 1.35; binary16 up to four turns, with more
 //   channels          0.88 times as fast), taken below 0.94 of the estimate without.  600 layers of 200 to 16000 tiles in binary16: 80 run otherwise
 //                     than before, 1.2 times as fast in the geometric mean, the slowest 0.92
 // Fitted to 2600 layers of 1 to 12000 tiles, 5 to 520 -> 1 to 520 channels, timed both ways on one MI355X (sd 6-13 %, one kernel n = 4
@@ -406,7 +406,7 @@ LayerShape layer_shape(const nova_transforms *t, const Geometry &g, int dtype, s
         static const LayerTimes kWideHalf[] = {{{0, 1.15}, {0, 1.9}, 0, 0}, {{0, 3.5}, {0, 5.3}, 0, 0}}, kWideFull[] = {{{0, 1.3}, {0, 0.9}, 0, 0}, {{0, 3.15}, {0, 3.6}, 0, 0}};
         const LayerTimes &wide = (half ? kWideHalf : kWideFull)[g.n / 2 - 2];
         double time = 2.0 + rounds_of(16, ceil_div(g.K, 2 * channels)) * (turns * wide.turn[1] + wide.once[1]);
-        if (g.n == 4) time = std::max(time, half ? 5.0 + turns * 1.7 : 3.9 + turns * 1.35);
+        if (g.n == 4) time = std::max(time, half ? 6.0 + turns * 1.9 : 3.9 + turns * 1.35);
         time += 3e-6 * cut;
         if (time < best * (shape.tiles ? 0.94 : 1.0)) shape = {16, 2 * channels};
     }
