@@ -139,6 +139,8 @@ struct OutShape {
     int k_pitch;      // LDS elements per channel
     int images;       // images per group (of which it takes all tiles then), in LDS one behind the other like further channels
     int batch;        // images of the call
+    int pieces;       // kStoreFlat: 16-byte pieces that can touch one channel's run of rows * W elements
+    unsigned piece_magic, w_magic;                 // ceil(2^32 / d) for d = pieces, W
     unsigned rows_magic, line_magic;               // ceil(2^32 / d) for d = rows, pieces of a row (0 for 1)
     int pool;         // 1: 2 x 2 max-pool while storing (H, W even)
     unsigned half_rows_magic;                      // ceil(2^32 / (rows / 2)), rows / 2 >= 2
@@ -208,18 +210,23 @@ __device__ __forceinline__ void store_row_part(T *dst, const T (&v)[COUNT], int 
     if (left & 1) dst[0] = rest[0];
 }
 // How the block leaves LDS.
-//   kStoreRows    a tile's row of M elements per thread, the tiles of an image row in neighbouring lanes: any W, any group, any alignment
+//   kStoreRows    a piece of an image row per thread (kRowPiece elements), neighbouring pieces in neighbouring lanes: any W, any group, any alignment
 //   kStoreVec     W (and the group width) a multiple of a 16-byte piece, y 16-byte aligned: whole aligned pieces
-enum { kStoreRows = 0, kStoreVec = 1 };
-// Elements that a thread takes at a time (F(6,r) in binary32: a row as 16 + 8 bytes per lane 0.82 to 1.2 times as fast as 16-byte pieces,
-// two threads of 12 bytes 0.92 to 1.25)
-template <typename T, int M> constexpr int kRowPiece = sizeof(T) == 4 && M == 6 ? 3 : M;
+//   kStoreFlat    the group spans the image width and y is 16-byte aligned: the rows of one channel are one contiguous run of y, written in
+//                 aligned 16-byte pieces, gathered element by element, whatever W is (element stores at its two ends)
+enum { kStoreRows = 0, kStoreVec = 1, kStoreFlat = 2 };
+// Elements of a piece, a whole number of which the row pitch of the LDS block is: a tile's row, but four of m = 6 in binary32 (12-byte pieces 0.95 times
+// as fast, 400 widths) and of m = 2 in binary16 (a tile's row there, 4 bytes, 0.97 with M in binary32, 0.95 in binary16).
+template <typename T, int M> constexpr int kRowPiece = (sizeof(T) == 4 && M == 6) || (sizeof(T) == 2 && M == 2) ? 4 : M;
 
-// kStoreRows was two ways: element by element, or, where a group spans the width, a channel's rows as one run of aligned 16-byte pieces
-// gathered element by element (100 instructions a piece).  The output transform alone, 270 widths that are no whole number of pieces,
-// their time against this one's: binary16 1.1 to 1.3 (up to 1.7 in wide images; F(2,3) on binary16 products 0.9 to 1.3), binary32
-// 1.05 to 1.15 (F(6,3) @50 columns 0.92).  512 ch @7x7 batch 256 F(8,3) 18.4 -> 16.6 us, 256 ch @14x14 with
-// products in binary16 23.6 -> 19.1.  With the streaming hint F(2,r) and F(4,r) 0.8 to 1.0, others the same.
+// Rows against the ways before them (kStoreFlat where a group spans the width, else element by element), the output transform alone, their time against
+// rows: binary16 1.0 to 1.45 (spanning) and 1.0 to 1.9, products in binary16 0.95 to 1.8; binary32 0.8 to 1.4 and 1.0 to 1.6.  Flat stays for binary32
+// where it is the faster one: M and y of 64 MB or more, which memory and not the instructions of a piece bind, with two or three columns in the last tile
+// (m = 4: 0.91 to 1.06; one column 0.98 to 1.12), any number (m = 6: 0.84 to 1.08) or six and seven (m = 8, two tiles or more: 0.77 to 0.99; fewer 0.97
+// to 1.18); images of one tile with at most half of its rows (m = 6 and 8: 0.79 to 1.0, with more 0.9 to 1.2).  64 ch @50x50 batch 48 F(6,3) 23.4 us in
+// rows, 19.9 flat; 8 -> 350 @14x11 batch 350 F(4,3), whole call, 122 and 105.  Not F(2,r) (1.0 to 1.35), F(4,5) (0.96 to 1.2), nor F(8,3) of at most
+// four input channels (1.0 to 1.3).
+template <typename T, int M, int N> constexpr bool kFlat32 = sizeof(T) == 4 && M >= 4 && !(M == 4 && N == 8);
 
 // The [32 channels][rows][columns] block of a group, staged in LDS (channel pitch sh.k_pitch, row pitch
 // sh.cols_pitch), to y [N][K][H][W] (or its 2 x 2 max-pooled form): lanes along W.  Called by all
@@ -313,9 +320,49 @@ __device__ __forceinline__ void store_output_block(const T *lds, T *__restrict__
             u32x4 *dst = reinterpret_cast<u32x4 *>(y + (((size_t)img * K + k) * H + h) * W + w0 + q * PE);
             __builtin_nontemporal_store(u32x4{lo.x, lo.y, hi.x, hi.y}, dst);    // y is not read again by this call
         }
+    } else if constexpr (STG == kStoreFlat) {
+        // the group spans the width: rows h0 .. h1-1 of one channel are one run of y
+        const int h0 = tr * M;
+        int h1 = h0 + sh.rows; if (h1 > H) h1 = H;
+        const int run = (h1 - h0) * W;
+        const int slots = kChanBlock * sh.pieces;
+        for (int s = threadIdx.x; s < slots; s += (int)blockDim.x) {
+            const int kk = (int)__umulhi((unsigned)s, sh.piece_magic);
+            const int kq = s - kk * sh.pieces;
+            const int k = kb * kChanBlock + kk;
+            if (k >= K) continue;
+            const long long e0 = (((long long)img * K + k) * H + h0) * W;         // first element of the run
+            const long long p0 = (e0 & ~(long long)(PE - 1)) + (long long)kq * PE;   // piece, aligned in y
+            const int rel = (int)(p0 - e0);                                        // -(PE-1) .. run-1 if needed
+            if (rel >= run) continue;
+            // (row, column) of the piece's first element inside the run, then step along it
+            const int q = rel < 0 ? 0 : rel;
+            int hr = (int)__umulhi((unsigned)q, sh.w_magic);
+            int w = q - hr * W;
+            const T *src = lds + kk * sh.k_pitch;
+            T val[PE];
+#pragma unroll
+            for (int e = 0; e < PE; ++e) {
+                const int pos = rel + e;
+                val[e] = (T)0.0f;
+                if (pos >= 0 && pos < run) {
+                    val[e] = src[hr * sh.cols_pitch + w];
+                    if (++w == W) { w = 0; ++hr; }
+                }
+            }
+            if (rel >= 0 && rel + PE <= run) {
+                u32x4 piece;
+                __builtin_memcpy(&piece, val, 16);
+                __builtin_nontemporal_store(piece, reinterpret_cast<u32x4 *>(y + p0));
+            } else {
+#pragma unroll
+                for (int e = 0; e < PE; ++e)
+                    if (rel + e >= 0 && rel + e < run) y[p0 + e] = val[e];
+            }
+        }
     } else {
         constexpr int P = kRowPiece<T, M>;
-        const int per_line = sh.twc * (M / P);
+        const int per_line = (sh.twc * M + P - 1) / P;
         const int slots = sh.images * kChanBlock * sh.rows * per_line;
         for (int s = threadIdx.x; s < slots; s += (int)blockDim.x) {
             const int line = per_line > 1 ? (int)__umulhi((unsigned)s, sh.line_magic) : s;
@@ -453,7 +500,8 @@ static size_t out_shape(int twb, int trb, OutShape &sh)
     // writing one (row, column) fall into different banks
     if ((kp / 4) % 2 == 0) kp += 4;
     sh.k_pitch = kp;
-    const int per_line = twb * (M / kRowPiece<T, M>);
+    const int per_line = (twb * M + kRowPiece<T, M> - 1) / kRowPiece<T, M>;
+    sh.pieces = 1; sh.piece_magic = 0; sh.w_magic = 0;
     sh.line_magic = per_line > 1 ? (unsigned)((((unsigned long long)1 << 32) + per_line - 1) / per_line) : 0;
     sh.images = 1;
     sh.pool = 0;

@@ -261,10 +261,26 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     const bool vec = g.W % PE == 0 && aligned && (sh.groups == 1 || (twb * M) % PE == 0);
     sh.pool = (flags & NOVA_FLAG_POOL2) ? 1 : 0;
     sh.batch = g.N;
+    // (binary32, memory-bound or hardly any rows: kFlat32 says with what times)
+    constexpr bool FLAT = kFlat32<T, M, N> && (CF == 0 || M < 8);
+    bool flat = false;
+    if constexpr (FLAT) {
+        const size_t bytes = (CF > 0 ? 0 : (size_t)N * N * g.k_blocks * (size_t)g.T * kChanBlock * sizeof(MT)) + (size_t)g.N * g.K * g.H * g.W * sizeof(T);
+        const bool ragged = M == 4 ? g.W % M >= 2 : M == 6 || (g.W % M >= 6 && g.tiles_w > 1);
+        const bool few_rows = M >= 6 && g.tiles_h * g.tiles_w == 1 && 2 * g.H <= M;
+        // (W >= 2 and at least two pieces: the reciprocals used for the divisions do not exist for 1)
+        flat = !vec && !sh.pool && aligned && sh.groups == 1 && g.W >= 2 && sh.rows * g.W + 2 * (PE - 1) >= 2 * PE &&
+               (long long)sh.rows * g.W < (1 << 15) && ((ragged && bytes >= ((size_t)64 << 20)) || few_rows);
+        if (flat) {
+            sh.pieces = (sh.rows * g.W + 2 * (PE - 1)) / PE;
+            sh.piece_magic = (unsigned)((((unsigned long long)1 << 32) + sh.pieces - 1) / sh.pieces);
+            sh.w_magic = (unsigned)((((unsigned long long)1 << 32) + g.W - 1) / g.W);
+        }
+    }
     // Images of one to four tiles: several to a group, up to 8 tiles (a tile by itself leaves half of its wave idle).  512 ch @7x7 batch 256 F(8,3) 16.6 us
     // with one image, 15.8 with two, 15.2 with four, 15.1 with eight; 256 ch @14x14 with products in binary16 19.1 with one, 18.4 with two.
     constexpr int kGroupTiles = 8;
-    if (CF == 0 && !sh.pool && !vec && sh.twb == g.tiles_h * g.tiles_w && sh.twb <= kGroupTiles / 2) {
+    if (CF == 0 && !sh.pool && !vec && !flat && sh.twb == g.tiles_h * g.tiles_w && sh.twb <= kGroupTiles / 2) {
         sh.images = kGroupTiles / sh.twb;
         if (sh.images > g.N) sh.images = g.N;
         while (sh.images > 1 && sh.images * lds_bytes > 64 * 1024) --sh.images;
@@ -276,6 +292,9 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     const bool relu = (flags & NOVA_FLAG_RELU) != 0;
     auto pick = [&](auto sym) {
         constexpr bool S = decltype(sym)::value;
+        if constexpr (FLAT) {
+            if (flat) return relu ? output_transform_kernel<N, R, T, MT, S, kStoreFlat, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreFlat, false, CF, COLUMNS_DONE>;
+        }
         if (vec) return relu ? output_transform_kernel<N, R, T, MT, S, kStoreVec, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreVec, false, CF, COLUMNS_DONE>;
         return relu ? output_transform_kernel<N, R, T, MT, S, kStoreRows, true, CF, COLUMNS_DONE> : output_transform_kernel<N, R, T, MT, S, kStoreRows, false, CF, COLUMNS_DONE>;
     };

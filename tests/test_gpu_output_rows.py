@@ -4,6 +4,7 @@ evaluated in binary64 on the M the kernel was given, with what lies around y unt
 import pytest
 import torch
 
+from launches import launches
 from paper_2512_18453_amd import nova, synth
 
 pytestmark = pytest.mark.gpu
@@ -14,6 +15,26 @@ DEV = "cuda:0"
 CASES = [(m, r, shape) for m, r in ((2, 3), (4, 3), (6, 3), (8, 3), (2, 5), (4, 5), (6, 5))
          for shape in [(3, 33, m + 1, 2 * m + rest) for rest in range(1, m)] + [(9, 5, m - 1, m - 1), (7, 40, m, m + 1), (5, 3, 2 * m - 1, 2 * m - 1),
                                                                                (2, 33, 3, 16 * m + 1)]]
+
+# binary32 whose rows of a channel leave as one run (2) or piece by piece (0): M and y of 64 MB or more by the columns in the last tile, images of one
+# tile with few rows and with more, a channel block that is not full
+RUNS = [(4, 3, (60, 100, 43, 42), 2), (4, 3, (60, 100, 43, 41), 0), (4, 3, (58, 96, 30, 31), 2), (6, 3, (48, 64, 50, 50), 2), (6, 3, (20, 64, 50, 50), 0), (6, 5, (80, 65, 26, 26), 2),
+        (8, 3, (512, 64, 15, 15), 2), (8, 3, (512, 64, 15, 13), 0), (6, 3, (40, 33, 3, 5), 2), (6, 3, (40, 33, 4, 5), 0), (8, 3, (40, 33, 4, 7), 2), (8, 3, (9, 40, 5, 7), 0),
+        (6, 5, (9, 5, 2, 3), 2), (2, 3, (9, 5, 2, 3), 0)]
+CASES += [(m, r, shape) for m, r, shape, way in RUNS if way == 2]
+
+
+@pytest.mark.parametrize("m,r,shape,way", RUNS)
+def test_way_of_binary32(m, r, shape, way):
+    N, K, H, W = shape
+    size = m + r - 3
+    t = nova.nova_make_transforms(synth.point_set("standard" if size == 2 else "nova", size), m, r)
+    M = torch.zeros(nova.nova_product_bytes(N, K, H, W, m, nova.NOVA_F32, 0, r) // 4, device=DEV)
+    around = torch.empty(N * K * H * W + 4, device=DEV)
+    for shift in (0, 1):
+        y = around[shift:shift + N * K * H * W].view(N, K, H, W)
+        name = launches(lambda: nova.nova_output_transform(t, M, N, K, H, W, torch.float32, 0, y=y))[0][0]
+        assert name.startswith(f"output_transform_kernel<{t.n}, {r}, float, float, 1, {0 if shift else way},"), name
 
 
 @pytest.mark.parametrize("m,r,shape", CASES)
