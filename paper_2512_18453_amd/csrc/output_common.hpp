@@ -221,12 +221,13 @@ template <typename T, int M> constexpr int kRowPiece = (sizeof(T) == 4 && M == 6
 
 // Rows against the ways before them (kStoreFlat where a group spans the width, else element by element), the output transform alone, their time against
 // rows: binary16 1.0 to 1.45 (spanning) and 1.0 to 1.9, products in binary16 0.95 to 1.8; binary32 0.8 to 1.4 and 1.0 to 1.6.  Flat stays for binary32
-// where it is the faster one: M and y of 64 MB or more, which memory and not the instructions of a piece bind, with two or three columns in the last tile
-// (m = 4: 0.91 to 1.06; one column 0.98 to 1.12), any number (m = 6: 0.84 to 1.08) or six and seven (m = 8, two tiles or more: 0.77 to 0.99; fewer 0.97
-// to 1.18); images of one tile with at most half of its rows (m = 6 and 8: 0.79 to 1.0, with more 0.9 to 1.2).  64 ch @50x50 batch 48 F(6,3) 23.4 us in
-// rows, 19.9 flat; 8 -> 350 @14x11 batch 350 F(4,3), whole call, 122 and 105.  Not F(2,r) (1.0 to 1.35), F(4,5) (0.96 to 1.2), nor F(8,3) of at most
-// four input channels (1.0 to 1.3).
-template <typename T, int M, int N> constexpr bool kFlat32 = sizeof(T) == 4 && M >= 4 && !(M == 4 && N == 8);
+// where it is the faster one:
+//   M and y of 192 MB or more, most of the last-level cache, past which its stores go.  Whole calls, 470 layers of 40 to 500 MB of M, flat over rows: up to
+//   128 MB 1.01, 192 1.0, 256 0.88 to 1.05 (0.97), more 0.80 to 1.0 (0.90).  8 -> 350 @14x11 batch 350 F(4,3) 122 us in rows, 105 flat.
+//   64 MB or more and a last tile of two or three columns (F(4,3)), any number (m = 6) or six and seven (m = 8, two tiles or more), where the transform
+//   alone takes 0.77 to 1.06 (other numbers 0.97 to 1.2) and the whole call 1.0 to 1.02: 64 ch @50x50 batch 48 F(6,3) 23.4 and 19.9.
+//   Images of one tile with at most half of its rows (m = 6 and 8: 0.79 to 1.0, with more 0.9 to 1.2).
+//   Not F(8,3) of at most four input channels (1.0 to 1.3).
 
 // The [32 channels][rows][columns] block of a group, staged in LDS (channel pitch sh.k_pitch, row pitch
 // sh.cols_pitch), to y [N][K][H][W] (or its 2 x 2 max-pooled form): lanes along W.  Called by all

@@ -261,16 +261,16 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
     const bool vec = g.W % PE == 0 && aligned && (sh.groups == 1 || (twb * M) % PE == 0);
     sh.pool = (flags & NOVA_FLAG_POOL2) ? 1 : 0;
     sh.batch = g.N;
-    // (binary32, memory-bound or hardly any rows: kFlat32 says with what times)
-    constexpr bool FLAT = kFlat32<T, M, N> && (CF == 0 || M < 8);
+    // (binary32, memory-bound or hardly any rows: output_common.hpp has the times)
+    constexpr bool FLAT = sizeof(T) == 4 && (CF == 0 || M < 8);
     bool flat = false;
     if constexpr (FLAT) {
         const size_t bytes = (CF > 0 ? 0 : (size_t)N * N * g.k_blocks * (size_t)g.T * kChanBlock * sizeof(MT)) + (size_t)g.N * g.K * g.H * g.W * sizeof(T);
-        const bool ragged = M == 4 ? g.W % M >= 2 : M == 6 || (g.W % M >= 6 && g.tiles_w > 1);
+        const bool ragged = (M == 4 && N == 6 && g.W % M >= 2) || M == 6 || (M == 8 && g.W % M >= 6 && g.tiles_w > 1);
         const bool few_rows = M >= 6 && g.tiles_h * g.tiles_w == 1 && 2 * g.H <= M;
         // (W >= 2 and at least two pieces: the reciprocals used for the divisions do not exist for 1)
         flat = !vec && !sh.pool && aligned && sh.groups == 1 && g.W >= 2 && sh.rows * g.W + 2 * (PE - 1) >= 2 * PE &&
-               (long long)sh.rows * g.W < (1 << 15) && ((ragged && bytes >= ((size_t)64 << 20)) || few_rows);
+               (long long)sh.rows * g.W < (1 << 15) && (bytes >= ((size_t)(ragged ? 64 : 192) << 20) || few_rows);
         if (flat) {
             sh.pieces = (sh.rows * g.W + 2 * (PE - 1)) / PE;
             sh.piece_magic = (unsigned)((((unsigned long long)1 << 32) + sh.pieces - 1) / sh.pieces);

@@ -16,11 +16,11 @@ CASES = [(m, r, shape) for m, r in ((2, 3), (4, 3), (6, 3), (8, 3), (2, 5), (4, 
          for shape in [(3, 33, m + 1, 2 * m + rest) for rest in range(1, m)] + [(9, 5, m - 1, m - 1), (7, 40, m, m + 1), (5, 3, 2 * m - 1, 2 * m - 1),
                                                                                (2, 33, 3, 16 * m + 1)]]
 
-# binary32 whose rows of a channel leave as one run (2) or piece by piece (0): M and y of 64 MB or more by the columns in the last tile, images of one
+# binary32 whose rows of a channel leave as one run (2) or piece by piece (0): M and y of 64 MB or more by the columns in the last tile, of 192, images of one
 # tile with few rows and with more, a channel block that is not full
 RUNS = [(4, 3, (60, 100, 43, 42), 2), (4, 3, (60, 100, 43, 41), 0), (4, 3, (58, 96, 30, 31), 2), (6, 3, (48, 64, 50, 50), 2), (6, 3, (20, 64, 50, 50), 0), (6, 5, (80, 65, 26, 26), 2),
         (8, 3, (512, 64, 15, 15), 2), (8, 3, (512, 64, 15, 13), 0), (6, 3, (40, 33, 3, 5), 2), (6, 3, (40, 33, 4, 5), 0), (8, 3, (40, 33, 4, 7), 2), (8, 3, (9, 40, 5, 7), 0),
-        (6, 5, (9, 5, 2, 3), 2), (2, 3, (9, 5, 2, 3), 0)]
+        (6, 5, (9, 5, 2, 3), 2), (2, 3, (9, 5, 2, 3), 0), (2, 3, (70, 160, 30, 31), 2), (4, 3, (92, 96, 41, 41), 2), (4, 5, (70, 96, 39, 39), 2)]
 CASES += [(m, r, shape) for m, r, shape, way in RUNS if way == 2]
 
 
