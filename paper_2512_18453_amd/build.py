@@ -23,9 +23,10 @@ SOURCES = ["transforms.cpp", "discovery.cpp", "api.cpp", "filter_transform.hip",
            "few_channels.hip"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall", "-Wno-unused-function"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# The first 64 bytes of a kernel's arguments -- pointers and sizes -- arrive in scalar registers with the launch instead of by a load that
-# every workgroup begins with: 13-layer stack on one image 185.6 -> 180 us (30 kernels of 5 us each).  Not where it measured otherwise: layer.hip
-# (registers: a variant with scratch gets more of it), output_transform.hip (256 -> 256 @56x56 F(8,3) batch 32 107.4 -> 108.1, the stack the same)
+# Up to 56 bytes of a kernel's arguments -- pointers and sizes, 14 of the 16 scalar registers that a launch can fill; two hold the argument pointer --
+# arrive with the launch instead of by a load that every workgroup begins with: 13-layer stack on one image (30 kernels of 5 us each) 185.6 -> 180 us
+# layer after layer on inputs that stay, 206 -> 202 as one call on inputs that change.  Not where it measured otherwise: layer.hip (registers: a variant
+# with scratch gets more of it), output_transform.hip (256 -> 256 @56x56 F(8,3) batch 32 107.4 -> 108.1, the stack the same)
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 NO_PRELOAD = ("layer.hip", "output_transform.hip")
 
@@ -39,11 +40,16 @@ def _newest_header():
 def _compile(name, force):
     src = os.path.join(SRC, name)
     obj = os.path.join(OBJ, name + ".o")
-    if (not force and os.path.exists(obj)
-            and os.path.getmtime(obj) > max(os.path.getmtime(src), _newest_header())):
-        return obj
     device = DEVICE + ([] if name in NO_PRELOAD else PRELOAD)
     cmd = ["hipcc"] + COMMON + (device if name.endswith(".hip") else []) + ["-c", src, "-o", obj]
+    # (the command that made an object lies beside it: other flags make it again)
+    made_by = obj + ".cmd"
+    if not force and os.path.exists(obj) and os.path.exists(made_by) and os.path.getmtime(obj) > max(os.path.getmtime(src), _newest_header()):
+        with open(made_by) as f:
+            if f.read() == "\n".join(cmd):
+                return obj
+    if os.path.exists(made_by):
+        os.remove(made_by)
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(ln for ln in res.stderr.splitlines() if noise not in ln)
@@ -51,6 +57,8 @@ def _compile(name, force):
         raise RuntimeError(f"hipcc failed on {name}:\n{err}")
     if err.strip():
         sys.stderr.write(err + "\n")
+    with open(made_by, "w") as f:
+        f.write("\n".join(cmd))
     return obj
 
 
