@@ -28,6 +28,7 @@ CASES_OF_16_TILES = [
     (2, 5, 11, 12, 33, 66, 5, F16), (2, 5, 7, 12, 16, 21, 53, F16), (2, 5, 7, 9, 33, 29, 18, F32), (2, 5, 9, 9, 17, 34, 13, F32),
     (6, 3, 11, 6, 33, 65, 51, F16), (6, 3, 17, 18, 48, 53, 37, F16), (6, 3, 17, 5, 64, 66, 14, F32), (6, 3, 13, 14, 96, 13, 49, F32),
     (4, 5, 5, 11, 33, 68, 49, F16), (4, 5, 19, 5, 17, 34, 51, F16), (4, 5, 17, 5, 64, 42, 9, F32), (4, 5, 15, 8, 33, 25, 25, F32),
+    (2, 3, 9, 5, 32, 90, 90, F16), (4, 3, 2, 256, 64, 121, 124, F16), (4, 3, 30, 8, 20, 75, 66, F16), (6, 3, 32, 70, 64, 44, 48, F16),
     (4, 5, 16, 48, 96, 35, 35, F16), (6, 3, 17, 64, 64, 50, 49, F16), (6, 3, 15, 64, 64, 51, 51, F16),
 ]
 # 64 input channels in binary16, 8 tiles, outputs transformed rows first
