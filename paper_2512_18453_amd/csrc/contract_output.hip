@@ -32,17 +32,6 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
-template <int I, int COUNT, typename F>
-__device__ __forceinline__ void static_for_from(F &&f)
-{
-    if constexpr (I < COUNT) {
-        f(std::integral_constant<int, I>{});
-        static_for_from<I + 1, COUNT>(f);
-    }
-}
-template <int COUNT, typename F>
-__device__ __forceinline__ void static_for(F &&f) { static_for_from<0, COUNT>(f); }
-
 // Four loads of 16 rows of 64 bytes, two from v and two from u, to four consecutive KiB of LDS
 __device__ __forceinline__ void co_loads(const void *v, const unsigned (&v_off)[2], const void *u, const unsigned (&u_off)[2], unsigned lds)
 {
@@ -56,16 +45,17 @@ __device__ __forceinline__ void co_loads(const void *v, const unsigned (&v_off)[
 
 static size_t co_v_bytes(const Geometry &g) { return (size_t)g.n * g.n * g.c_blocks * (size_t)g.T * kChanBlock * sizeof(f16); }
 
-// WT x WK waves of 16 tiles x 16 channels each; CHUNKS: stages of a pair of positions, 64 input channels each (an odd number of blocks of 32:
+// CHUNKS: stages of a pair of positions, 64 input channels each (an odd number of blocks of 32:
 // half of the last one is not used); OCC: workgroups per compute unit; HINT: streaming hint for the rows of y that leave from registers
-template <int N, int R, int WT, int WK, int CHUNKS, int S, int OCC, bool HINT>
-__global__ void __launch_bounds__(64 * WT * WK, (OCC * WT * WK + 3) / 4)
+constexpr int WT = 2, WK = 2;      // waves of a workgroup: WT x WK of 16 tiles x 16 channels each; a wave loads one (position, channel block) of a stage's four
+
+template <int N, int R, int CHUNKS, int S, int OCC, bool HINT>
+__global__ void __launch_bounds__(64 * WT * WK, OCC)
 contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16 *__restrict__ y, int K, int H, int W, int tiles_h,
                        int tiles_w, int Kp, int Ttot, int c_blocks, int k_groups, int flags, int narrow, OutCoef<N, R> coef)
 {
-    constexpr int M = N - R + 1, HP = (N - 2) / 2, STEPS = N / 2, WAVES = WT * WK, TILES = 16 * WT, CHANNELS = 16 * WK;
+    constexpr int M = N - R + 1, HP = (N - 2) / 2, STEPS = N / 2, TILES = 16 * WT, CHANNELS = 16 * WK;
     constexpr int PLANE = (TILES + CHANNELS) * 64, STAGE = 4 * PLANE;
-    static_assert(WAVES == 4 && WT == 2 && WK == 2, "a wave loads one (position, channel block) of a stage");
     extern __shared__ __align__(1024) unsigned char ring[];
     const unsigned lds_base = (unsigned)(size_t)((__attribute__((address_space(3))) void *)ring);
     const int lane = (int)(threadIdx.x & 63);
@@ -181,7 +171,7 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
             m[0] = next[0];
             m[1] = next[1];
         });
-        if constexpr (STEPS == 1) first(m); else pair(std::integral_constant<int, STEPS - 2>{}, m);
+        pair(std::integral_constant<int, STEPS - 2>{}, m);
     };
 
 #pragma unroll
@@ -257,7 +247,7 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
     };
     const int channel = wk * 16 + 4 * (lane >> 4);             // the lane's first, of the workgroup's
     if (narrow) {                                              // the results leave through LDS, 16 tiles at a time
-        static_assert(CHANNELS == TileRowsInLds<M>::CHANNELS && 64 * WAVES == 256 && TileRowsInLds<M>::BYTES <= S * STAGE, "block");
+        static_assert(CHANNELS == TileRowsInLds<M>::CHANNELS && 64 * WT * WK == 256 && TileRowsInLds<M>::BYTES <= S * STAGE, "block");
         f16 *block = reinterpret_cast<f16 *>(ring);
 #pragma unroll 1
         for (int part = 0; part < WT; ++part) {
@@ -293,7 +283,7 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
 template <int N, int R, int CHUNKS, int S, int OCC>
 static int launch_co_chunks(const nova_transforms *t, const void *U, const void *V, void *y, const Geometry &g, int flags, hipStream_t stream)
 {
-    constexpr int M = N - R + 1, WT = 2, WK = 2;
+    constexpr int M = N - R + 1;
     OutCoef<N, R> coef;
     fill_out_coef<N, R>(t, coef);
     const int k_groups = g.Kp / (16 * WK);
@@ -308,10 +298,10 @@ static int launch_co_chunks(const nova_transforms *t, const void *U, const void 
     // Streaming hint for rows of 12 bytes as in fused_output.hip, in images of three tiles or more (80 -> 128 5x5 @13x19 batch 1852, V and y 259 MB,
     // 366 us with it, 389 without; 72 -> 161 @4x6 batch 14517, 277 MB, 457 / 218).  Shorter rows never: 128 -> 256 @3x4 batch 7006 F(4,3)
     // 210 us with it, 87 without.  (Pooled rows of m = 6 leave value by value, without it.)
-    auto kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, false>;
+    auto kern = contract_output_kernel<N, R, CHUNKS, S, OCC, false>;
     if constexpr (M == 6) {
         constexpr size_t kCacheBytes = (size_t)256 << 20;
-        if (g.W > 2 * M && co_v_bytes(g) + (size_t)g.N * g.K * g.H * g.W * sizeof(f16) > kCacheBytes) kern = contract_output_kernel<N, R, WT, WK, CHUNKS, S, OCC, true>;
+        if (g.W > 2 * M && co_v_bytes(g) + (size_t)g.N * g.K * g.H * g.W * sizeof(f16) > kCacheBytes) kern = contract_output_kernel<N, R, CHUNKS, S, OCC, true>;
     }
     constexpr int LDS = S * 4 * (WT + WK) * 1024;
     static_assert(LDS * OCC <= 160 * 1024, "LDS of the workgroups of a compute unit");
@@ -330,7 +320,8 @@ static int launch_co_chunks(const nova_transforms *t, const void *U, const void 
 //   n = 6, r = 5   up to 130 0.55-0.9, from 136 on 1.0-1.4 (up to 128), 0.8-1.1 above
 //   n = 8, r = 5   up to 130 0.5-1.0, from 144 on 1.0-1.6 (up to 128), 0.8-1.1 above
 //   n = 10, r = 5  from 236 on 1.25-1.7 (up to 64), from 368 on 1.0-1.3 (up to 128), from 500 on 1.1-1.5 (up to 192), less below
-// One block of output channels 0.45-1.06: not taken.
+// One block of output channels 0.45-1.06: not taken.  (Workgroups on the whole chip, 256 compute units; partitions of it
+// were not timed.)
 struct CoRange { int max_blocks, workgroups[3]; };     // (up to 2 blocks of input channels, 4, more)
 static CoRange co_range(int n, int r)
 {

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "internal.hpp"
 
 namespace nova {
@@ -33,6 +35,18 @@ __device__ __forceinline__ f16 round_twice(float v, f16 *)
     asm volatile("" : "+v"(v));
     return (f16)v;
 }
+
+// f(0), f(1), .., f(COUNT - 1) with the index as a constant of the type
+template <int I, int COUNT, typename F>
+__device__ __forceinline__ void static_for_from(F &&f)
+{
+    if constexpr (I < COUNT) {
+        f(std::integral_constant<int, I>{});
+        static_for_from<I + 1, COUNT>(f);
+    }
+}
+template <int COUNT, typename F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_from<0, COUNT>(f); }
 
 __device__ __forceinline__ float fma32(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 

@@ -60,17 +60,6 @@ constexpr int kFusedCB = 2;            // blocks of 32 input channels
 // is otherwise free to drift to its first use, past the matrix instructions it is meant to sit between.
 __device__ __forceinline__ void stays_here(float &x) { asm volatile("" : "+v"(x)); }
 
-template <int I, int COUNT, typename F>
-__device__ __forceinline__ void static_for_from(F &&f)
-{
-    if constexpr (I < COUNT) {
-        f(std::integral_constant<int, I>{});
-        static_for_from<I + 1, COUNT>(f);
-    }
-}
-template <int COUNT, typename F>
-__device__ __forceinline__ void static_for(F &&f) { static_for_from<0, COUNT>(f); }
-
 // fold[d][p]: d = 0: (A[0][0], 0, ..., 0); d >= 1: the coefficients of the pair of points d (A[2d - 1][p])
 template <int N, int R>
 struct FoldCoef {

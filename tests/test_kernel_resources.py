@@ -49,8 +49,8 @@ def test_one_kernel_layers(tmp_path):
 
 
 def test_contraction_and_output_in_one_kernel(tmp_path):
-    # <n, r, waves over tiles, waves over channels, 64-channel stages, ring, workgroups per unit, streaming>
+    # <n, r, 64-channel stages, ring, workgroups per unit, streaming>
     scratch = {("8", "3", "1"): 32, ("8", "3", "2"): 28, ("10", "5", "1"): 48, ("10", "5", "2"): 36, ("10", "5", "3"): 40}
     for name, (registers, spilled) in resources("contract_output.hip", tmp_path).items():
-        n, r, _, _, chunks, _, per_unit = re.findall(r"[\w.]+", name)[1:8]
+        n, r, chunks, _, per_unit = re.findall(r"[\w.]+", name)[1:6]
         assert spilled <= scratch.get((n, r, chunks), 0) and registers <= (256 if per_unit == "2" else 168), name
