@@ -340,10 +340,13 @@ int nova_winograd_conv2d_int8(const nova_transforms *t, const void *x, const voi
  * NOVA_PATH_STAGES (input transform, contraction, output transform), NOVA_PATH_FEW_CHANNELS (at most 4
  * input channels: compact V, the products formed inside the output transform) or NOVA_PATH_FUSED_OUTPUT
  * (input transform, then the kernel above: taken wherever it is supported).  Negative: an error code.
- * The shape decides that much; the batch and the workspace decide two variants of these, with the same results bit for
+ * The shape decides that much; the batch and the workspace decide three variants of these, with the same results bit for
  * bit.  A call with little work runs the whole layer as one kernel and leaves its workspace as it was (with more than 4 input
- * channels).  NOVA_PATH_STAGES in binary16 with many products per slab: the contraction keeps, in the place of M, m of every n
- * of its planes with the columns of the output transform done, so that more images fit a slab.
+ * channels).  NOVA_PATH_STAGES in binary16 with products not kept in binary16, points in the paired order and tiles enough to fill the
+ * chip: up to 128 to 256 input channels by tile size contraction and output transform run as one kernel (the input transform, then that; no M,
+ * slabs of as many images as V of them fits the workspace and x and V together the last-level cache), not for F(8,3); otherwise, with
+ * many products per slab, the contraction keeps, in the place of M, m of every n of its planes with the columns of the output transform
+ * done, so that more images fit a slab.  Calls whose y overlaps x or U take only the last of the three.
  * Host only.
  */
 enum { NOVA_PATH_STAGES = 0, NOVA_PATH_FEW_CHANNELS = 1, NOVA_PATH_FUSED_OUTPUT = 2 };

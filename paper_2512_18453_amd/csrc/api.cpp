@@ -133,8 +133,9 @@ extern "C" int nova_input_transform(const nova_transforms *t, const void *x, voi
     if (!x || !V || !dims_ok(N, C, H, W, 1) || !dtype_ok(dtype)) return NOVA_EINVAL;
     const Geometry g = make_geometry(N, C, H, W, 1, t->m, t->r);
     if (V_bytes < v_bytes(g, dtype)) return NOVA_ENOSPC;
-    // (as the whole call decides; what follows is not known here: taken as for K = C.  With x and V from memory the
-    // hint does not cost the transform itself: 256 ch @56x56 batch 33 F(8,3) 36.9 us without, 34.7 with)
+    // (as a whole call of separate kernels decides, with what follows, which is not known here, taken as for K = C; a whole call that runs
+    // contraction and output as one kernel sizes its slabs so that x is not streamed.  With x and V from memory the hint does not cost the
+    // transform itself: 256 ch @56x56 batch 33 F(8,3) 36.9 us without, 34.7 with)
     const Geometry like = make_geometry(N, C, H, W, C, t->m, t->r);
     const size_t m_like = fused_contract_output_preferred(t, like, dtype, 0) ? 0 : m_bytes(like, dtype, 0);
     const bool stream_x = m_like > 0 && (size_t)N * C * H * W * dtype_size(dtype) + v_bytes(g, dtype) + m_like > kDefaultSlabBytes;

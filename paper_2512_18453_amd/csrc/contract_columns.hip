@@ -101,7 +101,10 @@ static int launch_columns_n(const nova_transforms *t, const void *U, const void 
     return launch_columns<N, R, 64, 64, 2, 2, 4, 2>(t, U, V, Z, g, s);
 }
 
-// Where the whole call runs this way (g: a slab).  A wave goes through n positions in turn where the separate contraction has
+// Where the whole call runs this way (g: a slab), once contract_output.hip has not taken the layer: F(8,3); F(6,3) and F(4,5) from 129, F(4,3) and F(6,5) from
+// 193 input channels on, F(2,5) from 129; fewer where the workgroups are too few for it (F(6,5) mostly); one block of output channels.  The rest of the
+// layers below -- all of F(2,3) -- come here only with a y that lies over x or U, which a kernel that writes y while others read U cannot serve:
+// there these figures are against the separate kernels.  A wave goes through n positions in turn where the separate contraction has
 // a wave for each, so there have to be tiles and output channels enough to fill the chip without them, and the fewer input
 // channels there are, the more of the time is M's.  Whole calls, separate kernels / this way, geometric means over 286
 // layers by n * n * T * K (1.5-6 / 6-15 / 15-30 / 30-60 / more millions) and blocks of 32 input channels:

@@ -228,7 +228,8 @@ static int launch_ot(const nova_transforms *t, const void *Mp, const void *few_u
         // of them, and without sharing a 64-byte sector between two workgroups if it is a whole number of
         // those; last groups narrower than the others leave lanes idle.  Taken: the evenly cut width or a
         // vectorisable one, by the lowest estimate of slots launched * (1 + 2 / width) * 1.2 for shared sectors
-        // * 1.3 for element stores.  us per launch, even
+        // * 1.3 for rows that leave piece by piece (fitted when they left element by element; with any factor from 1.0 to 1.5 the width
+        // taken is 1.05 to 1.15 times as slow as the best one, 119 widths, least with 1.0 to 1.1 for M in binary32, with 1.5 in binary16).  us per launch, even
         // cut / this rule: 64 ch @224x224 batch 4 F(6,3) 30.9 / 22.6, F(4,3) 34.7 / 27.4, 128 ch @96x96 batch 8 F(4,3)
         // 25.2 / 20.7.  (Pooled rows are a quarter of the bytes: 20.7 / 24.3, hence not for them.  Nor where the products are formed
         // here, 3 -> 64 @224x224 batch 32, whole call: binary32 F(8,3) 194 / 218, F(4,3) 145 / 148, binary16 with points in
