@@ -15,9 +15,11 @@
 // barrier per stage.  The stages of a column are unrolled; a stage's addresses are those of its column and an offset.
 // Scratch per lane: 28 to 48 bytes (7 to 12 registers) with m = 6, none elsewhere; outside the stages, but for 5 x 5 with more than 64 input channels,
 // which store and read back 6 or 7 registers for each pair of columns (and wait for all of the ring then).
-// What bounds it: about 1000 clocks per stage with two workgroups per compute unit, of which their loads from L2 take 512, the vector
-// instructions 350; the rest is waiting -- barrier, fragment reads, matrix instructions one after the other.  128 -> 128 @112x112
-// batch 32 F(6,3), pooled: 106 us for 189 MB of V where contraction with columns and row transform took 163, whole call 237 -> 169.
+// What bounds it: the units' time beside the waits.  64 stages, two workgroups per compute unit, 128 -> 128 @112x112 F(6,3), by counters: a
+// wave takes 908 clocks per stage, 258 of them at barriers and for loads, 296 until a unit takes its next instruction; the two waves of a SIMD
+// keep it busy with vector instructions for 287 clocks, scalar 232, matrix 128, and the loads of both workgroups take 512 at the 64 bytes per
+// clock of L2 (0.84 of them hit).  HBM: 136 MB read, 15 written in 48.5 us, 3.1 TB/s; no bank conflicts.  That layer, batch 32, pooled: 97 us for 189 MB
+// of V where contraction with columns and row transform took 152, whole call 231 -> 173.
 // Tried: all n^2 products in registers (each operand then read by one wave only, no barriers), transformed at the end through
 // LDS: 167 us, the transform's 70 of them beside nothing else; 8 waves with 32 x 64 per workgroup and compute unit, a quarter fewer
 // loads: 112, 156 against 139 for the whole call 128 -> 256 batch 16; rings of 3 and 5: 110, 108; n = 10 (M = 8) with the 256 outputs of a
@@ -88,7 +90,7 @@ contract_output_kernel(const f16 *__restrict__ U, const f16 *__restrict__ V, f16
         return (unsigned)(q == 0 ? my_pos * (N - 1) : 2 * q - 1 + my_pos) * row + (c == CHUNKS - 1 ? last_block : (unsigned)(2 * c + my_cb)) * plane;
     };
     // Kept in a table; for m = 6 with more than 64 input channels, 16 to 30 scalars too many beside the others (47 to 127 scalar spills), each is worked
-    // out when its loads are issued: 1.02 (F(6,3)) to 1.05 times as fast (F(6,5) up to 192 channels), elsewhere 0.98 to 1.0.
+    // out when its loads are issued: F(6,3) 1.01 to 1.03 times as fast, 0.99 to 1.0 with pooling; F(6,5) 1.0 to 1.05; elsewhere 0.98 to 1.0.
     constexpr bool TABLE = M < 6 || CHUNKS == 1;
     unsigned v_stage[TABLE ? PER_COLUMN : 1], u_stage[TABLE ? PER_COLUMN : 1];
     if constexpr (TABLE) {
